@@ -11,6 +11,28 @@ void set_error(const char* fmt, ...);
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+namespace dev {
+struct WeightTable;
+}
+// one grouped GEMM over the ragged rows of groups [g_begin, g_begin + ng) (ffn_gemm.hip)
+struct GroupedGemm {
+  const void* A;                    // rows, bf16, row stride lda
+  int lda;
+  const int* row_src;               // gate/up only: row r is A[row_src[r] / src_k, :], or null
+  int n_src_rows, src_k;
+  const int* offsets;
+  int g_begin, ng, R_cap;
+  int K, N;                         // contraction length and output columns (gate/up: of one matrix)
+  const dev::WeightTable* weights;  // row-major [K,N] matrices, row stride ldw
+  int ldw;
+  void* out;
+  int ldo;
+  void* aux;                        // gate/up: receives the derivatives p | q, or null
+  int ld_aux;
+};
+hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s);
+hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s);
+
 // backward-pass launchers (ffn_backward.hip), used by feplb_grouped_ffn_backward
 hipError_t launch_wgrad(const void* P, int ldp, int M, const void* Q, int ldq, int N, const int* offsets,
                         const int* order, int g_begin, int n_groups, int R_cap, void* const* c0, void* const* c1,

@@ -2,17 +2,16 @@
 // compute is a Grouped GEMM; Sections 1 and 2.3: its speed depends on each
 // expert's batch size and it must not fragment into per-expert launches).
 //
-// Two GEMM kernels, each ONE launch for a whole range of groups:
+// Forward: two grouped GEMMs, each ONE launch for a whole range of groups (ffn_gemm.hip):
 //   gate_up : H[r,:]  = bf16( silu(x_r Wg[g]) * (x_r Wu[g]) ),  x_r = Xp[r,:] or, with row_src,
 //             the token row X[row_src[r] / k, :] gathered while it is loaded
 //   down    : Yp[r,:] = H[r,:] Wd[g]
-// The same kernel serves training (Section 3.2 times the backward pass as well): the gate_up
-// form can also keep, for the backward pass, the two partial derivatives of its output with
-// respect to the products a = x Wg and b = x Wu,
-//   p = dH/da = b s (1 + a (1 - s)),   q = dH/db = a s,   s = sigmoid(a)        (bf16),
-// and two more forms give the input gradients,
+// The training form of gate_up also keeps, for the backward pass, the two partial derivatives of
+// its output with respect to the products a = x Wg and b = x Wu,
+//   p = dH/da = b s (1 + a (1 - s)),   q = dH/db = a s,   s = sigmoid(a)        (bf16).
+// The kernel in this file computes the input gradients (Section 3.2 times the backward pass as well):
 //   dswiglu : dH = dYp Wd^T, then [da | db] = [dH p | dH q], written over [p | q]
-//   plain   : dXp = [da | db] [Wg^T; Wu^T]   (the down form with another K)
+//   plain   : dXp = [da | db] [Wg^T; Wu^T]
 // with the transposed weights made by a small kernel of ffn_backward.hip, which also holds the
 // ragged weight-gradient GEMM.
 // A small schedule kernel turns offsets[] (device memory, ragged, possibly
@@ -634,16 +633,12 @@ int32_t forward_impl(const void* Xp, const int32_t* row_src, int32_t T, int32_t 
     FEPLB_LAUNCH_CHECK("ffn_schedule_kernel");
   }
   if (do_up) {
-    if (AB)
-      FEPLB_HIP((launch_gemm<0, true, true>(Xp, d, row_src, T, k, (const int4*)ws, d, f, f / 128, max_tiles, up_tab, H, f, s, AB, 2 * f)));
-    else
-      FEPLB_HIP((launch_gemm<0, true>(Xp, d, row_src, T, k, (const int4*)ws, d, f, f / 128, max_tiles, up_tab, H, f, s)));
+    const feplb::GroupedGemm a{Xp, d, row_src, T, k, offsets, g_begin, ng, R_cap, d, f, &up_tab, f, H, f, AB, 2 * f};
+    FEPLB_HIP(feplb::launch_gate_up(a, s));
   }
   if (do_down) {
-    if (yp_dtype == FEPLB_BF16)
-      FEPLB_HIP((launch_gemm<1, true>(H, f, nullptr, 0, 1, (const int4*)ws, f, d, d / 256, max_tiles, down_tab, Yp, d, s)));
-    else
-      FEPLB_HIP((launch_gemm<1, false>(H, f, nullptr, 0, 1, (const int4*)ws, f, d, d / 256, max_tiles, down_tab, Yp, d, s)));
+    const feplb::GroupedGemm a{H, f, nullptr, 0, 1, offsets, g_begin, ng, R_cap, f, d, &down_tab, d, Yp, d, nullptr, 0};
+    FEPLB_HIP(feplb::launch_plain_gemm(a, yp_dtype == FEPLB_BF16, s));
   }
   return FEPLB_OK;
 }

@@ -1,0 +1,263 @@
+// The grouped GEMM kernel: for every row r of a group g with rows in [offsets[g], offsets[g+1])
+//   MODE 0  gate/up:  H[r,:] = bf16( silu(x_r Wg[g]) * (x_r Wu[g]) ); with SAVE also the two derivatives p, q of that
+//           product with respect to its factors' products, bf16, in columns [0,N) and [N,2N) of `aux`
+//   MODE 1  plain:    out[r,:] = a_r W[g], fp32 or bf16
+// One launch covers a whole range of ragged groups; a workgroup finds its tile from offsets[] (device memory), so the
+// host never needs the number of rows: the grid covers an upper bound and surplus workgroups leave at once.
+// panel_gemm.h holds the main loop and the mapping of workgroups to tiles.
+//
+// Three tile shapes (rows x weight columns; for gate/up half of the columns are gate, half the matching up columns):
+//   256 x 256, 8 wavefronts, one workgroup per CU: the least operand traffic per flop, for shapes with several rounds
+//              of tiles per CU.  Two waves per SIMD cover each other's latencies, so a ragged tile may skip the MFMAs
+//              of its empty 32-row blocks (wave-uniform choice of a loop variant), which one wave per SIMD could not.
+//   128 x 256, 4 wavefronts, two workgroups per CU: one's prologue and epilogue hide behind the other's loop and half
+//              the rows are lost to rounding a group up, but operand traffic in LDS is 1.1x its bandwidth at full MFMA rate.
+//   64 x 128,  4 wavefronts, two workgroups per CU with deep rings: for launches that would leave most CUs idle otherwise.
+// 256 weight columns x 64 k of LDS-DMA loads in flight per CU also stream weights well: 16 groups of 8 rows, d = 4096,
+// f = 1536 (400 MB of gate/up weights): 109 -> 77 us, 5.2 TB/s.
+// The result's bits do not depend on the shape: every element is one chain of MFMAs 32x32x16 over ascending k.
+#include "common.h"
+#include "panel_gemm.h"
+
+namespace {
+using namespace feplb::dev;
+
+template <int MODE, bool OUT_BF16, bool SAVE, int WR, int MI, int NJ, int DA, int DB, int OCC>
+__global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
+    const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k,
+    const int* __restrict__ offsets, int g_begin, int ng, int R_cap, int K, int n_tiles_n, int band,
+    WeightTable wt, int ldw, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, true>;
+  __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
+  constexpr int SH = Core::BM == 64 ? 6 : Core::BM == 128 ? 7 : 8;
+  static_assert((1 << SH) == Core::BM, "tile height");
+
+  // ---- block -> tile: bands of `band` row tiles, walked column by column
+  RowTiles<SH> tiles;
+  tiles.init(offsets, g_begin, ng, R_cap);
+  const int total = tiles.total * n_tiles_n;
+  const int idx = tile_of_block<32 * Core::BLOCKS_PER_CU>(blockIdx.x, total);
+  if (idx < 0) return;
+  const int b0 = idx / (band * n_tiles_n) * band;
+  const int in_band = idx - b0 * n_tiles_n;
+  const int height = min(band, tiles.total - b0);
+  const int nt = in_band / height;
+  const RowTile tile = tiles.find(b0 + in_band % height, g_begin);
+  const int g = tile.g, row0 = tile.row0, rows = tile.rows;
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int wm = wave / 2, wn = wave % 2;
+  const int KT = K / 64;
+
+  // ---- loads
+  uint32_t a_goff[Core::LA];
+  const bool gather = MODE == 0 && row_src != nullptr;
+#pragma unroll
+  for (int i = 0; i < Core::LA; ++i) {
+    const int li = wave * Core::LA + i;
+    int row = min(Core::rows_row(li, lane), rows - 1);
+    if (gather) row = min(max(row_src[row0 + row] / src_k, 0), n_src_rows - 1);
+    a_goff[i] = ((uint32_t)row * (uint32_t)lda + Core::rows_chunk(li, lane) * 8) * 2;
+  }
+  const char* a_ptr = wave_uniform(gather ? A : A + (size_t)row0 * lda);
+  // the requests come in order, so each operand keeps one running scalar pointer; it stays on the last tile for
+  // requests past the end
+  auto issue_a = [&](uint32_t stage, int t, int i) {
+    load_to_lds_16(a_ptr, a_goff[i], stage + (wave * Core::LA + i) * 1024);
+    if (i == Core::LA - 1) a_ptr += t < KT - 1 ? 128 : 0;
+  };
+  uint32_t b_goff[Core::LB];
+  const char *b_ptr0, *b_ptr1;
+  const size_t ldw_bytes = (size_t)ldw * 2;
+#pragma unroll
+  for (int i = 0; i < Core::LB; ++i)
+    b_goff[i] = (uint32_t)Core::template cols_row<NJ>(wave * Core::LB + i, lane) * (uint32_t)ldw_bytes + Core::template cols_chunk<NJ>(i, lane) * 16;
+  if (MODE == 0) {
+    b_ptr0 = wave_uniform((const uint16_t*)wt.w0[g] + (size_t)nt * Core::HW);
+    b_ptr1 = wave_uniform((const uint16_t*)wt.w1[g] + (size_t)nt * Core::HW);
+  } else {
+    b_ptr0 = wave_uniform((const uint16_t*)wt.w0[g] + (size_t)nt * Core::BN);
+    b_ptr1 = b_ptr0 + Core::HW * 2;
+  }
+  const size_t b_step = 64 * ldw_bytes;
+  auto issue_b = [&](uint32_t stage, int u, int i) {
+    const int t = u >> 1, half = u & 1;
+    const char*& ptr = half ? b_ptr1 : b_ptr0;
+    load_to_lds_16(ptr, b_goff[i], stage + (wave * Core::LB + i) * 1024);
+    if (i == Core::LB - 1) {
+      ptr += t < KT - 1 ? b_step : 0;
+    }
+  };
+
+  typename Core::FragA fa;
+  typename Core::FragB fb;
+  fa.init(wm * 32, lane);
+  fb.init(wn * 32 * NJ, lane);
+  f32x16 acc[2][MI][NJ];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[hf][mi][nj][v] = 0.f;
+  auto none = [](int) {};
+  const int blocks32 = (rows + 32 * WR - 1 - wm * 32) / (32 * WR);   // row blocks of this wave that hold rows
+  static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
+  if (blocks32 >= MI) {
+    Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);
+  } else if (blocks32 == 1) {
+    Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);
+  } else {
+    Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);   // its loads and barriers only
+    return;
+  }
+
+  // ---- epilogue.  The MFMAs computed (X W)^T per 32 x 32 block: a lane holds ONE row and, in accumulator registers
+  // 4c .. 4c+3, FOUR consecutive columns 8c + 4 (lane / 32) .. +3.  Stored straight from there a row would leave in 8- or
+  // 16-byte pieces, and partial-line writes are slow in the L2.  Each wave passes 32 rows at a time through an LDS
+  // region of its own and reads them back with the lanes laid along the rows, so that a store instruction writes
+  // contiguous pieces of rows.  No barrier: the region is private and the LDS runs a wave's instructions in order.
+  constexpr int COLS = 32 * NJ;
+  constexpr int ESZ = (MODE == 0 || OUT_BF16) ? 2 : 4;
+  constexpr int ROW_BYTES = COLS * ESZ;
+  constexpr int CH = ROW_BYTES / 16;
+  constexpr int RPI = 64 / CH;
+  constexpr int SWZ_DIV = ROW_BYTES >= 256 ? 1 : 256 / ROW_BYTES;   // chunk q of row r sits at slot q ^ swz(r)
+  constexpr int PIECE = 32 * ROW_BYTES;            // one staged block of 32 rows
+  static_assert(3 * PIECE <= Core::LDS_BYTES / (2 * WR) || (!SAVE && PIECE <= Core::LDS_BYTES / (2 * WR)), "staging region");
+  const int l32 = lane % 32;
+  auto swz = [&](int r) { return (r / SWZ_DIV) & (CH - 1); };
+  char* const ep = lds + wave * (Core::LDS_BYTES / (2 * WR));
+  const int csub = (lane / 32) * 4;
+  const int rd_row = lane / CH, rd_chunk = lane % CH;
+  const int wrow = wm * 32;
+  auto piece = [&](int nj, int c) -> char* {
+    const int boff = (nj * 32 + 8 * c + csub) * ESZ;
+    return ep + l32 * ROW_BYTES + ((((boff >> 4) ^ swz(l32))) << 4) + (boff & 15);
+  };
+  auto store_lines = [&](const char* from, int mi, char* dst_wave, size_t ld_bytes, bool streaming) {
+#pragma unroll
+    for (int j = 0; j < 32 / RPI; ++j) {
+      const int r = j * RPI + rd_row;
+      const u32x4 v = *(const u32x4*)(from + r * ROW_BYTES + ((rd_chunk ^ swz(r)) << 4));
+      if (wrow + mi * 32 * WR + r < rows) {
+        u32x4* dst = (u32x4*)(dst_wave + (size_t)(mi * 32 * WR + r) * ld_bytes + rd_chunk * 16);
+        if (streaming) __builtin_nontemporal_store(v, dst); else *dst = v;
+      }
+    }
+  };
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    if (wrow + mi * 32 * WR >= rows) break;
+#pragma unroll
+    for (int hf = 0; hf < (MODE == 0 ? 1 : 2); ++hf) {
+      const int col0 = (MODE == 0 ? nt * Core::HW : nt * Core::BN + hf * Core::HW) + wn * COLS;
+      char* out_wave = (char*)out + ((size_t)(row0 + wrow) * ldo + col0) * ESZ;
+      char* aux_wave = (char*)aux + ((size_t)(row0 + wrow) * ld_aux + col0) * 2;
+      if constexpr (MODE == 0 && SAVE) {
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            char* dst = piece(nj, c);
+            float hv[4], pv[4], qv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float a = acc[0][mi][nj][4 * c + i], b = acc[1][mi][nj][4 * c + i];
+              const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-a));
+              qv[i] = a * sg;
+              hv[i] = qv[i] * b;
+              pv[i] = b * sg * (1.0f + a - qv[i]);
+            }
+            *(uint2*)dst = make_uint2(pack_bf16(hv[0], hv[1]), pack_bf16(hv[2], hv[3]));
+            *(uint2*)(dst + PIECE) = make_uint2(pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]));
+            *(uint2*)(dst + 2 * PIECE) = make_uint2(pack_bf16(qv[0], qv[1]), pack_bf16(qv[2], qv[3]));
+          }
+        store_lines(ep, mi, out_wave, (size_t)ldo * ESZ, false);
+        store_lines(ep + PIECE, mi, aux_wave, (size_t)ld_aux * 2, false);
+        store_lines(ep + 2 * PIECE, mi, aux_wave + ld_aux, (size_t)ld_aux * 2, false);
+      } else {
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            char* dst = piece(nj, c);
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              v[i] = MODE == 0 ? silu(acc[0][mi][nj][4 * c + i]) * acc[1][mi][nj][4 * c + i] : acc[hf][mi][nj][4 * c + i];
+            if (ESZ == 2)
+              *(uint2*)dst = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+            else
+              *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+          }
+        store_lines(ep, mi, out_wave, (size_t)ldo * ESZ, MODE == 1 && !OUT_BF16);   // fp32 rows are read once, by the combine
+      }
+    }
+  }
+}
+
+// Tile shape by estimated time.  A launch of B tiles runs B / (256 per_cu) full rounds and a rest; a round with one
+// (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
+// GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168); picking by it is 2 % slower on average than the
+// best of the three each time, and 1.37x faster than 256 x 256 tiles of four wavefronts for every shape.  B is estimated from
+// the row capacity: a group of rows ends half a tile early on average.
+struct Shape {
+  int bm, bn, per_cu;
+  double start, round[2];   // us; us per 1000 k
+};
+constexpr Shape SHAPES[3] = {{256, 256, 1, 3.5, {22.3, 0.}}, {128, 256, 2, 4.2, {14.1, 29.9}}, {64, 128, 2, 3.8, {4.8, 12.9}}};
+
+int pick_shape(int R_cap, int ng, int K, int weight_cols) {
+  int best = 0;
+  double best_us = 0.;
+  for (int i = 0; i < 3; ++i) {
+    const Shape& s = SHAPES[i];
+    const double m = (double)R_cap / s.bm + 0.5 * ng;
+    const double tiles = (m > ng ? m : ng) * (weight_cols / s.bn);
+    const double full = (double)(long)(tiles / (256 * s.per_cu)), rest = tiles - full * (256 * s.per_cu);
+    const double tail = rest <= 0. ? 0. : s.round[rest > 256 ? 1 : 0];
+    const double us = s.start + K * 1e-3 * (full * s.round[s.per_cu - 1] + tail);
+    if (i == 0 || us < best_us) {
+      best = i;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+template <int MODE, bool OUT_BF16, bool SAVE, int WR, int MI, int NJ, int DA, int DB, int OCC>
+hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, true>;
+  const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
+  const long row_tiles = a.R_cap / Core::BM + a.ng;
+  const int band = Core::BM == 256 ? 8 : 16;   // a run of tiles is about as many bytes of rows as of weights
+  hipLaunchKernelGGL((panel_gemm_kernel<MODE, OUT_BF16, SAVE, WR, MI, NJ, DA, DB, OCC>), dim3(blocks_for_tiles(row_tiles * n_tiles_n)),
+                     dim3(128 * WR), 0, s, (const uint16_t*)a.A, a.lda, a.row_src, a.n_src_rows, a.src_k, a.offsets, a.g_begin, a.ng,
+                     a.R_cap, a.K, n_tiles_n, band, *a.weights, a.ldw, a.out, a.ldo, a.aux, a.ld_aux);
+  return hipGetLastError();
+}
+
+template <int MODE, bool OUT_BF16, bool SAVE>
+hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
+  switch (pick_shape(a.R_cap, a.ng, a.K, MODE == 0 ? 2 * a.N : a.N)) {
+    case 0: return launch<MODE, OUT_BF16, SAVE, 4, 2, 2, 3, 3, 2>(a, s);
+    case 1: return launch<MODE, OUT_BF16, SAVE, 2, 2, 2, 2, 3, 2>(a, s);
+    default: return launch<MODE, OUT_BF16, SAVE, 2, 1, 1, 3, 6, 2>(a, s);
+  }
+}
+
+}  // namespace
+
+namespace feplb {
+
+hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s) {
+  return a.aux ? launch_shape<0, true, true>(a, s) : launch_shape<0, true, false>(a, s);
+}
+hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s) {
+  return out_bf16 ? launch_shape<1, true, false>(a, s) : launch_shape<1, false, false>(a, s);
+}
+
+}  // namespace feplb

@@ -237,6 +237,39 @@ def test_grouped_ffn_short_tail_tiles_repeatable(d, f, sizes):
     assert eh <= 1.0 and ey.max() <= ROW_TOL
 
 
+@pytest.mark.parametrize("f", [384, 128])
+def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
+    # The tile shape of the grouped GEMM is picked from the row capacity: 64-, 128- and 256-row tiles at the three
+    # capacities here.  Group sizes lie at the edges of the tiles, of their 32-row blocks and of the loop variants
+    # that skip empty blocks.  Every element is the same chain of MFMAs in all shapes, so the bytes must be equal.
+    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
+    d, G = 512, len(sizes)
+    say(f"ffn tile shapes d={d} f={f}")
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    R = int(offsets[-1])
+    Xp = torch.randn((R, d), generator=torch.Generator().manual_seed(27)).to(torch.bfloat16)
+    W = make_weights(G, d, f, 29)
+    cols = [[w[i].to(DEV) for w in W] for i in range(3)]
+    order = torch.from_numpy(np.random.default_rng(3).permutation(R).astype(np.int32))
+    X = torch.empty_like(Xp)
+    X[order.long()] = Xp
+    H_o, Yp_o = orc.grouped_ffn(f64(Xp), offsets, [tuple(f64(m) for m in w) for w in W])
+    first = None
+    for R_cap in (R, 8000, 100000):
+        for yp_dtype in (torch.float32, torch.bfloat16):
+            H = torch.full((R_cap, f), 512.0, dtype=torch.bfloat16, device=DEV)
+            Yp = torch.full((R_cap, d), 512.0, dtype=yp_dtype, device=DEV)
+            fe.feplb_grouped_ffn(X.to(DEV), torch.from_numpy(offsets).to(DEV), 0, G, d, f, *cols, H, Yp,
+                                 row_src=order.to(DEV), k=1)
+            torch.cuda.synchronize()
+            assert (H[R:].float() == 512.0).all() and (Yp[R:].float() == 512.0).all()
+            if first is None:
+                first = (H[:R], Yp[:R])
+                assert bf16_rounding_excess(f64(H)[:R], H_o) <= 1.0 and row_rel_err(f64(Yp)[:R], Yp_o).max() <= ROW_TOL
+            else:
+                assert torch.equal(H[:R], first[0]) and torch.equal(Yp[:R], first[1].to(yp_dtype))
+
+
 def test_grouped_ffn_repeatable_over_random_shapes():
     # a property that holds at any size: the hand-scheduled load pipeline has no timing-dependent
     # result.  Random widths (all loop shapes: whole trips of the stage ring plus 0, 4 or 8 steps)
