@@ -355,7 +355,7 @@ def training_leg(p, steps):
                 wgrad_tflops=3 * fl / (ms["wgrad"] * 1e-3) / 1e12,
                 backward_tflops=6 * fl / (ms["backward"] * 1e-3) / 1e12,
                 backward_over_forward=ms["backward"] / ms["forward_keeping_derivatives"],
-                note="backward = weight transposes + dH GEMM with the SwiGLU derivative + dXp GEMM + three ragged "
+                note="backward = dH GEMM with the SwiGLU derivative + dXp GEMM + three ragged "
                      "weight-gradient GEMMs (fp32 out); upstream gradient synthetic; Xp materialised")
 
 

@@ -157,10 +157,9 @@ int32_t feplb_permute_append(const int32_t* topk_ids, int32_t T, int32_t k, int3
  *           g_begin are not read
  *   H       device, bf16 [R_cap,f]   written by GATE_UP, read by DOWN
  *   Yp      device, [R_cap,d] of yp_dtype (FEPLB_F32 or FEPLB_BF16), written by DOWN
- *   phases  any non-empty subset of FEPLB_FFN_SCHEDULE (turn offsets[] into the
- *           tile table kept in ws), FEPLB_FFN_GATE_UP, FEPLB_FFN_DOWN; the GEMM
- *           phases need a table built by an earlier or the same call with the
- *           same offsets, range and R_cap.  FEPLB_FFN_ALL does all three.
+ *   phases  any non-empty subset of FEPLB_FFN_SCHEDULE (launches nothing: the GEMMs find
+ *           their tiles from offsets[]), FEPLB_FFN_GATE_UP, FEPLB_FFN_DOWN.
+ *           FEPLB_FFN_ALL does all three.
  *   ws      device, feplb_grouped_ffn_workspace_bytes(R_cap, G) bytes
  * Empty groups read no weights and do no work.
  * Limits: d % 256 == 0, f % 128 == 0, g_end <= FEPLB_MAX_GROUPS.
@@ -183,16 +182,10 @@ int32_t feplb_grouped_ffn(const void* Xp, const int32_t* row_src, int32_t T, int
 
 /* The same call for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * results and limits as feplb_grouped_ffn, without ws / ws_bytes: the tile table lives in
- * FEPLB_STATIC_WS_BYTES of device memory that is part of the library itself (each GPU the library
- * runs on holds its own copy until the process ends).  Nothing is allocated or freed, by the
- * library or through any routine it calls.
- *   - Refused with FEPLB_ESHAPE when feplb_grouped_ffn_workspace_bytes(R_cap, g_end - g_begin)
- *     exceeds FEPLB_STATIC_WS_BYTES (256 KiB: about 4.1 million rows in 128 groups).
- *   - Every call on one GPU shares that GPU's table.  SCHEDULE rewrites the part it uses, so a
- *     later call with another range or fewer rows is safe; a GEMM phase without SCHEDULE runs on
- *     the table the last SCHEDULE on this GPU left.  Calls that overlap on one GPU (two streams,
- *     two threads) race on the table: order them.
+ * results and limits as feplb_grouped_ffn, without ws / ws_bytes.  Nothing is allocated or freed, by
+ * the library or through any routine it calls.  Refused with FEPLB_ESHAPE when
+ * feplb_grouped_ffn_workspace_bytes(R_cap, g_end - g_begin) exceeds FEPLB_STATIC_WS_BYTES
+ * (256 KiB: about 4.1 million rows in 128 groups).
  */
 #define FEPLB_STATIC_WS_BYTES 262144
 
@@ -231,11 +224,12 @@ int32_t feplb_grouped_ffn_static(const void* Xp, const int32_t* row_src, int32_t
  *   dw_gate, dw_up, dw_down  host arrays of (g_end) device pointers indexed by g:
  *           fp32 [d,f], [d,f], [f,d]  out
  *   WT      device scratch, feplb_grouped_ffn_backward_wt_bytes(g_end - g_begin, d, f)
- *           bytes: receives the transposed weights (phase TRANSPOSE), read by DGRAD
- *   phases  any non-empty subset of FEPLB_BWD_SCHEDULE (tile table from offsets[], as
- *           in the forward call; may be skipped when ws still holds the forward call's
- *           table for the same range), FEPLB_BWD_TRANSPOSE, FEPLB_BWD_DGRAD (needs
- *           the table and WT), FEPLB_BWD_WGRAD.  WGRAD for the gate and up matrices
+ *           bytes: receives the transposed weights where TRANSPOSE is asked for without DGRAD
+ *   phases  any non-empty subset of FEPLB_BWD_SCHEDULE (launches nothing),
+ *           FEPLB_BWD_TRANSPOSE, FEPLB_BWD_DGRAD, FEPLB_BWD_WGRAD.  DGRAD reads the weights
+ *           themselves, so with TRANSPOSE in the same call nothing is transposed; a call without
+ *           TRANSPOSE may pass null entries in w_gate, w_up, w_down, and DGRAD then reads
+ *           WT as a call with TRANSPOSE and without DGRAD left it.  WGRAD for the gate and up matrices
  *           needs da | db, i.e. DGRAD in the same or an earlier call.  With
  *           FEPLB_BWD_ACCUMULATE added, WGRAD adds its results to what dw_gate, dw_up,
  *           dw_down hold (gradient accumulation over micro-batches; an empty group's

@@ -293,8 +293,8 @@ STATIC_WS_BYTES = 262144   # FEPLB_STATIC_WS_BYTES
 
 def feplb_grouped_ffn_static(Xp, offsets, g_begin, g_end, d, f, w_gate, w_up, w_down, H, Yp,
                              phases=FFN_ALL, stream=None, row_src=None, k=0):
-    """feplb_grouped_ffn without a workspace: the tile table lives in device memory that is part of
-    the library (for callers that cannot allocate).  Same arguments and results otherwise."""
+    """feplb_grouped_ffn without a workspace (for callers that cannot allocate).  Same arguments and
+    results otherwise."""
     R_cap = H.shape[0]
     yp_dtype = F32
     if Yp is not None:

@@ -23,15 +23,18 @@ struct GroupedGemm {
   const int* offsets;
   int g_begin, ng, R_cap;
   int K, N;                         // contraction length and output columns (gate/up: of one matrix)
-  const dev::WeightTable* weights;  // row-major [K,N] matrices, row stride ldw
+  const dev::WeightTable* weights;  // row-major [K,N] matrices, row stride ldw; with w_nk row-major [N,K] ones
   int ldw;
+  bool w_nk;                        // plain, dswiglu
+  int k_split;                      // w_nk: k from here on lies in the tables' second matrix; K if there is none
   void* out;
   int ldo;
-  void* aux;                        // gate/up: receives the derivatives p | q, or null
+  void* aux;                        // gate/up: receives the derivatives p | q, or null; dswiglu: p | q in, da | db out
   int ld_aux;
 };
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s);
 hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s);
+hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s);
 
 // backward-pass launchers (ffn_backward.hip), used by feplb_grouped_ffn_backward
 hipError_t launch_wgrad(const void* P, int ldp, int M, const void* Q, int ldq, int N, const int* offsets,

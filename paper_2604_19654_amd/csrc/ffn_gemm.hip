@@ -2,6 +2,7 @@
 //   MODE 0  gate/up:  H[r,:] = bf16( silu(x_r Wg[g]) * (x_r Wu[g]) ); with SAVE also the two derivatives p, q of that
 //           product with respect to its factors' products, bf16, in columns [0,N) and [N,2N) of `aux`
 //   MODE 1  plain:    out[r,:] = a_r W[g], fp32 or bf16
+//   MODE 2  dswiglu:  dH = a_r W[g], times the derivatives in `aux`: da = dH p | db = dH q, bf16, written over them
 // One launch covers a whole range of ragged groups; a workgroup finds its tile from offsets[] (device memory), so the
 // host never needs the number of rows: the grid covers an upper bound and surplus workgroups leave at once.
 // panel_gemm.h holds the main loop and the mapping of workgroups to tiles.
@@ -15,6 +16,9 @@
 //   64 x 128,  4 wavefronts, two workgroups per CU with deep rings: for launches that would leave most CUs idle otherwise.
 // 256 weight columns x 64 k of LDS-DMA loads in flight per CU also stream weights well: 16 groups of 8 rows, d = 4096,
 // f = 1536 (400 MB of gate/up weights): 109 -> 77 us, 5.2 TB/s.
+// The weights are row-major [K,N] (B_TR: the MFMA operand needs 8 consecutive k of one column, which the transposing LDS
+// read delivers), or row-major [N,K] for the products with W^T of the backward pass, read like the rows of A.  [N,K]
+// weights may be two matrices that share k: w0 holds the first k_split of it, w1 the rest (dXp = [da | db] [Wg | Wu]^T).
 // The result's bits do not depend on the shape: every element is one chain of MFMAs 32x32x16 over ascending k.
 #include "common.h"
 #include "panel_gemm.h"
@@ -22,12 +26,12 @@
 namespace {
 using namespace feplb::dev;
 
-template <int MODE, bool OUT_BF16, bool SAVE, int WR, int MI, int NJ, int DA, int DB, int OCC>
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB, int OCC>
 __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
     const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k,
     const int* __restrict__ offsets, int g_begin, int ng, int R_cap, int K, int n_tiles_n, int band,
-    WeightTable wt, int ldw, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
-  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, true>;
+    WeightTable wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
   __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
   constexpr int SH = Core::BM == 64 ? 6 : Core::BM == 128 ? 7 : 8;
   static_assert((1 << SH) == Core::BM, "tile height");
@@ -70,22 +74,32 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   const char *b_ptr0, *b_ptr1;
   const size_t ldw_bytes = (size_t)ldw * 2;
 #pragma unroll
-  for (int i = 0; i < Core::LB; ++i)
-    b_goff[i] = (uint32_t)Core::template cols_row<NJ>(wave * Core::LB + i, lane) * (uint32_t)ldw_bytes + Core::template cols_chunk<NJ>(i, lane) * 16;
+  for (int i = 0; i < Core::LB; ++i) {
+    const int li = wave * Core::LB + i;
+    b_goff[i] = B_TR ? (uint32_t)Core::template cols_row<NJ>(li, lane) * (uint32_t)ldw_bytes + Core::template cols_chunk<NJ>(i, lane) * 16
+                     : (uint32_t)Core::rows_row(li, lane) * (uint32_t)ldw_bytes + Core::rows_chunk(li, lane) * 16;
+  }
   if (MODE == 0) {
     b_ptr0 = wave_uniform((const uint16_t*)wt.w0[g] + (size_t)nt * Core::HW);
     b_ptr1 = wave_uniform((const uint16_t*)wt.w1[g] + (size_t)nt * Core::HW);
   } else {
-    b_ptr0 = wave_uniform((const uint16_t*)wt.w0[g] + (size_t)nt * Core::BN);
-    b_ptr1 = b_ptr0 + Core::HW * 2;
+    const size_t col_bytes = B_TR ? 2 : ldw_bytes;
+    b_ptr0 = wave_uniform((const char*)wt.w0[g] + nt * Core::BN * col_bytes);
+    b_ptr1 = b_ptr0 + Core::HW * col_bytes;
   }
-  const size_t b_step = 64 * ldw_bytes;
+  const size_t b_step = B_TR ? 64 * ldw_bytes : 128;
+  const int t_split = B_TR ? KT : k_split / 64;
+  const ptrdiff_t b_jump = !B_TR && t_split < KT   // from the last k tile of w0 to the first of w1
+                               ? wave_uniform(wt.w1[g]) - wave_uniform(wt.w0[g]) - (ptrdiff_t)(t_split - 1) * 128 : 0;
   auto issue_b = [&](uint32_t stage, int u, int i) {
     const int t = u >> 1, half = u & 1;
     const char*& ptr = half ? b_ptr1 : b_ptr0;
     load_to_lds_16(ptr, b_goff[i], stage + (wave * Core::LB + i) * 1024);
     if (i == Core::LB - 1) {
-      ptr += t < KT - 1 ? b_step : 0;
+      if (B_TR)
+        ptr += t < KT - 1 ? b_step : 0;
+      else
+        ptr += t >= KT - 1 ? 0 : t == t_split - 1 ? b_jump : 128;
     }
   };
 
@@ -120,7 +134,7 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   // region of its own and reads them back with the lanes laid along the rows, so that a store instruction writes
   // contiguous pieces of rows.  No barrier: the region is private and the LDS runs a wave's instructions in order.
   constexpr int COLS = 32 * NJ;
-  constexpr int ESZ = (MODE == 0 || OUT_BF16) ? 2 : 4;
+  constexpr int ESZ = (MODE != 1 || OUT_BF16) ? 2 : 4;
   constexpr int ROW_BYTES = COLS * ESZ;
   constexpr int CH = ROW_BYTES / 16;
   constexpr int RPI = 64 / CH;
@@ -148,6 +162,62 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
       }
     }
   };
+  if constexpr (MODE == 2) {
+    // p | q come in as whole lines, requested one pass ahead, go through the staging region to the lanes that hold the
+    // matching dH values, and da | db leave the same way
+    constexpr int LINES = 32 / RPI;
+    u32x4 pl[2][LINES], ql[2][LINES];
+    const size_t ld_bytes = (size_t)ld_aux * 2;
+    char* const aux_wave = (char*)aux + (size_t)(row0 + wrow) * ld_bytes + (nt * Core::BN + wn * COLS) * 2;
+    auto fetch = [&](int pass, int buf) {
+      const int mi = pass / 2, hf = pass % 2;
+#pragma unroll
+      for (int j = 0; j < LINES; ++j) {
+        const int r = mi * 32 * WR + j * RPI + rd_row;
+        pl[buf][j] = ql[buf][j] = u32x4{0u, 0u, 0u, 0u};
+        if (wrow + r < rows) {
+          const char* src = aux_wave + (size_t)r * ld_bytes + hf * Core::HW * 2 + rd_chunk * 16;
+          pl[buf][j] = *(const u32x4*)src;
+          ql[buf][j] = *(const u32x4*)(src + ld_aux);   // q sits ld_aux / 2 columns to the right of p
+        }
+      }
+    };
+    fetch(0, 0);
+#pragma unroll
+    for (int pass = 0; pass < 2 * MI; ++pass) {
+      const int mi = pass / 2, hf = pass % 2;
+      if (wrow + mi * 32 * WR >= rows) break;
+      if (pass + 1 < 2 * MI) fetch(pass + 1, (pass + 1) % 2);
+#pragma unroll
+      for (int j = 0; j < LINES; ++j) {
+        const int r = j * RPI + rd_row;
+        char* q = ep + r * ROW_BYTES + ((rd_chunk ^ swz(r)) << 4);
+        *(u32x4*)q = pl[pass % 2][j];
+        *(u32x4*)(q + PIECE) = ql[pass % 2][j];
+      }
+#pragma unroll
+      for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          char* q = piece(nj, c);
+          const uint2 pv = *(const uint2*)q, qv = *(const uint2*)(q + PIECE);
+          const float dp[4] = {bf16_lo(pv.x), bf16_hi(pv.x), bf16_lo(pv.y), bf16_hi(pv.y)};
+          const float dq[4] = {bf16_lo(qv.x), bf16_hi(qv.x), bf16_lo(qv.y), bf16_hi(qv.y)};
+          float da[4], db[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float dh = acc[hf][mi][nj][4 * c + i];
+            da[i] = dh * dp[i];
+            db[i] = dh * dq[i];
+          }
+          *(uint2*)q = make_uint2(pack_bf16(da[0], da[1]), pack_bf16(da[2], da[3]));
+          *(uint2*)(q + PIECE) = make_uint2(pack_bf16(db[0], db[1]), pack_bf16(db[2], db[3]));
+        }
+      store_lines(ep, mi, aux_wave + hf * Core::HW * 2, ld_bytes, false);
+      store_lines(ep + PIECE, mi, aux_wave + hf * Core::HW * 2 + ld_aux, ld_bytes, false);
+    }
+    return;
+  }
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     if (wrow + mi * 32 * WR >= rows) break;
@@ -228,24 +298,24 @@ int pick_shape(int R_cap, int ng, int K, int weight_cols) {
   return best;
 }
 
-template <int MODE, bool OUT_BF16, bool SAVE, int WR, int MI, int NJ, int DA, int DB, int OCC>
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB, int OCC>
 hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
-  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, true>;
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
   const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
   const long row_tiles = a.R_cap / Core::BM + a.ng;
   const int band = Core::BM == 256 ? 8 : 16;   // a run of tiles is about as many bytes of rows as of weights
-  hipLaunchKernelGGL((panel_gemm_kernel<MODE, OUT_BF16, SAVE, WR, MI, NJ, DA, DB, OCC>), dim3(blocks_for_tiles(row_tiles * n_tiles_n)),
+  hipLaunchKernelGGL((panel_gemm_kernel<MODE, OUT_BF16, SAVE, B_TR, WR, MI, NJ, DA, DB, OCC>), dim3(blocks_for_tiles(row_tiles * n_tiles_n)),
                      dim3(128 * WR), 0, s, (const uint16_t*)a.A, a.lda, a.row_src, a.n_src_rows, a.src_k, a.offsets, a.g_begin, a.ng,
-                     a.R_cap, a.K, n_tiles_n, band, *a.weights, a.ldw, a.out, a.ldo, a.aux, a.ld_aux);
+                     a.R_cap, a.K, n_tiles_n, band, *a.weights, a.ldw, a.k_split, a.out, a.ldo, a.aux, a.ld_aux);
   return hipGetLastError();
 }
 
-template <int MODE, bool OUT_BF16, bool SAVE>
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
 hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
   switch (pick_shape(a.R_cap, a.ng, a.K, MODE == 0 ? 2 * a.N : a.N)) {
-    case 0: return launch<MODE, OUT_BF16, SAVE, 4, 2, 2, 3, 3, 2>(a, s);
-    case 1: return launch<MODE, OUT_BF16, SAVE, 2, 2, 2, 2, 3, 2>(a, s);
-    default: return launch<MODE, OUT_BF16, SAVE, 2, 1, 1, 3, 6, 2>(a, s);
+    case 0: return launch<MODE, OUT_BF16, SAVE, B_TR, 4, 2, 2, 3, 3, 2>(a, s);
+    case 1: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 2, 2, 2, 3, 2>(a, s);
+    default: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 1, 1, 3, 6, 2>(a, s);
   }
 }
 
@@ -254,10 +324,14 @@ hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
 namespace feplb {
 
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s) {
-  return a.aux ? launch_shape<0, true, true>(a, s) : launch_shape<0, true, false>(a, s);
+  return a.aux ? launch_shape<0, true, true, true>(a, s) : launch_shape<0, true, false, true>(a, s);
 }
 hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s) {
-  return out_bf16 ? launch_shape<1, true, false>(a, s) : launch_shape<1, false, false>(a, s);
+  if (a.w_nk) return out_bf16 ? launch_shape<1, true, false, false>(a, s) : launch_shape<1, false, false, false>(a, s);
+  return out_bf16 ? launch_shape<1, true, false, true>(a, s) : launch_shape<1, false, false, true>(a, s);
+}
+hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s) {
+  return a.w_nk ? launch_shape<2, true, false, false>(a, s) : launch_shape<2, true, false, true>(a, s);
 }
 
 }  // namespace feplb

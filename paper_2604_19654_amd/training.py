@@ -125,7 +125,7 @@ def time_phases(step: FfnTrainingStep, Xp, offsets, w_gate, w_up, w_down, dYp, r
 
     out = {"forward_keeping_derivatives": timed(lambda: step.forward(Xp, offsets, w_gate, w_up, w_down))}
     step.forward(Xp, offsets, w_gate, w_up, w_down)
-    step.backward(Xp, offsets, w_gate, w_up, w_down, dYp)      # leaves tile table and transposes in place
+    step.backward(Xp, offsets, w_gate, w_up, w_down, dYp)
     for name, ph in (("transpose", B.BWD_TRANSPOSE), ("dgrad", B.BWD_DGRAD), ("wgrad", B.BWD_WGRAD),
                      ("wgrad_accumulating", B.BWD_WGRAD | B.BWD_ACCUMULATE), ("backward", B.BWD_ALL)):
         out[name] = timed(lambda ph=ph: step.backward(Xp, offsets, w_gate, w_up, w_down, dYp, phases=ph))

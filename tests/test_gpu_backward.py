@@ -151,6 +151,40 @@ def test_grouped_ffn_backward_parity(sizes, d, f, dxp_dtype):
     assert torch.isnan(r["dAB"][R:].float()).all() and torch.isnan(r["H"][R:].float()).all()
 
 
+@pytest.mark.parametrize("d,f", [(512, 256), (256, 768)])
+def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d, f):
+    # The tile shape is picked from the row capacity: 64-, 128- and 256-row tiles at the three capacities here.  The
+    # input gradients read the weights themselves, or transposes left in WT by an earlier call where none are given.
+    # Every element is the same chain of MFMAs on all six ways, so the bytes must be equal.  Group sizes lie at the
+    # edges of the tiles and of their 32-row blocks.
+    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
+    say(f"ffn input gradients d={d} f={f}")
+    r = run_forward_backward(sizes, d, f, torch.float32)
+    R, G = r["R"], len(sizes)
+    (dXp_o, _), _ = oracle_backward(r)
+    check_rows(f64(r["dXp"])[:R], dXp_o, "dXp")
+    offsets = torch.from_numpy(r["offsets"]).to(DEV)
+    W = [[w[i].to(DEV) for w in r["W"]] for i in range(3)]
+    WT = torch.zeros((B.feplb_grouped_ffn_backward_wt_bytes(G, d, f),), dtype=torch.uint8, device=DEV)
+    nothing = [[None] * G for _ in range(3)]
+    for R_cap in (R, 8000, 100000):
+        H = torch.zeros((R_cap, f), dtype=torch.bfloat16, device=DEV)
+        dYp = torch.full((R_cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        dYp[:R] = r["dYp"][:R].to(DEV)
+        for weights in (W, nothing):
+            for dxp_dtype in (torch.float32, torch.bfloat16):
+                AB = torch.full((R_cap, 2 * f), 512.0, dtype=torch.bfloat16, device=DEV)
+                AB[:R] = r["AB_saved"][:R]
+                dXp = torch.full((R_cap, d), 512.0, dtype=dxp_dtype, device=DEV)
+                args = (None, offsets, 0, G, d, f)
+                if weights is nothing:
+                    B.feplb_grouped_ffn_backward(*args, *W, H, AB, dYp, dXp, *nothing, WT=WT, phases=B.BWD_TRANSPOSE)
+                B.feplb_grouped_ffn_backward(*args, *weights, H, AB, dYp, dXp, *nothing, WT=WT, phases=B.BWD_DGRAD)
+                torch.cuda.synchronize()
+                assert torch.equal(AB[:R], r["dAB"][:R]) and torch.equal(dXp[:R], r["dXp"][:R].to(dxp_dtype))
+                assert (AB[R:].float() == 512.0).all() and (dXp[R:].float() == 512.0).all()
+
+
 def test_grouped_ffn_backward_larger_ragged_case_and_repeatability():
     # several row tiles per group, contraction tails of every residue class, f != d
     sizes = [517, 2, 1031, 0, 255, 770, 96, 1]
