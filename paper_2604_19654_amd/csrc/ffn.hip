@@ -20,8 +20,8 @@
 namespace {
 using namespace feplb::dev;
 
-// The workspace: 16 bytes per 256-row tile, in the worst split over the groups, and one more, which SCHEDULE used to
-// fill with a table of tiles (a caller's buffers are sized by it); then, backward pass only, the groups ordered by row count.
+// The workspace, which no kernel uses any more and callers still size and pass: 16 bytes per 256-row tile, in the worst split
+// over the groups, and one more; then one word per possible group.
 size_t table_bytes(int R_cap, int ng) { return (size_t)(R_cap / 256 + ng + 2) * 16; }
 
 }  // namespace
@@ -168,8 +168,6 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
   const int ng = g_end - g_begin;
   if (ng == 0) return FEPLB_OK;
   const bool asks_t = phases & FEPLB_BWD_TRANSPOSE, do_d = phases & FEPLB_BWD_DGRAD, do_w = phases & FEPLB_BWD_WGRAD;
-  // the weight-gradient kernel reads whole windows of 32 rows and runs for empty inputs too
-  // (it writes the zero gradients), so the row buffers must hold at least one window
   FEPLB_REQUIRE(!do_w || R_cap >= 32, FEPLB_ESHAPE, "grouped_ffn_backward: WGRAD needs R_cap >= 32 (R_cap=%d)", R_cap);
   FEPLB_REQUIRE(offsets, FEPLB_EINVAL, "grouped_ffn_backward: null offsets");
   // column offsets inside a row travel as 32-bit byte offsets
@@ -210,18 +208,13 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
                     FEPLB_EALIGN, "grouped_ffn_backward: gradient of group %d not 16-byte aligned", g);
     }
   }
-  const size_t order_at = table_bytes(R_cap, ng);
   {
-    const size_t need = order_at + FEPLB_MAX_GROUPS * sizeof(int);
+    const size_t need = table_bytes(R_cap, ng) + FEPLB_MAX_GROUPS * sizeof(int);
     FEPLB_REQUIRE(ws && ws_bytes >= need, FEPLB_EWORKSPACE, "grouped_ffn_backward: workspace %zu < %zu", ws_bytes, need);
     FEPLB_REQUIRE(feplb::aligned16(ws), FEPLB_EALIGN, "grouped_ffn_backward: workspace not 16-byte aligned");
   }
   hipStream_t s = (hipStream_t)stream;
   const size_t df = (size_t)d * f;
-  // the order in which the weight-gradient grid walks the groups is rebuilt by every WGRAD call
-  if (do_w && R_cap > 0)
-    FEPLB_HIP(feplb::launch_wgrad_order(offsets, g_begin, ng, R_cap, (int*)((char*)ws + order_at), s));
-  const int* order = (const int*)((const char*)ws + order_at);
   if (do_t) {
     // per group: Wd^T [d,f], then Wg^T [f,d] and Wu^T [f,d], the last two forming [2f,d]
     uint16_t* wt0 = (uint16_t*)WT;
@@ -237,14 +230,14 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
     gu_tab.w1[g] = direct ? w_up[g] : nullptr;
   }
   if (do_w && R_cap > 0)   // dW_down = H^T dYp: before DGRAD, which does not touch H or dYp
-    FEPLB_HIP(feplb::launch_wgrad(H, f, f, dYp, d, d, offsets, order, g_begin, ng, R_cap, dw_down, nullptr, d, d, phases & FEPLB_BWD_ACCUMULATE, s));
+    FEPLB_HIP(feplb::launch_wgrad(H, f, f, dYp, d, d, offsets, g_begin, ng, R_cap, dw_down, nullptr, d, d, phases & FEPLB_BWD_ACCUMULATE, s));
   if (do_d && R_cap > 0) {   // dH = dYp Wd^T, turned into [da | db] in place over the saved [p | q]
     const feplb::GroupedGemm a{dYp, d, nullptr, 0, 1, offsets, g_begin, ng, R_cap, d, f, &down_tab, direct ? d : f, direct, d,
                                nullptr, 0, AB, 2 * f};
     FEPLB_HIP(feplb::launch_dswiglu(a, s));
   }
   if (do_w && R_cap > 0)   // [dW_gate | dW_up] = Xp^T [da | db]
-    FEPLB_HIP(feplb::launch_wgrad(Xp, d, d, AB, 2 * f, 2 * f, offsets, order, g_begin, ng, R_cap, dw_gate, dw_up, f, f, phases & FEPLB_BWD_ACCUMULATE, s));
+    FEPLB_HIP(feplb::launch_wgrad(Xp, d, d, AB, 2 * f, 2 * f, offsets, g_begin, ng, R_cap, dw_gate, dw_up, f, f, phases & FEPLB_BWD_ACCUMULATE, s));
   if (do_d && R_cap > 0) {   // dXp = [da | db] [Wg | Wu]^T
     const feplb::GroupedGemm a{AB, 2 * f, nullptr, 0, 1, offsets, g_begin, ng, R_cap, 2 * f, d, &gu_tab, direct ? f : d, direct,
                                direct ? f : 2 * f, dXp, d, nullptr, 0};

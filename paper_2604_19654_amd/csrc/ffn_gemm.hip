@@ -116,15 +116,14 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
       for (int nj = 0; nj < NJ; ++nj)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[hf][mi][nj][v] = 0.f;
-  auto none = [](int) {};
   const int blocks32 = (rows + 32 * WR - 1 - wm * 32) / (32 * WR);   // row blocks of this wave that hold rows
   static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
   if (blocks32 >= MI) {
-    Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);
+    Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
   } else if (blocks32 == 1) {
-    Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);
+    Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
   } else {
-    Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, none, none, acc);   // its loads and barriers only
+    Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);   // its loads and barriers only
     return;
   }
 

@@ -141,12 +141,11 @@ struct PanelGemm {
   }
 
   // issue_a(stage, t, i), issue_b(stage, u, i): load i of this wave's share of tile t / half tile u to LDS
-  // byte address `stage`; each operand's loads are asked for in order.  landed_a(t), landed_b(u): called when
-  // this wave's share has landed, before the barrier that publishes it.  ME: this wave's row blocks that hold
+  // byte address `stage`; each operand's loads are asked for in order.  ME: this wave's row blocks that hold
   // rows (0 .. MI); the other accumulators are left alone.  U = 2 x the number of k tiles.
-  template <int ME, class IA, class IB, class FA, class FB>
+  template <int ME, class IA, class IB>
   static __device__ __forceinline__ void run(char* lds, int U, const FragA& fa, const FragB& fb, IA&& issue_a, IB&& issue_b,
-                                             FA&& landed_a, FB&& landed_b, f32x16 (&acc)[2][MI][NJ]) {
+                                             f32x16 (&acc)[2][MI][NJ]) {
     char* const lds_b = lds + DA * A_BYTES;
     const uint32_t a_off = lds_offset(lds), b_off = lds_offset(lds_b);
     bf16x8 af[4][ME > 0 ? ME : 1];
@@ -197,8 +196,6 @@ struct PanelGemm {
       });
     });
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(in_flight_start(), 15));
-    landed_a(0);
-    landed_b(0);
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) read_a(0, ks);
@@ -222,8 +219,6 @@ struct PanelGemm {
       slice(std::integral_constant<int, 1>{});
       slice(std::integral_constant<int, 2>{});
       __builtin_amdgcn_s_waitcnt(waitcnt_imm(in_flight(half == 1), 0));
-      landed_b(u + 1);
-      if (half == 0) landed_a(u / 2 + 1);
       __syncthreads();
       slot(sc, u, std::integral_constant<int, 0>{});
       read_b(sb_next, 0);

@@ -31,7 +31,7 @@ class FfnTrainingStep:
         self.ws = torch.empty((B.feplb_grouped_ffn_workspace_bytes(R, G),), dtype=torch.uint8, device=dev)
 
     def _need_rows(self, t, name):
-        # the kernels size their grids by R_cap and the weight gradients read whole 32-row windows
+        # the kernels size their grids by R_cap and the weight gradients want that many rows too
         if t.shape[0] < self.R_cap or t.shape[1] != self.d:
             raise B.FeplbError(f"{name} must be [{self.R_cap}, {self.d}] (rows past the last group are not used), "
                                f"got {tuple(t.shape)}")

@@ -185,6 +185,53 @@ def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d,
                 assert (AB[R:].float() == 512.0).all() and (dXp[R:].float() == 512.0).all()
 
 
+@pytest.mark.parametrize("d,f", [(512, 256), (1024, 768)])
+def test_weight_gradients_at_the_edges_of_their_shapes(d, f):
+    # The tile shape is picked from the row capacity and the matrices: 64 x 128 and 128 x 256 tiles at the two capacities
+    # for the smaller matrices, 128 x 256 and 256 x 256 for the larger.  Every element is the same chain of MFMAs in all of
+    # them, so the bytes must be equal.  Group sizes lie at the edges of the 64-row steps and of their four slices; one
+    # group's rows are NaN in every operand, and so are the rows past the last group: neither may reach another group.
+    # Adding to gradients is one more fp32 addition per element.
+    sizes = [1, 15, 16, 17, 63, 64, 65, 0, 127, 128, 129, 191, 193, 257, 40, 300, 2]
+    poisoned = 14
+    say(f"ffn weight gradients d={d} f={f}")
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    R, G = int(offsets[-1]), len(sizes)
+    gen = torch.Generator().manual_seed(41)
+    data = [torch.randn((R, c), generator=gen).to(torch.bfloat16) for c in (d, f, 2 * f, d)]   # Xp, H, da | db, dYp
+    for t in data:
+        t[offsets[poisoned]: offsets[poisoned + 1]] = float("nan")
+    off = torch.from_numpy(offsets).to(DEV)
+    nothing = [None] * G
+    ws = torch.empty((B.feplb_grouped_ffn_workspace_bytes(100000, G),), dtype=torch.uint8, device=DEV)
+    first = None
+    for R_cap in (R, 100000):
+        bufs = [torch.full((R_cap, t.shape[1]), float("nan"), dtype=torch.bfloat16, device=DEV) for t in data]
+        for buf, t in zip(bufs, data):
+            buf[:R] = t.to(DEV)
+        Xp, H, AB, dYp = bufs
+        for phases in (B.BWD_WGRAD, B.BWD_WGRAD | B.BWD_ACCUMULATE):
+            dW = [torch.full((G,) + sh, 1.5, dtype=torch.float32, device=DEV) for sh in ((d, f), (d, f), (f, d))]
+            B.feplb_grouped_ffn_backward(Xp, off, 0, G, d, f, nothing, nothing, nothing, H, AB, dYp, dYp,
+                                         *[list(w.unbind(0)) for w in dW], phases=phases, ws=ws)
+            torch.cuda.synchronize()
+            if first is None:
+                first = dW
+                x, h, ab, dy = (f64(t) for t in data)
+                for g in range(G):
+                    lo, hi = offsets[g], offsets[g + 1]
+                    if g == poisoned:
+                        assert all(torch.isnan(w[g]).all() for w in dW)
+                        continue
+                    for w, want in zip(dW, (x[lo:hi].T @ ab[lo:hi, :f], x[lo:hi].T @ ab[lo:hi, f:], h[lo:hi].T @ dy[lo:hi])):
+                        # exact products, fp32 sums of at most 300 terms of size 1: 300 * 2^-24 * sum of magnitudes
+                        assert np.abs(f64(w[g]) - want).max() <= 300 * 2.0 ** -24 * 300
+            else:
+                add = 1.5 if phases & B.BWD_ACCUMULATE else 0.0
+                for w, w0 in zip(dW, first):
+                    assert torch.equal(torch.nan_to_num(w), torch.nan_to_num(w0 + add))
+
+
 def test_grouped_ffn_backward_larger_ragged_case_and_repeatability():
     # several row tiles per group, contraction tails of every residue class, f != d
     sizes = [517, 2, 1031, 0, 255, 770, 96, 1]
