@@ -9,13 +9,13 @@
 //   1. chunk_hist : per-chunk, per-expert counts (LDS histogram per wave)
 //   2. chunk_scan : per expert, exclusive prefix over chunks -> the ordinal of
 //                   the first occurrence in each chunk, and the expert's total
-//   3. group_offsets : sizes of the ordinal windows -> offsets[G+1]; per-expert
-//                   chains of groups for the lookup in step 4
-//   4. assign_rows: per chunk, walk 64 assignments at a time; the ordinal inside
-//                   the slice comes from a ballot-based match of equal experts,
-//                   the running ordinal per expert lives in LDS; the window
-//                   that contains the ordinal gives the row
-//   5. gather_rows: Xp[r,:] = X[row_src[r] / k, :], one wavefront per row,
+//   3. assign_rows: sizes of the ordinal windows -> offsets[G+1], and per-expert
+//                   chains of groups; then per chunk, walk 64 assignments at a
+//                   time; the ordinal inside the slice comes from a ballot-based
+//                   match of equal experts, the running ordinal per expert lives
+//                   in LDS; the window that contains the ordinal gives the row
+// (small batches: all three in one workgroup, permute_one_kernel)
+//   4. gather_rows: Xp[r,:] = X[row_src[r] / k, :], one wavefront per row,
 //                   16-byte lanes (pure HBM traffic: 2*R*d*2 bytes)
 #include "common.h"
 
@@ -83,84 +83,101 @@ __global__ __launch_bounds__(BLOCK) void chunk_scan_kernel(int* __restrict__ chu
   if (lane == 63) total[e] = incl;
 }
 
-// meta layout (ints): head[E] | next[G] | lo[G] | hi[G] | start[G]
-__global__ __launch_bounds__(FEPLB_MAX_GROUPS) void group_offsets_kernel(
-    GroupTable tab, int G, int E, const int* __restrict__ total, int* offsets,
-    int* __restrict__ meta, int append) {
-  __shared__ int scan[FEPLB_MAX_GROUPS];
-  const int g = threadIdx.x;
-  // appending: the rows of these groups follow those of an earlier call, whose end is offsets[0]
-  const int base = append ? offsets[0] : 0;
-  __syncthreads();   // every thread has read the base before offsets[0] is written again
-  int size = 0, lo = 0, hi = 0, e = -1;
+// LDS tables of the groups: the groups of expert e are the chain head[e], next[.] in table order (end: G or more)
+struct GroupTables {
+  int *head, *next, *lo, *hi, *start, *sums;   // [E], 4 x [G], [2]; row = start + ordinal
+  static __host__ __device__ int ints(int E, int G) { return E + 4 * G + 2; }
+  __device__ GroupTables(int* lds, int E, int G)
+      : head(lds), next(head + E), lo(next + G), hi(lo + G), start(hi + G), sums(start + G) {}
+};
+
+// Made by every workgroup for itself, by all its threads (at least FEPLB_MAX_GROUPS): in a launch of its own the
+// tables cost a launch and a trip through memory, and one thread linked the chains (the whole permutation inside a graph:
+// T = 8192, k = 8, G = 16 18.1 -> 14.8 us; T = 32768, G = 32 30.8 -> 25.9 us).  total[e]: occurrences of expert e; base: first row; offsets: written if given.
+__device__ __forceinline__ void make_group_tables(const GroupTable& tab, int G, int E, const int* total, int base,
+                                                  const GroupTables& t, int* offsets, bool append) {
+  static_assert(FEPLB_MAX_GROUPS == 128, "one group per thread of two wavefronts");
+  const int g = threadIdx.x, lane = g % 64;
+  for (int i = g; i < E; i += blockDim.x) t.head[i] = G;
+  int lo = 0, hi = 0, e = -1, size = 0;
   if (g < G) {
     e = tab.g[g].expert;
     lo = tab.g[g].ord_lo;
     hi = tab.g[g].ord_hi;
-    const int n = ((unsigned)e < (unsigned)E) ? total[e] : 0;
+    const int n = total[e];   // the host has checked every e
     size = max(0, min(hi, n) - min(lo, n));
   }
-  scan[g] = size;
-  __syncthreads();
-  for (int d = 1; d < FEPLB_MAX_GROUPS; d <<= 1) {
-    const int v = g >= d ? scan[g - d] : 0;
-    __syncthreads();
-    scan[g] += v;
-    __syncthreads();
+  int incl = size;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
   }
-  int* head = meta;
-  int* next = meta + E;
-  int* glo = next + G;
-  int* ghi = glo + G;
-  int* gstart = ghi + G;
+  if (g < FEPLB_MAX_GROUPS && lane == 63) t.sums[g / 64] = incl;
+  __syncthreads();
   if (g < G) {
-    const int off = base + scan[g] - size;
-    offsets[g] = off;
-    glo[g] = lo;
-    ghi[g] = hi;
-    gstart[g] = off - lo;  // row = start + ordinal
-    if (g == G - 1) offsets[G] = base + scan[g];
-  }
-  if (G == 0 && g == 0) offsets[0] = base;
-  for (int i = g; i < E; i += FEPLB_MAX_GROUPS) head[i] = -1;
-  __syncthreads();
-  if (g == 0) {
-    for (int i = G - 1; i >= 0; --i) {
-      const int ei = tab.g[i].expert;
-      if ((unsigned)ei < (unsigned)E) {
-        next[i] = head[ei];
-        head[ei] = i;
-      } else {
-        next[i] = -1;
-      }
+    const int end = base + incl + (g >= 64 ? t.sums[0] : 0), off = end - size;
+    t.lo[g] = lo;
+    t.hi[g] = hi;
+    t.start[g] = off - lo;
+    atomicMin(&t.head[e], g);
+    int next = G;
+    for (int h = G - 1; h >= 0; --h)
+      if (h > g && tab.g[h].expert == e) next = h;
+    t.next[g] = next;
+    if (offsets) {
+      if (g > 0 || !append) offsets[g] = off;   // appending: offsets[0] is the base, it stays
+      if (g == G - 1) offsets[G] = end;
     }
   }
+  if (G == 0 && g == 0 && offsets && !append) offsets[0] = base;
+  __syncthreads();
 }
 
+// rows of 64 consecutive assignments, one per lane (e < 0: none); run[e]: the wavefront's next ordinal of expert e
+__device__ __forceinline__ int next_row(int e, int nbits, int G, volatile int* run, const GroupTables& t) {
+  const int lane = threadIdx.x % 64;
+  const bool valid = e >= 0;
+  unsigned long long same = __ballot(valid);
+  for (int b = 0; b < nbits; ++b) {
+    const bool bit = (e >> b) & 1;
+    const unsigned long long m = __ballot(bit);
+    same &= bit ? m : ~m;
+  }
+  int row = -1;
+  if (valid) {
+    const int base = run[e];
+    const int o = base + __popcll(same & ((1ull << lane) - 1ull));
+    if ((same >> lane) == 1ull) run[e] = base + __popcll(same);  // highest lane of the set
+    for (int g = t.head[e]; g < G; g = t.next[g])
+      if (o >= t.lo[g] && o < t.hi[g]) {
+        row = t.start[g] + o;
+        break;
+      }
+  }
+  __builtin_amdgcn_wave_barrier();
+  return row;
+}
+
+__device__ __forceinline__ int bits_for(int E) { return E > 1 ? 32 - __builtin_clz(E - 1) : 0; }
+
 __global__ __launch_bounds__(BLOCK) void assign_rows_kernel(
-    const int* __restrict__ ids, long long A, int E, int G, int nchunks, int chunk,
-    const int* __restrict__ chunk_base, const int* __restrict__ meta, int R_cap,
+    GroupTable tab, const int* __restrict__ ids, long long A, int E, int G, int nchunks, int chunk,
+    const int* __restrict__ chunk_base, const int* __restrict__ total, int R_cap, int* offsets,
     int* __restrict__ row_src, int* __restrict__ inv, int append) {
   extern __shared__ int lds[];
-  // LDS: run[WAVES][E] | head[E] | next[G] lo[G] hi[G] start[G]
-  volatile int* run_all = lds;
-  int* head = lds + WAVES * E;
-  int* next = head + E;
-  int* glo = next + G;
-  int* ghi = glo + G;
-  int* gstart = ghi + G;
-  for (int i = threadIdx.x; i < E + 4 * G; i += BLOCK) head[i] = meta[i];
+  // LDS: run[WAVES][E] | group tables
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int c = blockIdx.x * WAVES + wave;
-  volatile int* run = run_all + wave * E;
+  volatile int* run = lds + wave * E;
   if (c < nchunks)
     for (int e = lane; e < E; e += 64) run[e] = chunk_base[(long long)c * E + e];
-  __syncthreads();
+  const GroupTables t(lds + WAVES * E, E, G);
+  // appending: the rows of these groups follow those of an earlier call, whose end is offsets[0]
+  make_group_tables(tab, G, E, total, append ? offsets[0] : 0, t, blockIdx.x == 0 ? offsets : nullptr, append);
   if (c >= nchunks) return;
-  int nbits = 0;
-  while ((1 << nbits) < E) ++nbits;
+  const int nbits = bits_for(E);
   const long long a0 = (long long)c * chunk;
-  const unsigned long long below = (1ull << lane) - 1ull;
   for (int i = 0; i < chunk; i += 64) {
     const long long a = a0 + i + lane;
     if (a0 + i >= A) break;  // uniform across the wave
@@ -169,28 +186,70 @@ __global__ __launch_bounds__(BLOCK) void assign_rows_kernel(
       e = ids[a];
       if ((unsigned)e >= (unsigned)E) e = -1;
     }
-    const bool valid = e >= 0;
-    unsigned long long same = __ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
-      const bool bit = (e >> b) & 1;
-      const unsigned long long m = __ballot(bit);
-      same &= bit ? m : ~m;
-    }
-    int row = -1;
-    if (valid) {
-      const int base = run[e];
-      const int o = base + __popcll(same & below);
-      if ((same >> lane) == 1ull) run[e] = base + __popcll(same);  // highest lane of the set
-      for (int g = head[e]; g >= 0; g = next[g])
-        if (o >= glo[g] && o < ghi[g]) {
-          row = gstart[g] + o;
-          break;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
+    const int row = next_row(e, nbits, G, run, t);
     if (a < A) {
       if (!append || row >= 0) inv[a] = row;   // appending leaves the other calls' entries alone
       if (row >= 0 && row < R_cap) row_src[row] = (int)a;
+    }
+  }
+}
+
+// All of it in one workgroup, for batches of at most ONE_WAVES * 64 * SLICES assignments: wavefront w owns a run of
+// 64 SLICES assignments, kept in registers between the counting and the walk, so the batch is read once and the
+// histograms and bases never leave LDS.  Bound by latency: the walk takes about 0.9 us
+// per slice.  Inside a graph, against the launches one after the other: T = 96, k = 8, E = 128 14.3 -> 4.8 us;
+// T = 512, k = 2, E = 8 12.2 -> 4.3 us; T = 512, k = 8, E = 128 15.1 -> 7.9 us.
+constexpr int ONE_WAVES = 16;
+constexpr int ONE_MAX_E = 512;       // 16 histograms, the totals and the tables in 64 KB of LDS
+constexpr int ONE_MAX_A = ONE_WAVES * 64 * 4;
+template <int SLICES>
+__global__ __launch_bounds__(ONE_WAVES * 64) void permute_one_kernel(GroupTable tab, const int* __restrict__ ids, int A,
+                                                                     int E, int G, int R_cap, int* offsets,
+                                                                     int* __restrict__ row_src, int* __restrict__ inv,
+                                                                     int append) {
+  extern __shared__ int lds[];
+  // LDS: run[ONE_WAVES][E] | total[E] | group tables
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  int* const total = lds + ONE_WAVES * E;
+  const GroupTables t(total + E, E, G);
+  const int a0 = wave * (64 * SLICES) + lane;
+  int e[SLICES];
+#pragma unroll
+  for (int i = 0; i < SLICES; ++i) {
+    const int a = a0 + i * 64;
+    e[i] = a < A ? ids[a] : -1;
+    if ((unsigned)e[i] >= (unsigned)E) e[i] = -1;
+  }
+  const int base = append ? offsets[0] : 0;   // offsets[0] is not written when appending
+  for (int i = threadIdx.x; i < ONE_WAVES * E; i += ONE_WAVES * 64) lds[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < SLICES; ++i)
+    if (e[i] >= 0) atomicAdd(&lds[wave * E + e[i]], 1);
+  __syncthreads();
+  for (int x = threadIdx.x; x < E; x += ONE_WAVES * 64) {
+    int n[ONE_WAVES];
+#pragma unroll
+    for (int w = 0; w < ONE_WAVES; ++w) n[w] = lds[w * E + x];
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < ONE_WAVES; ++w) {
+      lds[w * E + x] = sum;
+      sum += n[w];
+    }
+    total[x] = sum;
+  }
+  __syncthreads();
+  make_group_tables(tab, G, E, total, base, t, offsets, append);
+  const int nbits = bits_for(E);
+#pragma unroll
+  for (int i = 0; i < SLICES; ++i) {
+    const int a = a0 + i * 64;
+    if (a - lane >= A) break;   // uniform across the wave
+    const int row = next_row(e[i], nbits, G, lds + wave * E, t);
+    if (a < A) {
+      if (!append || row >= 0) inv[a] = row;
+      if (row >= 0 && row < R_cap) row_src[row] = a;
     }
   }
 }
@@ -231,7 +290,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
   int nchunks, chunk;
-  size_t hist_off, total_off, meta_off, bytes;
+  size_t hist_off, total_off, bytes;
 };
 
 Layout layout(long long A, int E, int G) {
@@ -243,7 +302,7 @@ Layout layout(long long A, int E, int G) {
   off = align_up(off + (size_t)(L.nchunks > 0 ? L.nchunks : 1) * E * sizeof(int), 256);
   L.total_off = off;
   off = align_up(off + (size_t)E * sizeof(int), 256);
-  L.meta_off = off;
+  // the group tables' place: callers size and share workspaces by this formula, so it stays in the sum
   off = align_up(off + ((size_t)E + 4 * (size_t)(G > 0 ? G : 1)) * sizeof(int), 256);
   L.bytes = off;
   return L;
@@ -300,23 +359,30 @@ int32_t permute_impl(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E,
   char* base = (char*)ws;
   int* hist = (int*)(base + L.hist_off);
   int* total = (int*)(base + L.total_off);
-  int* meta = (int*)(base + L.meta_off);
-  const int cblocks = (L.nchunks + WAVES - 1) / WAVES;
-  if (L.nchunks > 0) {
-    hipLaunchKernelGGL(chunk_hist_kernel, dim3(cblocks), dim3(BLOCK),
-                       (size_t)WAVES * E * sizeof(int), s, topk_ids, A, E, L.nchunks, L.chunk, hist);
-    FEPLB_LAUNCH_CHECK("chunk_hist_kernel");
-  }
-  hipLaunchKernelGGL(chunk_scan_kernel, dim3((E + WAVES - 1) / WAVES), dim3(BLOCK), 0, s, hist, E,
-                     L.nchunks, total);
-  FEPLB_LAUNCH_CHECK("chunk_scan_kernel");
-  hipLaunchKernelGGL(group_offsets_kernel, dim3(1), dim3(FEPLB_MAX_GROUPS), 0, s, tab, G, E, total,
-                     offsets, meta, append);
-  FEPLB_LAUNCH_CHECK("group_offsets_kernel");
-  if (L.nchunks > 0) {
-    const size_t lds = ((size_t)WAVES * E + E + 4 * (size_t)G) * sizeof(int);
-    hipLaunchKernelGGL(assign_rows_kernel, dim3(cblocks), dim3(BLOCK), lds, s, topk_ids, A, E, G,
-                       L.nchunks, L.chunk, hist, meta, R_cap, row_src, inv, append);
+  // One workgroup up to 4096 assignments, where it takes 8.6 us (E = 512) and the three launches 14.9; with 16 slices
+  // per wavefront it took 16.7 us at 6018 assignments and 21.8 at 16384 (three launches: 12 to 15.7).
+  if (A <= ONE_MAX_A && E <= ONE_MAX_E) {
+    const size_t lds = ((size_t)(ONE_WAVES + 1) * E + GroupTables::ints(E, G)) * sizeof(int);
+#define FEPLB_PERMUTE_ONE(S)                                                                             \
+  hipLaunchKernelGGL((permute_one_kernel<S>), dim3(1), dim3(ONE_WAVES * 64), lds, s, tab, topk_ids, (int)A, E, G, \
+                     R_cap, offsets, row_src, inv, append)
+    if (A <= ONE_WAVES * 64) FEPLB_PERMUTE_ONE(1);
+    else FEPLB_PERMUTE_ONE(4);
+#undef FEPLB_PERMUTE_ONE
+    FEPLB_LAUNCH_CHECK("permute_one_kernel");
+  } else {
+    const int blocks = L.nchunks > 0 ? (L.nchunks + WAVES - 1) / WAVES : 1;   // no chunk: the offsets alone
+    if (L.nchunks > 0) {
+      hipLaunchKernelGGL(chunk_hist_kernel, dim3(blocks), dim3(BLOCK), (size_t)WAVES * E * sizeof(int), s, topk_ids, A,
+                         E, L.nchunks, L.chunk, hist);
+      FEPLB_LAUNCH_CHECK("chunk_hist_kernel");
+    }
+    hipLaunchKernelGGL(chunk_scan_kernel, dim3((E + WAVES - 1) / WAVES), dim3(BLOCK), 0, s, hist, E,
+                       L.nchunks, total);
+    FEPLB_LAUNCH_CHECK("chunk_scan_kernel");
+    const size_t lds = ((size_t)WAVES * E + GroupTables::ints(E, G)) * sizeof(int);
+    hipLaunchKernelGGL(assign_rows_kernel, dim3(blocks), dim3(BLOCK), lds, s, tab, topk_ids, A, E, G,
+                       L.nchunks, L.chunk, hist, total, R_cap, offsets, row_src, inv, append);
     FEPLB_LAUNCH_CHECK("assign_rows_kernel");
   }
   if (X && Xp && R_cap > 0 && d > 0) {

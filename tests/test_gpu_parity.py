@@ -108,6 +108,43 @@ def test_permute_parity(T, E, k, d, skew, seed):
         assert torch.equal(Xp.cpu()[:R], want)            # byte copy: bit-exact
 
 
+@pytest.mark.parametrize("A,E,G", [(1, 8, 1), (1023, 8, 8), (1024, 3, 5), (1025, 512, 128), (4096, 512, 128),
+                                   (4097, 130, 65), (4095, 512, 128), (4096, 513, 128), (16385, 128, 128),
+                                   (70001, 128, 100)])
+def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
+    # up to 4096 assignments over at most 512 experts one workgroup does it all, 1 or 4 slices of 64 per wavefront;
+    # groups in both wavefronts of the table, several windows per expert, ids that name no expert
+    say(f"permute A={A} E={E} G={G}")
+    rng = np.random.default_rng(A + E)
+    ids = np.minimum(rng.zipf(1.3, size=(A, 1)) - 1, E - 1).astype(np.int32)
+    ids[rng.random((A, 1)) < 0.3] = rng.integers(0, E)
+    n = np.bincount(ids[:, 0], minlength=E)
+    ids[rng.random((A, 1)) < 0.02] = -1
+    ids[rng.random((A, 1)) < 0.02] = E
+    groups = []
+    for i in range(G):
+        e = i % min(E, 50)
+        w = i // min(E, 50)
+        step = max(1, int(n[e]) // 3)
+        groups.append((e, w * step, (w + 1) * step if w < G // min(E, 50) else fe.ORD_MAX))
+    groups = [groups[i] for i in rng.permutation(G)]
+    off_o, src_o, inv_o = orc.permute(ids, groups)
+    R = int(off_o[-1])
+    d_ids = torch.from_numpy(ids).to(DEV)
+    for cut in (0, G // 2):        # in one call, and appended to the first groups
+        R_cap = max(R - 1, 1)      # one row too many: offsets and inv tell the truth, row_src ends
+        off = torch.full((G + 1,), -5, dtype=torch.int32, device=DEV)
+        src = torch.full((R_cap + 8,), -7, dtype=torch.int32, device=DEV)
+        inv = torch.full((A,), -9, dtype=torch.int32, device=DEV)
+        fe.feplb_permute(d_ids, E, groups[: cut or G], None, R_cap, None, off[: (cut or G) + 1], src, inv)
+        if cut:
+            fe.feplb_permute(d_ids, E, groups[cut:], None, R_cap, None, off[cut:], src, inv, append=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(off.cpu().numpy(), off_o) and np.array_equal(inv.cpu().numpy(), inv_o)
+        have = min(R, R_cap)
+        assert np.array_equal(src.cpu().numpy()[:have], src_o[:have]) and (src.cpu().numpy()[have:] == -7).all()
+
+
 def test_permute_in_two_calls_equals_one_call():
     # static groups first, replicas appended later (Section 2.3 timeline): same offsets, row_src, inv, Xp
     T, E, k, d = 3000, 64, 4, 128
