@@ -280,10 +280,10 @@ def _rooflines(name, res):
                 "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic, "avg_launch_ms": t_ms, "algorithmic_bytes_per_launch": nbytes}
 
     out = {
-        "gate_up": mfma("grouped_gemm_kernel<0,true,false> (gate/up GEMM + SwiGLU)", "gate_up", 4.0 * d * f, "gate_up_bytes"),
-        "down": mfma("grouped_gemm_kernel<1,%s,false> (down GEMM)" % ("true" if yp_bytes == 2 else "false"), "down", 2.0 * d * f, "down_bytes"),
+        "gate_up": mfma("panel_gemm_kernel<0> (gate/up GEMM + SwiGLU)", "gate_up", 4.0 * d * f, "gate_up_bytes"),
+        "down": mfma("panel_gemm_kernel<1> (down GEMM)", "down", 2.0 * d * f, "down_bytes"),
         "combine": hbm("combine_kernel", ms["combine"], R * d * yp_bytes + T * d * 2 + T * k * 8),
-        "permute_with_gather": hbm("chunk_hist + chunk_scan + group_offsets + assign_rows + gather_rows_kernel",
+        "permute_with_gather": hbm("index kernels of the permutation + gather_rows_kernel",
                                    res["permute_with_gather_ms"], 2 * R * d * 2 + T * k * 8 + R * 4),
         "row_gather_alone": hbm("gather_rows_kernel (the step above minus its index kernels)",
                                 res["hbm_kernels"]["row_gather_alone"]["ms"], 2 * R * d * 2),
