@@ -31,13 +31,29 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
   return __uint_as_float(u);
 }
 
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_move(unsigned long long v) {
+  const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  return ((unsigned long long)h << 32) | l;
+}
+
+__device__ __forceinline__ unsigned long long max64(unsigned long long a, unsigned long long b) { return a > b ? a : b; }
+
+// The maximum of SG >= 8 neighbouring lanes, in all of them.  The chain of these exchanges is what a token waits
+// for k times over: within rows of 16 lanes they are register moves (DPP) instead of trips through the LDS crossbar.
+// The mirrors pair lanes of the two halves, whose lanes all hold the same value by then.  With the counters'
+// clearing launch, inside a graph: T = 96, k = 8, E = 128 8.0 -> 7.1 us, T = 1003, k = 6, E = 64 7.2 -> 6.7, T = 16000,
+// k = 8, E = 256 47.9 -> 45.1: from a thousand wavefronts on the 64-bit compares bound it, not the exchanges.
 template <int SG>
 __device__ __forceinline__ unsigned long long group_max(unsigned long long v) {
-#pragma unroll
-  for (int m = SG / 2; m >= 1; m >>= 1) {
-    unsigned long long o = __shfl_xor(v, m, SG);
-    v = o > v ? o : v;
-  }
+  v = max64(v, dpp_move<0xB1>(v));                          // quad_perm [1,0,3,2]
+  v = max64(v, dpp_move<0x4E>(v));                          // quad_perm [2,3,0,1]
+  v = max64(v, dpp_move<0x141>(v));                         // row_half_mirror: the other quad of eight lanes
+  if constexpr (SG >= 16) v = max64(v, dpp_move<0x140>(v)); // row_mirror: the other eight of a row
+  if constexpr (SG >= 32) v = max64(v, __shfl_xor(v, 16, SG));
+  if constexpr (SG >= 64) v = max64(v, __shfl_xor(v, 32, SG));
   return v;
 }
 
