@@ -58,13 +58,15 @@ __device__ __forceinline__ int group_of_rank(const int* __restrict__ offsets, in
   return (rank < n0 ? 0 : 64) + __ffsll((unsigned long long)hit) - 1;
 }
 
-// 16-byte-per-lane buffer load into LDS, as load_to_lds_16; lanes at or past `bytes` from base bring zeros.  The s_nop is
-// the wait state that a write of M0 needs ahead of an LDS-DMA load.
+// 16-byte-per-lane buffer load into LDS, as load_to_lds_16; lanes at or past `bytes` from base bring zeros.  `bytes` is what
+// keeps rows past the group's end out, and the compiler computes it with vector instructions and a readfirstlane right
+// ahead of the load: the 5 wait states that the descriptor then needs stand here (s_mov_b32 counts as 1, s_nop 3 as 4).
+// With fewer the load could still see the bound of an earlier step.
 __device__ __forceinline__ void bounded_load_to_lds_16(const char* base, uint32_t bytes, uint32_t lane_off, uint32_t lds_base) {
   const uint64_t v = (uint64_t)(uintptr_t)base;
   const u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) & 0xffffu,
                       (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
                :
                : "v"(lane_off), "s"(rsrc), "s"(lds_base)
                : "memory", "m0");

@@ -21,8 +21,10 @@ constexpr int XCDS = 8;   // workgroups are dealt round-robin to the 8 XCDs, eac
 // inline assembly so that the loads' completion is tracked by the explicit s_waitcnt vmcnt(n)
 // of the pipeline below: the compiler's own tracking would wait for ALL outstanding loads
 // before any LDS read in a loop, i.e. also for the tiles requested for later steps.
-// The s_nop is the wait state that a write of M0 needs ahead of an LDS-DMA load, which the compiler does not add in
-// inline assembly.  The address is a wave-uniform base (scalar register pair) plus a 32-bit per-lane byte offset.
+// The compiler adds no wait states inside or ahead of inline assembly.  The load needs 1 after the write of M0, which is the
+// s_nop, and 5 after a vector instruction that wrote its scalar address: the kernels' base addresses are wave-uniform
+// scalars that only scalar instructions advance (a test reads the built code for it; waiting 5 at each load all the same
+// made the large forward cases 0.7 % slower).  The per-lane byte offset has 32 bits.
 __device__ __forceinline__ void load_to_lds_16(const char* base, uint32_t lane_off, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
