@@ -224,12 +224,15 @@ int32_t feplb_grouped_ffn_static(const void* Xp, const int32_t* row_src, int32_t
  *   dw_gate, dw_up, dw_down  host arrays of (g_end) device pointers indexed by g:
  *           fp32 [d,f], [d,f], [f,d]  out
  *   WT      device scratch, feplb_grouped_ffn_backward_wt_bytes(g_end - g_begin, d, f)
- *           bytes: receives the transposed weights where TRANSPOSE is asked for without DGRAD
+ *           bytes: receives the transposed weights (phase TRANSPOSE) for later calls
  *   phases  any non-empty subset of FEPLB_BWD_SCHEDULE (launches nothing),
  *           FEPLB_BWD_TRANSPOSE, FEPLB_BWD_DGRAD, FEPLB_BWD_WGRAD.  DGRAD reads the weights
- *           themselves, so with TRANSPOSE in the same call nothing is transposed; a call without
- *           TRANSPOSE may pass null entries in w_gate, w_up, w_down, and DGRAD then reads
- *           WT as a call with TRANSPOSE and without DGRAD left it.  WGRAD for the gate and up matrices
+ *           themselves where the call has them all, 16-byte aligned; a call without TRANSPOSE may leave
+ *           entries of w_gate, w_up, w_down null, and DGRAD then reads all of them from WT as the last
+ *           TRANSPOSE left it.  With FEPLB_BWD_DIRECT added, a call that lacks a weight is refused instead
+ *           (FEPLB_EINVAL, or FEPLB_EALIGN for a misaligned one) and DGRAD does not need WT: a caller
+ *           that always passes the weights asks for DGRAD | DIRECT in place of TRANSPOSE | DGRAD, and
+ *           nothing is transposed.  WGRAD for the gate and up matrices
  *           needs da | db, i.e. DGRAD in the same or an earlier call.  With
  *           FEPLB_BWD_ACCUMULATE added, WGRAD adds its results to what dw_gate, dw_up,
  *           dw_down hold (gradient accumulation over micro-batches; an empty group's
@@ -244,6 +247,7 @@ int32_t feplb_grouped_ffn_static(const void* Xp, const int32_t* row_src, int32_t
 #define FEPLB_BWD_WGRAD 8
 #define FEPLB_BWD_ALL 15
 #define FEPLB_BWD_ACCUMULATE 16
+#define FEPLB_BWD_DIRECT 32
 
 int32_t feplb_grouped_ffn_train(const void* Xp, const int32_t* row_src, int32_t T, int32_t k,
                                 const int32_t* offsets,

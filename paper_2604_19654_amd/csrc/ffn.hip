@@ -159,20 +159,23 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
                 "grouped_ffn_backward: negative size or empty range reversed");
   FEPLB_REQUIRE(g_end <= FEPLB_MAX_GROUPS, FEPLB_ESHAPE, "grouped_ffn_backward: g_end=%d above %d", g_end,
                 FEPLB_MAX_GROUPS);
-  FEPLB_REQUIRE((phases & ~(FEPLB_BWD_ALL | FEPLB_BWD_ACCUMULATE)) == 0 && (phases & FEPLB_BWD_ALL) != 0, FEPLB_EINVAL,
-                "grouped_ffn_backward: phases=%d", phases);
+  FEPLB_REQUIRE((phases & ~(FEPLB_BWD_ALL | FEPLB_BWD_ACCUMULATE | FEPLB_BWD_DIRECT)) == 0 && (phases & FEPLB_BWD_ALL) != 0,
+                FEPLB_EINVAL, "grouped_ffn_backward: phases=%d", phases);
+  FEPLB_REQUIRE(!(phases & FEPLB_BWD_DIRECT) || (phases & FEPLB_BWD_DGRAD), FEPLB_EINVAL,
+                "grouped_ffn_backward: DIRECT without DGRAD (phases=%d)", phases);
   FEPLB_REQUIRE(dxp_dtype == FEPLB_F32 || dxp_dtype == FEPLB_BF16, FEPLB_EINVAL,
                 "grouped_ffn_backward: unknown dxp_dtype %d", dxp_dtype);
   FEPLB_REQUIRE(d % 256 == 0 && f % 256 == 0 && d > 0 && f > 0, FEPLB_ESHAPE,
                 "grouped_ffn_backward: need d %% 256 == 0 and f %% 256 == 0 (d=%d f=%d)", d, f);
   const int ng = g_end - g_begin;
   if (ng == 0) return FEPLB_OK;
-  const bool asks_t = phases & FEPLB_BWD_TRANSPOSE, do_d = phases & FEPLB_BWD_DGRAD, do_w = phases & FEPLB_BWD_WGRAD;
+  const bool do_t = phases & FEPLB_BWD_TRANSPOSE, do_d = phases & FEPLB_BWD_DGRAD, do_w = phases & FEPLB_BWD_WGRAD;
+  const bool must_direct = phases & FEPLB_BWD_DIRECT;
   FEPLB_REQUIRE(!do_w || R_cap >= 32, FEPLB_ESHAPE, "grouped_ffn_backward: WGRAD needs R_cap >= 32 (R_cap=%d)", R_cap);
   FEPLB_REQUIRE(offsets, FEPLB_EINVAL, "grouped_ffn_backward: null offsets");
   // column offsets inside a row travel as 32-bit byte offsets
   FEPLB_REQUIRE((uint64_t)(2 * (size_t)f + d) * 64 * 2 <= 0xffffffffull, FEPLB_ESHAPE, "grouped_ffn_backward: d, f too large");
-  if (asks_t) {
+  if (do_t || must_direct) {
     FEPLB_REQUIRE(w_gate && w_up && w_down, FEPLB_EINVAL, "grouped_ffn_backward: null weight tables");
     for (int g = g_begin; g < g_end; ++g) {
       FEPLB_REQUIRE(w_gate[g] && w_up[g] && w_down[g], FEPLB_EINVAL, "grouped_ffn_backward: null weights of group %d", g);
@@ -180,18 +183,18 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
                     FEPLB_EALIGN, "grouped_ffn_backward: weights of group %d not 16-byte aligned", g);
     }
   }
-  if (asks_t || do_d) {
+  if (do_t || (do_d && !must_direct)) {
     const size_t need_wt = feplb_grouped_ffn_backward_wt_bytes(ng, d, f);
     FEPLB_REQUIRE(WT && wt_bytes >= need_wt, FEPLB_EWORKSPACE, "grouped_ffn_backward: WT %zu < %zu", wt_bytes, need_wt);
     FEPLB_REQUIRE(feplb::aligned16(WT), FEPLB_EALIGN, "grouped_ffn_backward: WT not 16-byte aligned");
   }
   // The input gradients read the weights themselves.  Only where they are not given (a call without TRANSPOSE may leave
-  // them out, or misaligned) are the transposes read that an earlier call with TRANSPOSE alone has left in WT.
+  // them out, or misaligned) are the transposes read that an earlier call has left in WT: every call that asks for them
+  // writes them, since it cannot know whether a later one will rely on them.
   bool direct = do_d && w_gate && w_up && w_down;
   for (int g = g_begin; direct && g < g_end; ++g)
     direct = w_gate[g] && w_up[g] && w_down[g] && feplb::aligned16(w_gate[g]) && feplb::aligned16(w_up[g]) &&
              feplb::aligned16(w_down[g]);
-  const bool do_t = asks_t && !do_d;
   if (do_d) {
     FEPLB_REQUIRE(AB && dYp && dXp, FEPLB_EINVAL, "grouped_ffn_backward: null AB/dYp/dXp");
     FEPLB_REQUIRE(feplb::aligned16(AB) && feplb::aligned16(dYp) && feplb::aligned16(dXp), FEPLB_EALIGN,

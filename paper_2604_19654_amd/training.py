@@ -14,7 +14,11 @@ class FfnTrainingStep:
     """Holds what feplb_grouped_ffn (training form) and feplb_grouped_ffn_backward need for G
     groups and up to R_cap permuted rows: H, the SwiGLU derivatives p|q (turned into da|db by the
     backward), Yp, dXp,
-    the fp32 weight gradients, the transposed-weight scratch and the workspace."""
+    the fp32 weight gradients, the transposed-weight scratch and the workspace.
+
+    The input gradients read the weights that a backward call passes, so a call for TRANSPOSE and DGRAD
+    together transposes nothing.  A DGRAD call that leaves weights out (None entries) needs a call for
+    TRANSPOSE without DGRAD before it, with no combined one in between; otherwise it raises FeplbError."""
 
     def __init__(self, R_cap: int, G: int, d: int, f: int, device="cuda:0", dxp_dtype=torch.float32):
         dev = torch.device(device)
@@ -29,6 +33,7 @@ class FfnTrainingStep:
         self.dW_down = [torch.empty((f, d), dtype=torch.float32, device=dev) for _ in range(G)]
         self.WT = torch.empty((max(B.feplb_grouped_ffn_backward_wt_bytes(G, d, f), 16),), dtype=torch.uint8, device=dev)
         self.ws = torch.empty((B.feplb_grouped_ffn_workspace_bytes(R, G),), dtype=torch.uint8, device=dev)
+        self._transposed = False    # WT holds the weights of the last call that asked for TRANSPOSE
 
     def _need_rows(self, t, name):
         # the kernels size their grids by R_cap and the weight gradients want that many rows too
@@ -47,9 +52,16 @@ class FfnTrainingStep:
         """dYp bf16 [R_cap,d] -> dXp; the weight gradients land in dW_gate / dW_up / dW_down."""
         self._need_rows(Xp, "Xp")
         self._need_rows(dYp, "dYp")
+        combined = phases & B.BWD_TRANSPOSE and phases & B.BWD_DGRAD
+        if combined:
+            phases = phases & ~B.BWD_TRANSPOSE | B.BWD_DIRECT
+        elif phases & B.BWD_DGRAD and not self._transposed:
+            phases |= B.BWD_DIRECT      # nothing for it in WT: a missing weight is an error
         B.feplb_grouped_ffn_backward(Xp, offsets, 0, self.G, self.d, self.f, w_gate, w_up, w_down, self.H, self.AB,
                                      dYp, self.dXp, self.dW_gate, self.dW_up, self.dW_down, WT=self.WT,
                                      phases=phases, ws=self.ws, stream=stream)
+        if combined or phases & B.BWD_TRANSPOSE:
+            self._transposed = not combined
         return self.dXp
 
 

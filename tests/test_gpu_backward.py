@@ -10,6 +10,7 @@ import torch
 
 import paper_2604_19654_amd as fe
 from paper_2604_19654_amd import binding as B
+from paper_2604_19654_amd.training import FfnTrainingStep
 from oracle import feplb_oracle as orc
 from tests.util import (f64, row_rel_err, row_rms_err, bf16_rounding_excess, BWD_RMS_TOL, BWD_MAX_TOL, FORMAT_NSIGMA,
                         h_rounding_variance)
@@ -183,6 +184,65 @@ def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d,
                 torch.cuda.synchronize()
                 assert torch.equal(AB[:R], r["dAB"][:R]) and torch.equal(dXp[:R], r["dXp"][:R].to(dxp_dtype))
                 assert (AB[R:].float() == 512.0).all() and (dXp[R:].float() == 512.0).all()
+
+
+def test_transposes_serve_later_calls_that_leave_the_weights_out():
+    # Every call that asks for TRANSPOSE leaves the transposes in WT, with DGRAD beside it or not; a later DGRAD call with
+    # missing or misaligned weights reads them and gives the same bytes (gradient accumulation: BWD_ALL on the first
+    # micro-batch, DGRAD | WGRAD | ACCUMULATE after it).  With DIRECT such a call is refused.  The training step's own
+    # calls never transpose unless asked for it alone, and refuse instead of reading transposes that are not there.
+    sizes, d, f = [40, 0, 300, 1], 256, 512
+    say("ffn backward, weights left out of later calls")
+    r = run_forward_backward(sizes, d, f, torch.float32)
+    R, R_cap, G = r["R"], r["R_cap"], len(sizes)
+    (dXp_o, _), _ = oracle_backward(r)
+    check_rows(f64(r["dXp"])[:R], dXp_o, "dXp")
+    off = torch.from_numpy(r["offsets"]).to(DEV)
+    W = [[w[i].to(DEV) for w in r["W"]] for i in range(3)]
+    other = [[w * 2 for w in ws] for ws in W]
+    Xp, dYp = r["Xp"].to(DEV), r["dYp"].to(DEV)
+    dW = [[torch.empty(sh, dtype=torch.float32, device=DEV) for _ in range(G)] for sh in ((d, f), (d, f), (f, d))]
+    nothing = [[None] * G for _ in range(3)]
+    partly = [list(W[0]), list(W[1]), [W[2][0], None, W[2][2], W[2][3]]]
+    shifted = torch.empty((d * f + 8,), dtype=torch.bfloat16, device=DEV)[1: d * f + 1].view(d, f)   # never read
+    misaligned = [[shifted] + list(W[0][1:]), list(W[1]), list(W[2])]
+    for first in (B.BWD_ALL, B.BWD_TRANSPOSE | B.BWD_DGRAD, B.BWD_TRANSPOSE):
+        for later in (nothing, partly, misaligned):
+            WT = torch.zeros((B.feplb_grouped_ffn_backward_wt_bytes(G, d, f),), dtype=torch.uint8, device=DEV)
+
+            def call(weights, phases):
+                AB, dXp = r["AB_saved"].clone(), torch.full((R_cap, d), 512.0, dtype=torch.float32, device=DEV)
+                B.feplb_grouped_ffn_backward(Xp, off, 0, G, d, f, *weights, r["H"], AB, dYp, dXp, *dW, WT=WT, phases=phases)
+                torch.cuda.synchronize()
+                return AB, dXp
+            call(W, first)
+            AB, dXp = call(later, B.BWD_DGRAD | B.BWD_WGRAD | B.BWD_ACCUMULATE)
+            assert torch.equal(AB[:R], r["dAB"][:R]) and torch.equal(dXp[:R], r["dXp"][:R])
+            with pytest.raises(fe.FeplbError, match="not 16-byte aligned" if later is misaligned else "null weights"):
+                call(later, B.BWD_DGRAD | B.BWD_DIRECT)
+    AB, dXp = call(W, B.BWD_DGRAD | B.BWD_DIRECT)
+    assert torch.equal(AB[:R], r["dAB"][:R]) and torch.equal(dXp[:R], r["dXp"][:R])
+
+    step = FfnTrainingStep(R_cap, G, d, f, device=DEV)
+    step.WT.zero_()
+
+    def backward(weights, phases):
+        step.AB.copy_(r["AB_saved"])
+        step.H.copy_(r["H"])
+        step.dXp.zero_()
+        step.backward(Xp, off, *weights, dYp, phases=phases)
+        torch.cuda.synchronize()
+        return step.dXp[:R]
+    backward(W, B.BWD_TRANSPOSE)
+    assert torch.equal(backward(nothing, B.BWD_DGRAD), r["dXp"][:R])
+    for combined in (B.BWD_ALL, B.BWD_TRANSPOSE | B.BWD_DGRAD):
+        assert torch.equal(backward(W, combined), r["dXp"][:R])
+        assert not torch.equal(backward(other, combined), r["dXp"][:R])
+        assert torch.equal(backward(W, B.BWD_DGRAD), r["dXp"][:R])
+        with pytest.raises(fe.FeplbError, match="null weights"):
+            backward(nothing, B.BWD_DGRAD)       # WT holds the weights of an earlier call
+    backward(W, B.BWD_TRANSPOSE)
+    assert torch.equal(backward(nothing, B.BWD_DGRAD), r["dXp"][:R])
 
 
 @pytest.mark.parametrize("d,f", [(512, 256), (1024, 768)])

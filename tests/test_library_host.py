@@ -77,6 +77,26 @@ def test_argument_validation_happens_before_any_device_work():
     assert fe.feplb_grouped_ffn_workspace_bytes(4096, 20) >= (4096 // 256 + 20) * 16   # one entry per 256-row tile
 
 
+def test_backward_refuses_direct_input_gradients_without_the_weights():
+    # DIRECT is about DGRAD and wants every weight; with them the transposed-weight scratch is not needed
+    L = fe.lib()
+    bw = L.feplb_grouped_ffn_backward
+    one = (C.c_void_p * 1)(4096)
+    odd = (C.c_void_p * 1)(4098)
+    null = (C.c_void_p * 1)(None)
+
+    def call(w, phases):
+        return bw(None, 4096, 0, 1, 64, 256, 256, one, w, one, None, None, None, None, 0, None, None, None,
+                  None, 0, phases, None, 0, None)
+    D = fe.BWD_DIRECT
+    assert call(one, D) == -1 and b"phases" in L.feplb_last_error()
+    assert call(one, D | fe.BWD_WGRAD) == -1 and b"DIRECT without DGRAD" in L.feplb_last_error()
+    assert call(null, D | fe.BWD_DGRAD) == -1 and b"null weights" in L.feplb_last_error()
+    assert call(odd, D | fe.BWD_DGRAD) == -3 and b"not 16-byte aligned" in L.feplb_last_error()
+    assert call(one, fe.BWD_DGRAD) == -4 and b"WT" in L.feplb_last_error()
+    assert call(one, D | fe.BWD_DGRAD) == -1 and b"null AB" in L.feplb_last_error()
+
+
 def as_tuples(moves):
     return [tuple(int(v) for v in m) for m in moves]
 
