@@ -162,7 +162,7 @@ int32_t feplb_permute_append(const int32_t* topk_ids, int32_t T, int32_t k, int3
  *           FEPLB_FFN_ALL does all three.
  *   ws      device, feplb_grouped_ffn_workspace_bytes(R_cap, G) bytes
  * Empty groups read no weights and do no work.
- * Limits: d % 256 == 0, f % 128 == 0, g_end <= FEPLB_MAX_GROUPS.
+ * Limits: d % 256 == 0, f % 128 == 0, g_end <= FEPLB_MAX_GROUPS; 64 rows of d or f elements fit 4 GiB.
  */
 #define FEPLB_FFN_GATE_UP 1
 #define FEPLB_FFN_DOWN 2
@@ -270,6 +270,19 @@ int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* offsets,
                                    void* const* dw_gate, void* const* dw_up, void* const* dw_down,
                                    void* WT, size_t wt_bytes, int32_t phases,
                                    void* ws, size_t ws_bytes, void* stream);
+
+/* Height in rows (64, 128 or 256) of the tiles that a grouped GEMM of these entry points computes in,
+ * picked on the host from the row capacity and the sizes alone; results do not depend on it.  For
+ * tests that want every shape covered and for reading profiles.  R_cap, n_groups (g_end - g_begin),
+ * d, f as in the call (GATE_UP: without row_src; DH, DXP: with the weights given); 0 for arguments
+ * out of range.  Host-only. */
+#define FEPLB_GEMM_GATE_UP 0
+#define FEPLB_GEMM_DOWN 1
+#define FEPLB_GEMM_DH 2
+#define FEPLB_GEMM_DXP 3
+#define FEPLB_GEMM_DW_DOWN 4
+#define FEPLB_GEMM_DW_GATE_UP 5
+int32_t feplb_grouped_ffn_tile_rows(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f);
 
 /* ------------------------------------------------------------------ combine
  * Section 2.3: the last step of a micro-batch hands the experts' outputs back to the

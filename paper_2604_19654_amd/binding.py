@@ -21,6 +21,7 @@ F32, BF16 = 0, 1
 FFN_GATE_UP, FFN_DOWN, FFN_SCHEDULE, FFN_ALL = 1, 2, 4, 7
 BWD_SCHEDULE, BWD_TRANSPOSE, BWD_DGRAD, BWD_WGRAD, BWD_ALL = 1, 2, 4, 8, 15
 BWD_ACCUMULATE, BWD_DIRECT = 16, 32
+GEMM_GATE_UP, GEMM_DOWN, GEMM_DH, GEMM_DXP, GEMM_DW_DOWN, GEMM_DW_GATE_UP = range(6)
 PLAN_WHOLE, PLAN_OVERFLOW = 0, 1
 
 
@@ -73,6 +74,7 @@ def lib():
         L.feplb_grouped_ffn_backward.argtypes = [vp, vp, i32, i32, i32, i32, i32, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp),
                                                  vp, vp, vp, vp, i32, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp),
                                                  vp, sz, i32, vp, sz, vp]
+        L.feplb_grouped_ffn_tile_rows.argtypes = [i32] * 5
         L.feplb_unpermute_combine.argtypes = [vp, i32, i32, vp, vp, i32, i32, i32, vp, vp]
         L.feplb_combine_backward.argtypes = [vp, vp, i32, i32, vp, vp, i32, i32, i32, vp, vp, vp]
         L.feplb_route_topk_backward.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp]
@@ -332,6 +334,11 @@ def feplb_grouped_ffn_backward(Xp, offsets, g_begin, g_end, d, f, w_gate, w_up, 
                                             _ptr(WT), WT.numel(), phases, _ptr(ws), ws.numel(), _stream(stream)),
            "feplb_grouped_ffn_backward")
     return dXp
+
+
+def feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f) -> int:
+    """Host-only: height in rows of the tiles that grouped GEMM `gemm` (GEMM_*) would compute in."""
+    return int(lib().feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f))
 
 
 def feplb_unpermute_combine(Yp, inv, topk_w, T, k, d, Y=None, stream=None):

@@ -35,11 +35,16 @@ struct GroupedGemm {
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s);
 hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s);
 hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s);
+int gemm_tile_rows(const GroupedGemm& a, bool gate_up);   // rows of a tile of the shape that these pick
+
+// The GEMMs address the rows of a tile as 32-bit byte offsets from its first row: can `rows` rows of `ld` bf16 be?
+inline bool rows_fit_32_bits(int64_t rows, int64_t ld) { return rows * ld * 2 <= 0xffffffffll; }
 
 // backward-pass launchers (ffn_backward.hip), used by feplb_grouped_ffn_backward
 hipError_t launch_wgrad(const void* P, int ldp, int M, const void* Q, int ldq, int N, const int* offsets,
                         int g_begin, int n_groups, int R_cap, void* const* c0, void* const* c1,
                         int n_split, int ldc, bool accumulate, hipStream_t s);
+int wgrad_tile_rows(int R_cap, int n_groups, int M, int N);
 hipError_t launch_transpose(const void* const* src, int g_begin, int n_groups, int rows, int cols, void* dst,
                             size_t group_stride, hipStream_t s);
 

@@ -54,6 +54,10 @@ int32_t forward_impl(const void* Xp, const int32_t* row_src, int32_t T, int32_t 
   if (ng == 0 || R_cap == 0) return FEPLB_OK;
   FEPLB_REQUIRE(offsets, FEPLB_EINVAL, "grouped_ffn: null offsets");
   const bool do_up = phases & FEPLB_FFN_GATE_UP, do_down = phases & FEPLB_FFN_DOWN;
+  const int rows = R_cap < 64 ? R_cap : 64;   // of the smallest tile; 64 rows of each weight matrix are a k tile
+  FEPLB_REQUIRE((!do_up || ((row_src || feplb::rows_fit_32_bits(rows, d)) && feplb::rows_fit_32_bits(64, f))) &&
+                    (!do_down || (feplb::rows_fit_32_bits(rows, f) && feplb::rows_fit_32_bits(64, d))),
+                FEPLB_ESHAPE, "grouped_ffn: 64 rows do not fit 32-bit byte offsets (d=%d f=%d)", d, f);
   if (do_up) {
     FEPLB_REQUIRE(Xp && H && w_gate && w_up, FEPLB_EINVAL, "grouped_ffn: null Xp/H/w_gate/w_up");
     if (row_src) {
@@ -173,7 +177,7 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
   const bool must_direct = phases & FEPLB_BWD_DIRECT;
   FEPLB_REQUIRE(!do_w || R_cap >= 32, FEPLB_ESHAPE, "grouped_ffn_backward: WGRAD needs R_cap >= 32 (R_cap=%d)", R_cap);
   FEPLB_REQUIRE(offsets, FEPLB_EINVAL, "grouped_ffn_backward: null offsets");
-  // column offsets inside a row travel as 32-bit byte offsets
+  // offsets inside the smallest tile travel as 32-bit byte offsets
   FEPLB_REQUIRE((uint64_t)(2 * (size_t)f + d) * 64 * 2 <= 0xffffffffull, FEPLB_ESHAPE, "grouped_ffn_backward: d, f too large");
   if (do_t || must_direct) {
     FEPLB_REQUIRE(w_gate && w_up && w_down, FEPLB_EINVAL, "grouped_ffn_backward: null weight tables");
@@ -247,4 +251,20 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
     FEPLB_HIP(feplb::launch_plain_gemm(a, dxp_dtype == FEPLB_BF16, s));
   }
   return FEPLB_OK;
+}
+
+extern "C" int32_t feplb_grouped_ffn_tile_rows(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f) {
+  if (R_cap < 0 || n_groups < 1 || n_groups > FEPLB_MAX_GROUPS || d < 256 || f < 128) return 0;
+  feplb::GroupedGemm a{};
+  a.R_cap = R_cap;
+  a.ng = n_groups;
+  switch (gemm) {
+    case FEPLB_GEMM_GATE_UP: a.K = a.lda = d; a.N = a.ldw = f; return feplb::gemm_tile_rows(a, true);
+    case FEPLB_GEMM_DOWN: a.K = a.lda = f; a.N = a.ldw = d; return feplb::gemm_tile_rows(a, false);
+    case FEPLB_GEMM_DH: a.K = a.lda = a.ldw = d; a.N = f; a.w_nk = true; return feplb::gemm_tile_rows(a, false);
+    case FEPLB_GEMM_DXP: a.K = a.lda = 2 * f; a.N = d; a.ldw = f; a.w_nk = true; return feplb::gemm_tile_rows(a, false);
+    case FEPLB_GEMM_DW_DOWN: return feplb::wgrad_tile_rows(R_cap, n_groups, f, d);
+    case FEPLB_GEMM_DW_GATE_UP: return feplb::wgrad_tile_rows(R_cap, n_groups, d, 2 * f);
+    default: return 0;
+  }
 }

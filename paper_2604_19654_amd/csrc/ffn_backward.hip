@@ -304,6 +304,8 @@ hipError_t launch_wgrad(const void* P, int ldp, int M, const void* Q, int ldq, i
   return accumulate ? run(std::true_type{}) : run(std::false_type{});
 }
 
+int wgrad_tile_rows(int R_cap, int n_groups, int M, int N) { return WGRAD_SHAPES[pick_wgrad_shape(R_cap, n_groups, M, N)].bm; }
+
 // dst + i * group_stride (elements) receives the transpose of src[g_begin + i] ([rows, cols] bf16)
 hipError_t launch_transpose(const void* const* src, int g_begin, int n_groups, int rows, int cols, void* dst,
                             size_t group_stride, hipStream_t s) {

@@ -272,24 +272,27 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
 // (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
 // GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168); picking by it is 2 % slower on average than the
 // best of the three each time, and 1.37x faster than 256 x 256 tiles of four wavefronts for every shape.  B is estimated from
-// the row capacity: a group of rows ends half a tile early on average.
+// the row capacity: a group of rows ends half a tile early on average.  A shape whose rows do not fit the loads' 32-bit
+// offsets (256 rows of more than 8.3 million elements) is not taken; the entry points see to it that 64 rows do.
 struct Shape {
   int bm, bn, per_cu;
   double start, round[2];   // us; us per 1000 k
 };
 constexpr Shape SHAPES[3] = {{256, 256, 1, 3.5, {22.3, 0.}}, {128, 256, 2, 4.2, {14.1, 29.9}}, {64, 128, 2, 3.8, {4.8, 12.9}}};
 
-int pick_shape(int R_cap, int ng, int K, int weight_cols) {
-  int best = 0;
+int pick_shape(const feplb::GroupedGemm& a, int weight_cols) {
+  int best = -1;
   double best_us = 0.;
   for (int i = 0; i < 3; ++i) {
     const Shape& s = SHAPES[i];
-    const double m = (double)R_cap / s.bm + 0.5 * ng;
-    const double tiles = (m > ng ? m : ng) * (weight_cols / s.bn);
+    const bool fits = (a.row_src || feplb::rows_fit_32_bits(s.bm, a.lda)) && (!a.w_nk || feplb::rows_fit_32_bits(s.bn / 2, a.ldw));
+    if (!fits && i < 2) continue;
+    const double m = (double)a.R_cap / s.bm + 0.5 * a.ng;
+    const double tiles = (m > a.ng ? m : a.ng) * (weight_cols / s.bn);
     const double full = (double)(long)(tiles / (256 * s.per_cu)), rest = tiles - full * (256 * s.per_cu);
     const double tail = rest <= 0. ? 0. : s.round[rest > 256 ? 1 : 0];
-    const double us = s.start + K * 1e-3 * (full * s.round[s.per_cu - 1] + tail);
-    if (i == 0 || us < best_us) {
+    const double us = s.start + a.K * 1e-3 * (full * s.round[s.per_cu - 1] + tail);
+    if (best < 0 || us < best_us) {
       best = i;
       best_us = us;
     }
@@ -311,7 +314,7 @@ hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
 hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
-  switch (pick_shape(a.R_cap, a.ng, a.K, MODE == 0 ? 2 * a.N : a.N)) {
+  switch (pick_shape(a, MODE == 0 ? 2 * a.N : a.N)) {
     case 0: return launch<MODE, OUT_BF16, SAVE, B_TR, 4, 2, 2, 3, 3, 2>(a, s);
     case 1: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 2, 2, 2, 3, 2>(a, s);
     default: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 1, 1, 3, 6, 2>(a, s);
@@ -332,5 +335,6 @@ hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s)
 hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s) {
   return a.w_nk ? launch_shape<2, true, false, false>(a, s) : launch_shape<2, true, false, true>(a, s);
 }
+int gemm_tile_rows(const GroupedGemm& a, bool gate_up) { return SHAPES[pick_shape(a, gate_up ? 2 * a.N : a.N)].bm; }
 
 }  // namespace feplb

@@ -97,6 +97,37 @@ def test_backward_refuses_direct_input_gradients_without_the_weights():
     assert call(one, D | fe.BWD_DGRAD) == -1 and b"null AB" in L.feplb_last_error()
 
 
+def test_tiles_whose_rows_do_not_fit_32_bit_offsets_are_not_used():
+    # The GEMMs address a tile's rows by 32-bit byte offsets.  The taller tile shapes are left where their rows would not
+    # fit, and sizes at which 64 rows do not are refused (before any pointer is used: these are not device addresses).
+    tile = fe.binding.feplb_grouped_ffn_tile_rows
+    wide = 1 << 23                       # 256 rows of 2^23 bf16 are 4 GiB
+    R_cap = 1 << 17
+    B = fe.binding
+    assert tile(B.GEMM_DOWN, R_cap, 1, 256, wide // 2) == 256
+    for gemm, d, f in ((B.GEMM_GATE_UP, wide, 128), (B.GEMM_DOWN, 256, wide), (B.GEMM_DH, wide, 256), (B.GEMM_DXP, 256, wide // 2)):
+        assert tile(gemm, R_cap, 1, d, f) == 128
+        assert tile(gemm, R_cap, 1, *(2 * x if x >= wide // 2 else x for x in (d, f))) == 64
+        for rows in range(0, R_cap, 9973):
+            for size in (d - 256, d, 2 * d, 4 * d - 256) if d > f else (f - 256, f, 2 * f, 4 * f - 256):
+                dd, ff = (size, f) if d > f else (d, size)
+                stride = {B.GEMM_GATE_UP: dd, B.GEMM_DOWN: ff, B.GEMM_DH: dd, B.GEMM_DXP: 2 * ff}[gemm]
+                assert tile(gemm, rows, 1, dd, ff) * stride * 2 < 1 << 32
+    L = fe.lib()
+    one = (C.c_void_p * 1)(4096)
+    phase = {"up": fe.FFN_GATE_UP, "down": fe.FFN_DOWN}
+
+    def forward(d, f, phases, R_cap=4096, row_src=None):
+        return L.feplb_grouped_ffn(4096, row_src, 1, 1, 4096, 0, 1, R_cap, d, f, one, one, one, 4096, 4096, 0, phases, None, 0, None)
+    big = 1 << 25
+    for d, f, phases in ((big, 128, "up"), (256, big, "up"), (big, 128, "down"), (256, big, "down")):
+        assert forward(d, f, phase[phases]) == -2 and b"32-bit" in L.feplb_last_error()
+        d, f = (x - 256 if x == big else x for x in (d, f))
+        assert forward(d, f, phase[phases]) == -4          # the next check: no workspace
+    assert forward(big, 128, fe.FFN_GATE_UP, R_cap=63) == -4                       # 63 rows do fit
+    assert forward(big, 128, fe.FFN_GATE_UP, row_src=4096) == -4                   # gathered rows: T * d counts
+
+
 def as_tuples(moves):
     return [tuple(int(v) for v in m) for m in moves]
 
