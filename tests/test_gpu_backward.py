@@ -154,9 +154,9 @@ def test_grouped_ffn_backward_parity(sizes, d, f, dxp_dtype):
 
 @pytest.mark.parametrize("d,f", [(512, 256), (256, 768)])
 def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d, f):
-    # The tile shape is picked from the row capacity: 64-, 128- and 256-row tiles at the three capacities here.  The
-    # input gradients read the weights themselves, or transposes left in WT by an earlier call where none are given.
-    # Every element is the same chain of MFMAs on all six ways, so the bytes must be equal.  Group sizes lie at the
+    # The tile shape is picked from the row capacity: each of the two GEMMs takes 64-, 128- and 256-row tiles at one of the
+    # four capacities here.  The input gradients read the weights themselves, or transposes left in WT by an earlier call where none are given.
+    # Every element is the same chain of MFMAs on all ways, so the bytes must be equal.  Group sizes lie at the
     # edges of the tiles and of their 32-row blocks.
     sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
     say(f"ffn input gradients d={d} f={f}")
@@ -168,7 +168,10 @@ def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d,
     W = [[w[i].to(DEV) for w in r["W"]] for i in range(3)]
     WT = torch.zeros((B.feplb_grouped_ffn_backward_wt_bytes(G, d, f),), dtype=torch.uint8, device=DEV)
     nothing = [[None] * G for _ in range(3)]
-    for R_cap in (R, 8000, 100000):
+    capacities = (R, 8000, 16000, 100000)
+    for gemm in (B.GEMM_DH, B.GEMM_DXP):
+        assert {B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities} == {64, 128, 256}
+    for R_cap in capacities:
         H = torch.zeros((R_cap, f), dtype=torch.bfloat16, device=DEV)
         dYp = torch.full((R_cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
         dYp[:R] = r["dYp"][:R].to(DEV)
@@ -247,8 +250,8 @@ def test_transposes_serve_later_calls_that_leave_the_weights_out():
 
 @pytest.mark.parametrize("d,f", [(512, 256), (1024, 768)])
 def test_weight_gradients_at_the_edges_of_their_shapes(d, f):
-    # The tile shape is picked from the row capacity and the matrices: 64 x 128 and 128 x 256 tiles at the two capacities
-    # for the smaller matrices, 128 x 256 and 256 x 256 for the larger.  Every element is the same chain of MFMAs in all of
+    # The tile shape is picked from the row capacity and the matrices: both GEMMs take 64- and 128-row tiles at the two
+    # capacities for the smaller matrices, 128- and 256-row tiles for the larger.  Every element is the same chain of MFMAs in all of
     # them, so the bytes must be equal.  Group sizes lie at the edges of the 64-row steps and of their four slices; one
     # group's rows are NaN in every operand, and so are the rows past the last group: neither may reach another group.
     # Adding to gradients is one more fp32 addition per element.
@@ -265,6 +268,8 @@ def test_weight_gradients_at_the_edges_of_their_shapes(d, f):
     nothing = [None] * G
     ws = torch.empty((B.feplb_grouped_ffn_workspace_bytes(100000, G),), dtype=torch.uint8, device=DEV)
     first = None
+    for gemm in (B.GEMM_DW_DOWN, B.GEMM_DW_GATE_UP):
+        assert [B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in (R, 100000)] == ([64, 128] if d == 512 else [128, 256])
     for R_cap in (R, 100000):
         bufs = [torch.full((R_cap, t.shape[1]), float("nan"), dtype=torch.bfloat16, device=DEV) for t in data]
         for buf, t in zip(bufs, data):

@@ -276,8 +276,8 @@ def test_grouped_ffn_short_tail_tiles_repeatable(d, f, sizes):
 
 @pytest.mark.parametrize("f", [384, 128])
 def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
-    # The tile shape of the grouped GEMM is picked from the row capacity: 64-, 128- and 256-row tiles at the three
-    # capacities here.  Group sizes lie at the edges of the tiles, of their 32-row blocks and of the loop variants
+    # The tile shape of the grouped GEMM is picked from the row capacity: both GEMMs take 64-, 128- and 256-row tiles at one
+    # of the four capacities here.  Group sizes lie at the edges of the tiles, of their 32-row blocks and of the loop variants
     # that skip empty blocks.  Every element is the same chain of MFMAs in all shapes, so the bytes must be equal.
     sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
     d, G = 512, len(sizes)
@@ -292,7 +292,10 @@ def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
     X[order.long()] = Xp
     H_o, Yp_o = orc.grouped_ffn(f64(Xp), offsets, [tuple(f64(m) for m in w) for w in W])
     first = None
-    for R_cap in (R, 8000, 100000):
+    capacities = (R, 8000, 16000, 100000)
+    for gemm in (fe.binding.GEMM_GATE_UP, fe.binding.GEMM_DOWN):
+        assert {fe.binding.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities} == {64, 128, 256}
+    for R_cap in capacities:
         for yp_dtype in (torch.float32, torch.bfloat16):
             H = torch.full((R_cap, f), 512.0, dtype=torch.bfloat16, device=DEV)
             Yp = torch.full((R_cap, d), 512.0, dtype=yp_dtype, device=DEV)
