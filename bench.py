@@ -28,15 +28,16 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 (no sparsity)
 HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 # HBM bytes per launch (read, written) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs, scaled by what the
 # same counters read for the row-copy and combine kernels of the same run (sizes known); see the named profile.
-# The figures belong to the kernel source they were measured on: bench.py reports them only while
-# csrc/ffn.hip still has that content (sha256), and null otherwise.
+# The figures belong to the kernel source they were measured on: bench.py reports them only while the files that
+# decide what the GEMMs move still have that content (one sha256 over all of them), and null otherwise.
+TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "ffn_hip_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
+           "sources_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
            "gate_up": {"read": 2496533 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
            "down": {"read": 1271943 * 1024 * 2.0, "written": 1573573 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "ffn_hip_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
+           "sources_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
            "gate_up": {"read": 454829 * 1024 * 2.0, "written": 61188 * 1024},
            "down": {"read": 227325 * 1024 * 2.0, "written": 326958 * 1024}},
 }
@@ -242,17 +243,21 @@ def _reference_dense_gemm(R, d, f, device):
     return out
 
 
+def _traffic_sources_sha256(csrc=os.path.join(ROOT, "paper_2604_19654_amd", "csrc")):
+    import hashlib
+    h = hashlib.sha256()
+    for name in TRAFFIC_SOURCES:
+        with open(os.path.join(csrc, name), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
+
+
 def _traffic(name, kernel):
     """Measured HBM bytes per launch of `kernel` on workload `name`, or None when there is no
     measurement for the kernel source as it stands."""
-    import hashlib
     m = MEASURED_TRAFFIC.get(name)
-    if not m or not m.get(kernel):
+    if not m or not m.get(kernel) or _traffic_sources_sha256() != m["sources_sha256"]:
         return None
-    src = os.path.join(ROOT, "paper_2604_19654_amd", "csrc", "ffn.hip")
-    with open(src, "rb") as fh:
-        if hashlib.sha256(fh.read()).hexdigest() != m["ffn_hip_sha256"]:
-            return None
     return m[kernel]["read"] + m[kernel]["written"]
 
 

@@ -2,12 +2,15 @@
 refused with a message (this build is one EP rank's share on one GPU)."""
 import json
 import os
+import re
+import shutil
 import subprocess
 import sys
 
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2604_19654_amd", "csrc")
 
 
 def run_bench(*args, timeout=300):
@@ -19,6 +22,30 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     r = run_bench("--gpus", "2")
     assert r.returncode != 0
     assert "single-GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_measured_traffic_belongs_to_every_source_of_the_gemms(tmp_path):
+    # the measured traffic is reported only for the kernels it was measured on: the guard covers the file that holds the
+    # kernel, the one that launches it, and all of this library's headers that they include
+    import bench
+    holders = [n for n in os.listdir(CSRC) if "panel_gemm_kernel" in open(os.path.join(CSRC, n)).read()
+               or "launch_gate_up(a" in open(os.path.join(CSRC, n)).read()]
+    assert {"ffn.hip", "ffn_gemm.hip"} <= set(holders)
+    sources, todo = set(), holders
+    while todo:
+        name = todo.pop()
+        sources.add(name)
+        included = re.findall(r'#include "([^"]+)"', open(os.path.join(CSRC, name)).read())
+        todo += [n for n in included if n not in sources and os.path.exists(os.path.join(CSRC, n))]
+    assert sources <= set(bench.TRAFFIC_SOURCES)
+    now = bench._traffic_sources_sha256()
+    for name in bench.TRAFFIC_SOURCES:
+        copy = tmp_path / name.replace(".", "_")
+        shutil.copytree(CSRC, copy)
+        assert bench._traffic_sources_sha256(str(copy)) == now
+        with open(copy / name, "a") as fh:
+            fh.write("\n")
+        assert bench._traffic_sources_sha256(str(copy)) != now, name
 
 
 @pytest.mark.gpu
