@@ -33,13 +33,13 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
-           "gate_up": {"read": 2496533 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
-           "down": {"read": 1271943 * 1024 * 2.0, "written": 1573573 * 1024}},
+           "sources_sha256": "aaf735130c409c8c8dc1924baa851526bae0feafa69c97dd04066d7c7ba271bc",
+           "gate_up": {"read": 2666182 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
+           "down": {"read": 1346189 * 1024 * 2.0, "written": 1578718 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "e220b4efd4c5d5adfadee6c4b4c8fb1beb505f7a128794e6795867ee6e9636ce",
-           "gate_up": {"read": 454829 * 1024 * 2.0, "written": 61188 * 1024},
-           "down": {"read": 227325 * 1024 * 2.0, "written": 326958 * 1024}},
+           "sources_sha256": "aaf735130c409c8c8dc1924baa851526bae0feafa69c97dd04066d7c7ba271bc",
+           "gate_up": {"read": 549983 * 1024 * 2.0, "written": 61188 * 1024},
+           "down": {"read": 242963 * 1024 * 2.0, "written": 327153 * 1024}},
 }
 METRIC = "grouped-FFN TFLOP/s & % bf16 MFMA peak per rank share; permute/combine GB/s"
 
@@ -83,9 +83,9 @@ def time_workload(name, steps, warmup, source_kind="device", fused_gather=True, 
         span("start", "combined", "step_events")
         per_step.append(tl["start"].elapsed_ms(tl["combined"]))
         if p.rebalanced:
-            span("static_scheduled", "static_gate_up", "gate_up")
+            span("static_begin", "static_gate_up", "gate_up")
             span("static_gate_up", "static_down", "down")
-            span("dynamic_scheduled", "dynamic_gate_up", "gate_up")
+            span("dynamic_begin", "dynamic_gate_up", "gate_up")
             span("dynamic_gate_up", "dynamic_down", "down")
             span("copy_start", "copy_end", "copy")
             span("static_down", "staged", "wait_for_copy")
@@ -95,7 +95,7 @@ def time_workload(name, steps, warmup, source_kind="device", fused_gather=True, 
             span("routed", "permuted", "permute_static" if early_static else "plan_stage_permute")
         else:
             span("routed", "permuted", "permute")
-            span("static_scheduled", "static_gate_up", "gate_up")
+            span("static_begin", "static_gate_up", "gate_up")
             span("static_gate_up", "static_down", "down")
             span("static_down", "combined", "combine")
     acc.setdefault("copy", 0.0)

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(128 * WR, OCC) void wgrad_gemm_kernel(
 // 383 (128 x 256), 558 (64 x 128); 32 groups of 2500 rows, d = 7168, f = 2048: 5.97, 6.20, 10.1 ms; one group of 8192
 // rows, d = 2048, f = 1024, which leaves CUs idle: 259, 175, 148 us.  (The kernel before, 256 x 256 tiles of four
 // wavefronts with masked 32-row windows: 516 us, 7.04 ms, 356 us; adding to the gradients 1175 us and 9.51 ms against
-// 507 us and 6.57 ms now, that are requested a pass ahead.)
+// 507 us and 6.49 ms now, that are requested a pass ahead.)
 struct WgradShape {
   int bm, bn, per_cu;
   double start, round[2];   // us; us per 1000 rows

@@ -272,7 +272,9 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
 // (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
 // GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168); picking by it is 2 % slower on average than the
 // best of the three each time, and 1.37x faster than 256 x 256 tiles of four wavefronts for every shape.  B is estimated from
-// the row capacity: a group of rows ends half a tile early on average.  A shape whose rows do not fit the loads' 32-bit
+// the row capacity, which was the number of rows in those 60: a group of rows ends half a tile early on average, empty ones
+// included.  Where the capacity is a multiple of the rows the estimate is of another launch (64 experts, 16 groups, 2110 of
+// 6018 rows, d = 2048, f = 1408: gate/up 48 us in 128 x 256 tiles, down 29 us in 256 x 256).  A shape whose rows do not fit the loads' 32-bit
 // offsets (256 rows of more than 8.3 million elements) is not taken; the entry points see to it that 64 rows do.
 struct Shape {
   int bm, bn, per_cu;

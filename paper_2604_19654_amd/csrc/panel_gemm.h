@@ -7,9 +7,11 @@
 // stay in registers over both halves.  LDS holds DA tiles of the first operand and a ring of DB half
 // tiles of the second, filled by LDS-DMA loads in rows of 128 bytes or more, i.e. whole memory lines.
 //
-// What bounds it.  On large shapes the chip is limited by power, not by the pipeline: ring depths, band
-// heights, s_setprio and the order of LDS reads between the MFMAs change nothing (+-0.5 %), and the loop
-// with its loads taken out runs 12 % faster, because the clock rises.  What did move it is data movement:
+// What bounds it.  On large shapes the chip is limited by power and by moving operands, not by the pipeline: the matrix
+// pipes are busy 81 % of the time at a clock that has come down to 1.5 to 1.6 GHz (gate/up, 93580 and 37490 rows,
+// d = 6144, f = 2048), and ring depths, band heights, s_setprio and the order of LDS reads between the MFMAs change
+// nothing (+-0.5 %).  The loop with its loads taken out, which multiplies the same operands again and again, runs 1.3x as
+// fast (93580 x 6144 x 4096: 3500 -> 2690 us).  What did move it is data movement:
 // requesting the loads of a sub-step spread over its four slices instead of in one burst behind the
 // barrier (93580 x 6144 x 4096: 4040 -> 3550 us), and neighbouring runs of tiles on all XCDs at once
 // (tile_of_block below: 3550 -> 3340 us).

@@ -93,7 +93,7 @@ struct GroupTables {
 
 // Made by every workgroup for itself, by all its threads (at least FEPLB_MAX_GROUPS): in a launch of its own the
 // tables cost a launch and a trip through memory, and one thread linked the chains (the whole permutation inside a graph:
-// T = 8192, k = 8, G = 16 18.1 -> 14.8 us; T = 32768, G = 32 30.8 -> 25.9 us).  total[e]: occurrences of expert e; base: first row; offsets: written if given.
+// T = 8192, k = 8, G = 16 18.1 -> 14.8 us; T = 32768, G = 32 30.8 -> 25.7 us).  total[e]: occurrences of expert e; base: first row; offsets: written if given.
 __device__ __forceinline__ void make_group_tables(const GroupTable& tab, int G, int E, const int* total, int base,
                                                   const GroupTables& t, int* offsets, bool append) {
   static_assert(FEPLB_MAX_GROUPS == 128, "one group per thread of two wavefronts");

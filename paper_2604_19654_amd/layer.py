@@ -104,9 +104,9 @@ class RankLayer:
                         stream=stream, append=first > 0)
 
     def _ffn_range(self, X, g0, g1, wg, wu, wd, tag, mark):
-        """One ragged launch per GEMM for groups [g0, g1).  With mark=True the
-        schedule / gate_up / down launches are issued by separate calls so that
-        HIP events can bracket each GEMM kernel on its stream."""
+        """One ragged launch per GEMM for groups [g0, g1).  With mark=True the gate_up and
+        down launches are issued by separate calls so that HIP events can bracket each
+        GEMM kernel on its stream."""
         b = self.buf
         src = (X, b.row_src) if self.fused_gather else (b.Xp, None)
         args = (src[0], b.offsets, g0, g1, self.d, self.f, wg, wu, wd, b.H, b.Yp)
@@ -114,8 +114,7 @@ class RankLayer:
         if not mark:
             B.feplb_grouped_ffn(*args, phases=B.FFN_ALL, **kw)
             return
-        B.feplb_grouped_ffn(*args, phases=B.FFN_SCHEDULE, **kw)
-        self._mark(tag + "_scheduled", True)
+        self._mark(tag + "_begin", True)
         B.feplb_grouped_ffn(*args, phases=B.FFN_GATE_UP, **kw)
         self._mark(tag + "_gate_up", True)
         B.feplb_grouped_ffn(*args, phases=B.FFN_DOWN, **kw)

@@ -1,5 +1,5 @@
-"""The forward FFN call that allocates nothing (feplb_grouped_ffn_static: its tile table lives in
-device memory that is part of the library) against the ordinary call with a caller's workspace.
+"""The forward FFN call that takes no workspace and allocates nothing (feplb_grouped_ffn_static)
+against the ordinary call with a caller's workspace.
 Same kernels, so every output must be bit-identical.  Needs an MI355X: run with -m gpu."""
 import numpy as np
 import pytest
@@ -52,8 +52,8 @@ def run_both(sizes, d, f, seed, yp_dtype, pad=5):
 
 
 def test_static_scratch_call_equals_the_workspace_call_twice_in_a_row():
-    # two calls in a row on the same GPU share the built-in table: the second is smaller, with
-    # another group count and other shapes, and must not see anything of the first
+    # the second of two calls in a row on the same GPU is smaller, with another group count and
+    # other shapes, and must not see anything of the first
     say("static-scratch FFN, first call: 9 groups, 2400 rows")
     r1 = run_both([300, 0, 513, 1, 256, 700, 0, 130, 500], 512, 256, seed=1, yp_dtype=torch.float32)
     say("static-scratch FFN, second call: 3 groups, 270 rows")
