@@ -134,15 +134,13 @@ __global__ __launch_bounds__(128 * WR, OCC) void wgrad_gemm_kernel(
   typename Core::FragB fb;
   fa.init(wm * 32, lane);
   fb.init(wn * 32 * NJ, lane);
-  f32x16 acc[2][MI][NJ];
+  f32x4 acc[2][2 * MI][2 * NJ];
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-      for (int nj = 0; nj < NJ; ++nj)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[hf][mi][nj][v] = 0.f;
+      for (int j = 0; j < 2 * NJ; ++j) acc[hf][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (hi > lo) Core::template run<MI>(lds, 2 * ((hi - lo + 63) / 64), fa, fb, issue_p, issue_q, acc);
 
   // ---- epilogue, as the forward kernel's: each wave passes 32 rows x 32 NJ columns at a time through an LDS region of
@@ -154,8 +152,6 @@ __global__ __launch_bounds__(128 * WR, OCC) void wgrad_gemm_kernel(
   constexpr int LINES = 32 / RPI;
   constexpr int SWZ_DIV = ROW_BYTES >= 256 ? 1 : 256 / ROW_BYTES;
   static_assert(32 * ROW_BYTES <= Core::LDS_BYTES / (2 * WR), "staging region");
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const int l32 = lane % 32, csub = (lane / 32) * 4;
   auto swz = [&](int r) { return (r / SWZ_DIV) & (CH - 1); };
   char* const ep = lds + wave * (Core::LDS_BYTES / (2 * WR));
   const int rd_row = lane / CH, rd_chunk = lane % CH;
@@ -180,12 +176,11 @@ __global__ __launch_bounds__(128 * WR, OCC) void wgrad_gemm_kernel(
   for (int pass = 0; pass < 2 * MI; ++pass) {
     if (ACCUMULATE && pass + 1 < 2 * MI) fetch(pass + 1);
 #pragma unroll
-    for (int nj = 0; nj < NJ; ++nj)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const f32x16& v = acc[pass % 2][pass / 2][nj];
-        const int chunk = (nj * 32 + 8 * c + csub) / 4;
-        *(f32x4*)(ep + l32 * ROW_BYTES + ((chunk ^ swz(l32)) << 4)) = f32x4{v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]};
+      for (int j = 0; j < 2 * NJ; ++j) {
+        const int r = i * 16 + lane % 16, chunk = j * 4 + lane / 16;
+        *(f32x4*)(ep + r * ROW_BYTES + ((chunk ^ swz(r)) << 4)) = acc[pass % 2][2 * (pass / 2) + i][j];
       }
 #pragma unroll
     for (int j = 0; j < LINES; ++j) {

@@ -19,7 +19,7 @@
 // The weights are row-major [K,N] (B_TR: the MFMA operand needs 8 consecutive k of one column, which the transposing LDS
 // read delivers), or row-major [N,K] for the products with W^T of the backward pass, read like the rows of A.  [N,K]
 // weights may be two matrices that share k: w0 holds the first k_split of it, w1 the rest (dXp = [da | db] [Wg | Wu]^T).
-// The result's bits do not depend on the shape: every element is one chain of MFMAs 32x32x16 over ascending k.
+// The result's bits do not depend on the shape: every element is one chain of MFMAs 16x16x32 over ascending k.
 #include "common.h"
 #include "panel_gemm.h"
 
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
 #pragma unroll
   for (int i = 0; i < Core::LB; ++i) {
     const int li = wave * Core::LB + i;
-    b_goff[i] = B_TR ? (uint32_t)Core::template cols_row<NJ>(li, lane) * (uint32_t)ldw_bytes + Core::template cols_chunk<NJ>(i, lane) * 16
+    b_goff[i] = B_TR ? (uint32_t)Core::template cols_row<NJ>(li, lane) * (uint32_t)ldw_bytes + Core::template cols_chunk<NJ>(li, lane) * 16
                      : (uint32_t)Core::rows_row(li, lane) * (uint32_t)ldw_bytes + Core::rows_chunk(li, lane) * 16;
   }
   if (MODE == 0) {
@@ -107,15 +107,13 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   typename Core::FragB fb;
   fa.init(wm * 32, lane);
   fb.init(wn * 32 * NJ, lane);
-  f32x16 acc[2][MI][NJ];
+  f32x4 acc[2][2 * MI][2 * NJ];
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-      for (int nj = 0; nj < NJ; ++nj)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[hf][mi][nj][v] = 0.f;
+      for (int j = 0; j < 2 * NJ; ++j) acc[hf][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int blocks32 = (rows + 32 * WR - 1 - wm * 32) / (32 * WR);   // row blocks of this wave that hold rows
   static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
   if (blocks32 >= MI) {
@@ -127,8 +125,8 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
     return;
   }
 
-  // ---- epilogue.  The MFMAs computed (X W)^T per 32 x 32 block: a lane holds ONE row and, in accumulator registers
-  // 4c .. 4c+3, FOUR consecutive columns 8c + 4 (lane / 32) .. +3.  Stored straight from there a row would leave in 8- or
+  // ---- epilogue.  The MFMAs computed (X W)^T per 16 x 16 block: a lane holds ONE row, lane % 16, and FOUR consecutive
+  // columns, 4 (lane / 16) .. +3.  Stored straight from there a row would leave in 8- or
   // 16-byte pieces, and partial-line writes are slow in the L2.  Each wave passes 32 rows at a time through an LDS
   // region of its own and reads them back with the lanes laid along the rows, so that a store instruction writes
   // contiguous pieces of rows.  No barrier: the region is private and the LDS runs a wave's instructions in order.
@@ -140,15 +138,14 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   constexpr int SWZ_DIV = ROW_BYTES >= 256 ? 1 : 256 / ROW_BYTES;   // chunk q of row r sits at slot q ^ swz(r)
   constexpr int PIECE = 32 * ROW_BYTES;            // one staged block of 32 rows
   static_assert(3 * PIECE <= Core::LDS_BYTES / (2 * WR) || (!SAVE && PIECE <= Core::LDS_BYTES / (2 * WR)), "staging region");
-  const int l32 = lane % 32;
   auto swz = [&](int r) { return (r / SWZ_DIV) & (CH - 1); };
   char* const ep = lds + wave * (Core::LDS_BYTES / (2 * WR));
-  const int csub = (lane / 32) * 4;
   const int rd_row = lane / CH, rd_chunk = lane % CH;
   const int wrow = wm * 32;
-  auto piece = [&](int nj, int c) -> char* {
-    const int boff = (nj * 32 + 8 * c + csub) * ESZ;
-    return ep + l32 * ROW_BYTES + ((((boff >> 4) ^ swz(l32))) << 4) + (boff & 15);
+  // where this lane's values of fragment (i, j) of the 32 rows go
+  auto piece = [&](int i, int j) -> char* {
+    const int r = i * 16 + lane % 16, boff = (j * 16 + lane / 16 * 4) * ESZ;
+    return ep + r * ROW_BYTES + ((((boff >> 4) ^ swz(r))) << 4) + (boff & 15);
   };
   auto store_lines = [&](const char* from, int mi, char* dst_wave, size_t ld_bytes, bool streaming) {
 #pragma unroll
@@ -195,19 +192,19 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
         *(u32x4*)(q + PIECE) = ql[pass % 2][j];
       }
 #pragma unroll
-      for (int nj = 0; nj < NJ; ++nj)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          char* q = piece(nj, c);
+        for (int j = 0; j < 2 * NJ; ++j) {
+          char* q = piece(i, j);
           const uint2 pv = *(const uint2*)q, qv = *(const uint2*)(q + PIECE);
           const float dp[4] = {bf16_lo(pv.x), bf16_hi(pv.x), bf16_lo(pv.y), bf16_hi(pv.y)};
           const float dq[4] = {bf16_lo(qv.x), bf16_hi(qv.x), bf16_lo(qv.y), bf16_hi(qv.y)};
           float da[4], db[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float dh = acc[hf][mi][nj][4 * c + i];
-            da[i] = dh * dp[i];
-            db[i] = dh * dq[i];
+          for (int c = 0; c < 4; ++c) {
+            const float dh = acc[hf][2 * mi + i][j][c];
+            da[c] = dh * dp[c];
+            db[c] = dh * dq[c];
           }
           *(uint2*)q = make_uint2(pack_bf16(da[0], da[1]), pack_bf16(da[2], da[3]));
           *(uint2*)(q + PIECE) = make_uint2(pack_bf16(db[0], db[1]), pack_bf16(db[2], db[3]));
@@ -227,18 +224,18 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
       char* aux_wave = (char*)aux + ((size_t)(row0 + wrow) * ld_aux + col0) * 2;
       if constexpr (MODE == 0 && SAVE) {
 #pragma unroll
-        for (int nj = 0; nj < NJ; ++nj)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            char* dst = piece(nj, c);
+          for (int j = 0; j < 2 * NJ; ++j) {
+            char* dst = piece(i, j);
             float hv[4], pv[4], qv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float a = acc[0][mi][nj][4 * c + i], b = acc[1][mi][nj][4 * c + i];
+            for (int c = 0; c < 4; ++c) {
+              const float a = acc[0][2 * mi + i][j][c], b = acc[1][2 * mi + i][j][c];
               const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-a));
-              qv[i] = a * sg;
-              hv[i] = qv[i] * b;
-              pv[i] = b * sg * (1.0f + a - qv[i]);
+              qv[c] = a * sg;
+              hv[c] = qv[c] * b;
+              pv[c] = b * sg * (1.0f + a - qv[c]);
             }
             *(uint2*)dst = make_uint2(pack_bf16(hv[0], hv[1]), pack_bf16(hv[2], hv[3]));
             *(uint2*)(dst + PIECE) = make_uint2(pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]));
@@ -249,14 +246,14 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
         store_lines(ep + 2 * PIECE, mi, aux_wave + ld_aux, (size_t)ld_aux * 2, false);
       } else {
 #pragma unroll
-        for (int nj = 0; nj < NJ; ++nj)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            char* dst = piece(nj, c);
+          for (int j = 0; j < 2 * NJ; ++j) {
+            char* dst = piece(i, j);
             float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              v[i] = MODE == 0 ? silu(acc[0][mi][nj][4 * c + i]) * acc[1][mi][nj][4 * c + i] : acc[hf][mi][nj][4 * c + i];
+            for (int c = 0; c < 4; ++c)
+              v[c] = MODE == 0 ? silu(acc[0][2 * mi + i][j][c]) * acc[1][2 * mi + i][j][c] : acc[hf][2 * mi + i][j][c];
             if (ESZ == 2)
               *(uint2*)dst = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
             else

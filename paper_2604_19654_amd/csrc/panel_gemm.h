@@ -3,9 +3,13 @@
 // A workgroup of 2 WR wavefronts (WR wave rows x 2 wave columns) computes a tile of BM = 32 WR MI rows
 // x BN = 128 NJ columns.  The contraction runs in tiles of 64.  The second operand of a tile is taken in
 // two halves of HW = 64 NJ columns: sub-step u = 2 t + half multiplies the tile's BM x 64 first operand
-// with a 64 x HW half of the second, 4 MI NJ MFMAs 32x32x16 per wave.  The first operand's fragments
+// with a 64 x HW half of the second, 16 MI NJ MFMAs 16x16x32 per wave.  The first operand's fragments
 // stay in registers over both halves.  LDS holds DA tiles of the first operand and a ring of DB half
 // tiles of the second, filled by LDS-DMA loads in rows of 128 bytes or more, i.e. whole memory lines.
+//
+// MFMAs of 16 x 16 x 32, not 32 x 32 x 16: the same flops per cycle and the same LDS reads, but half of the accumulator
+// words read and written per flop, and on a chip limited by power that is speed.  93580 x 6144 x 4096: 3308 -> 3099 us (1424 ->
+// 1520 TFLOP/s); all grouped GEMMs of the large shapes 1.03x (weight gradients) to 1.08x, small ones unchanged.
 //
 // What bounds it.  On large shapes the chip is limited by power and by moving operands, not by the pipeline: the matrix
 // pipes are busy 81 % of the time at a clock that has come down to 1.5 to 1.6 GHz (gate/up, 93580 and 37490 rows,
@@ -20,11 +24,12 @@
 // reads; 16-byte slot p of row r holds k-chunk p ^ ((r >> 1) & 7), so that 16 consecutive rows hit 16
 // different bank groups.  "Cols" (A_TR, B_TR): the k index runs over the rows as they lie in memory; a
 // line of LDS is one k-row of the panel's columns, read with the transposing ds_read_b64_tr_b16; the
-// 64-byte groups of a k-row are XOR-ed with the row so that the four k-rows of a read cover all banks.
+// 64-byte groups of a k-row are XOR-ed with the row, and the halves of a group with its bit 3, so that the eight
+// k-rows that half a wave reads 32 bytes each of cover all banks.
 //
-// Pipeline.  One barrier per sub-step, between the third and the fourth 16-wide slice of k: there every
-// wave holds the last fragments of half tile u, and half tile u+1 (and, if u was a first half, the first
-// operand of the next tile) has landed.  Behind the barrier half tile u+DB is requested into the stage
+// Pipeline.  A sub-step is four slices: 32 k of half of a wave's columns, of the other half, then the other 32 k of both.
+// One barrier per sub-step, between the third and the fourth slice: there every wave holds the last fragments
+// of half tile u, and half tile u+1 (and, if u was a first half, the first operand of the next tile) has landed.  Behind the barrier half tile u+DB is requested into the stage
 // just freed, and behind the barrier of a first half tile t+DA of the first operand.  The LDS-DMA
 // loads complete in issue order, so the barrier waits with a counted vmcnt for the loads it needs only.
 // Requests past the end of the contraction re-read its last tile into stages nobody reads.
@@ -92,35 +97,36 @@ struct PanelGemm {
     return n;
   }
 
+  // An MFMA takes 16 rows of either operand and 32 k: lane l holds k 8 (l / 16) .. +7 of row (or column) l % 16.
+  // A wave's rows and columns come in blocks of 32, i.e. two fragments: fragment i is half i % 2 of block i / 2.
   template <int STRIDE>   // rows between the wave's blocks
   struct FragRows {
-    uint32_t base[4];
+    uint32_t base[2];
     __device__ __forceinline__ void init(int first_row, int lane) {
-      const int r = first_row + lane % 32, h = lane / 32;
+      const int r = first_row + lane % 16, h = lane / 16;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) base[ks] = r * 128 + (((2 * ks + h) ^ ((r >> 1) & 7)) << 4);
+      for (int ks = 0; ks < 2; ++ks) base[ks] = r * 128 + (((4 * ks + h) ^ ((r >> 1) & 7)) << 4);
     }
-    __device__ __forceinline__ bf16x8 read(const char* stage, int block, int ks) const {
-      return *(const bf16x8*)(stage + base[ks] + block * (STRIDE * 128));
+    __device__ __forceinline__ bf16x8 read(const char* stage, int i, int ks) const {
+      return *(const bf16x8*)(stage + base[ks] + (i / 2 * STRIDE + i % 2 * 16) * 128);
     }
   };
   template <int NB, int BLOCKS, int STRIDE>   // panel of 64 NB columns (a k-row is 128 NB bytes); the wave's blocks and the columns between them
   struct FragCols {
     static constexpr int ROW = 128 * NB;
-    uint32_t base[BLOCKS];
+    uint32_t base[2 * BLOCKS];
     __device__ __forceinline__ void init(int first_col, int lane) {
-      const int r = (lane / 32) * 8 + (lane % 16) / 4;
-      const int x = NB == 1 ? (r >> 1) & 1 : r & 3;
+      const int r = (lane / 16) * 8 + (lane % 16) / 4;
 #pragma unroll
-      for (int b = 0; b < BLOCKS; ++b) {
-        const int col = first_col + b * STRIDE + ((lane / 16) % 2) * 16 + (lane % 4) * 4;
-        base[b] = r * ROW + (((col / 32) ^ x) << 6) + (col % 32) * 2;
+      for (int i = 0; i < 2 * BLOCKS; ++i) {
+        const int col = first_col + i / 2 * STRIDE + i % 2 * 16 + (lane % 4) * 4;
+        base[i] = r * ROW + (cols_slot<NB>(r, col / 8) << 4) + (col % 8) * 2;
       }
     }
     // lane s of a 16-lane group addresses 4 columns of k-row s/4 and gets the 4 k-values of column s
-    __device__ __forceinline__ bf16x8 read(const char* stage, int block, int ks) const {
+    __device__ __forceinline__ bf16x8 read(const char* stage, int i, int ks) const {
       typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-      const char* p = stage + base[block] + ks * 16 * ROW;
+      const char* p = stage + base[i] + ks * 32 * ROW;
       const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
       const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 4 * ROW));
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -135,44 +141,52 @@ struct PanelGemm {
   static __device__ __forceinline__ int rows_chunk(int idx, int lane) { return (lane % 8) ^ ((rows_row(idx, lane) >> 1) & 7); }
   template <int NB>
   static __device__ __forceinline__ int cols_row(int idx, int lane) { return idx * (8 / NB) + lane / (8 * NB); }
+  // 16-byte slot of k-row r that holds piece p of its columns, and (the same map) the piece in slot p: the 64-byte groups
+  // are XOR-ed with the k-row, and the halves of a group with its bit 3
   template <int NB>
-  static __device__ __forceinline__ int cols_chunk(int idx, int lane) {
-    const int r = cols_row<NB>(idx, lane), p = lane % (8 * NB);
+  static __device__ __forceinline__ int cols_slot(int r, int p) {
     const int x = NB == 1 ? (r >> 1) & 1 : r & 3;
-    return (((p >> 2) ^ x) << 2) | (p & 3);
+    return p ^ (x << 2) ^ (((r >> 3) & 1) << 1);
   }
+  template <int NB>
+  static __device__ __forceinline__ int cols_chunk(int idx, int lane) { return cols_slot<NB>(cols_row<NB>(idx, lane), lane % (8 * NB)); }
 
   // issue_a(stage, t, i), issue_b(stage, u, i): load i of this wave's share of tile t / half tile u to LDS
   // byte address `stage`; each operand's loads are asked for in order.  ME: this wave's row blocks that hold
   // rows (0 .. MI); the other accumulators are left alone.  U = 2 x the number of k tiles.
   template <int ME, class IA, class IB>
   static __device__ __forceinline__ void run(char* lds, int U, const FragA& fa, const FragB& fb, IA&& issue_a, IB&& issue_b,
-                                             f32x16 (&acc)[2][MI][NJ]) {
+                                             f32x4 (&acc)[2][2 * MI][2 * NJ]) {
     char* const lds_b = lds + DA * A_BYTES;
     const uint32_t a_off = lds_offset(lds), b_off = lds_offset(lds_b);
-    bf16x8 af[4][ME > 0 ? ME : 1];
+    bf16x8 af[2][ME > 0 ? 2 * ME : 1];
     bf16x8 bf[2][NJ];
-    constexpr int B_READS = (B_TR ? 2 : 1) * NJ;
-    auto read_a = [&](int stage, int ks) {
+    constexpr int B_READS = (B_TR ? 2 : 1) * NJ, A_READS = (A_TR ? 2 : 1) * ME;
+    // quarter q of the first operand's tile: half of the fragments of 32 k
+    auto read_a = [&](int stage, int q) {
       if constexpr (ME > 0) {
 #pragma unroll
-        for (int mi = 0; mi < ME; ++mi) af[ks][mi] = fa.read(lds + stage * A_BYTES, mi, ks);
+        for (int i = 0; i < ME; ++i) af[q / 2][q % 2 * ME + i] = fa.read(lds + stage * A_BYTES, q % 2 * ME + i, q / 2);
       }
     };
-    auto read_b = [&](int stage, int ks) {
+    // slice s of a half tile: 32 k (s / 2) of half of the wave's columns (s % 2)
+    auto read_b = [&](int stage, int s) {
       if constexpr (ME > 0) {
 #pragma unroll
-        for (int nj = 0; nj < NJ; ++nj) bf[ks & 1][nj] = fb.read(lds_b + stage * B_BYTES, nj, ks);
+        for (int j = 0; j < NJ; ++j) bf[s & 1][j] = fb.read(lds_b + stage * B_BYTES, s % 2 * NJ + j, s / 2);
       }
     };
-    auto mfma = [&](int half, int ks) {
+    auto mfma = [&](int half, int s) {
       if constexpr (ME > 0) {
 #pragma unroll
-        for (int mi = 0; mi < ME; ++mi)
+        for (int i = 0; i < 2 * ME; ++i)
 #pragma unroll
-          for (int nj = 0; nj < NJ; ++nj)
-            // second operand first: the product comes out transposed, a lane holds one row and runs of four columns
-            acc[half][mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ks & 1][nj], af[ks][mi], acc[half][mi][nj], 0, 0, 0);
+          for (int jj = 0; jj < NJ; ++jj) {
+            const int j = i % 2 ? NJ - 1 - jj : jj;   // there and back: neighbouring MFMAs share an operand (0.4 % on large shapes)
+            // second operand first: the product comes out transposed, a lane holds one row and four consecutive columns
+            f32x4& c = acc[half][i][s % 2 * NJ + j];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[s & 1][j], af[s / 2][i], c, 0, 0, 0);
+          }
       }
     };
     // load x of interval u; j = u modulo PERIOD
@@ -199,22 +213,24 @@ struct PanelGemm {
     });
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(in_flight_start(), 15));
     __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) read_a(0, ks);
+    read_a(0, 0);
+    read_a(0, 1);
     read_b(0, 0);
 
+    // the first operand's quarters are read a slice each: 0 and 1 of the next tile in the last two slices of a second
+    // half, when the present tile's are done with, 2 and 3 in the first two of the first half that follows
     auto step = [&](auto sc, int u) {
       constexpr int s = decltype(sc)::value;         // u mod PERIOD
-      constexpr int half = s & 1, sb = s % DB, sb_next = (s + 1) % DB, sa_next = (s / 2 + 1) % DA;
+      constexpr int half = s & 1, sb = s % DB, sb_next = (s + 1) % DB, sa = s / 2 % DA, sa_next = (s / 2 + 1) % DA;
       constexpr std::integral_constant<int, s - 1> before{};
       auto slice = [&](auto kc) {
-        constexpr int ks = decltype(kc)::value;
-        slot(before, u - 1, std::integral_constant<int, ks + 1>{});
-        read_b(sb, ks + 1);
-        if (half == 1 && ks > 0) read_a(sa_next, ks - 1);
-        mfma(half, ks);
-        constexpr int reads = B_READS + (half == 1 && ks > 0 ? (A_TR ? 2 : 1) * ME : 0);
-        interleave<reads, ME * NJ>();
+        constexpr int q = decltype(kc)::value;
+        slot(before, u - 1, std::integral_constant<int, q + 1>{});
+        read_b(sb, q + 1);
+        if (half == 0 && q < 2) read_a(sa, q + 2);
+        if (half == 1 && q == 2) read_a(sa_next, 0);
+        mfma(half, q);
+        interleave<B_READS + (((half == 0 && q < 2) || (half == 1 && q == 2)) ? A_READS : 0), 2 * ME * NJ>();
         __builtin_amdgcn_sched_barrier(0);
       };
       slice(std::integral_constant<int, 0>{});
@@ -224,12 +240,10 @@ struct PanelGemm {
       __syncthreads();
       slot(sc, u, std::integral_constant<int, 0>{});
       read_b(sb_next, 0);
-      if (half == 1) read_a(sa_next, 2);
+      if (half == 1) read_a(sa_next, 1);
       mfma(half, 3);
-      constexpr int reads = B_READS + (half == 1 ? (A_TR ? 2 : 1) * ME : 0);
-      interleave<reads, ME * NJ>();
+      interleave<B_READS + (half == 1 ? A_READS : 0), 2 * ME * NJ>();
       __builtin_amdgcn_sched_barrier(0);
-      if (half == 1) read_a(sa_next, 3);
     };
     int u = 0;
     for (; u + PERIOD <= U; u += PERIOD) range<0, PERIOD>([&](auto sc) { step(sc, u + decltype(sc)::value); });
