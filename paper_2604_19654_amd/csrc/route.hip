@@ -16,6 +16,7 @@
 // among equal logits the lower expert id stays ahead: the same total order, on plain
 // float compares (-0.0 equals +0.0), with a third of the instructions per token and no
 // cross-lane traffic.
+#include <algorithm>
 #include "common.h"
 
 namespace {
@@ -57,18 +58,20 @@ __device__ __forceinline__ unsigned long long group_max(unsigned long long v) {
   return v;
 }
 
+// block 0 clears the counts for count_kernel, which runs next
+__device__ __forceinline__ void clear_counts(int* __restrict__ counts, int E) {
+  if (counts && blockIdx.x == 0)
+    for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = 0;
+}
+
 // Expert e of a token sits in lane (e % SG) of the token's sub-group, register e / SG.
 template <int SG, int VPL>
 __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict__ logits, int T,
                                                          int E, int k, int* __restrict__ ids,
                                                          float* __restrict__ w,
                                                          int* __restrict__ counts) {
-  extern __shared__ int hist[];
   const int tid = threadIdx.x;
-  if (counts) {
-    for (int e = tid; e < E; e += 256) hist[e] = 0;
-    __syncthreads();
-  }
+  clear_counts(counts, E);
   constexpr int TOK_PER_BLOCK = 256 / SG;
   const int sub = tid / SG;   // token slot inside the block
   const int li = tid % SG;    // lane inside the sub-group
@@ -112,13 +115,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
     if (live && li < k) {
       ids[t * k + li] = mine_id;
       w[t * k + li] = mine_x / sum;
-      if (counts) atomicAdd(&hist[mine_id], 1);
     }
-  }
-  if (counts) {
-    __syncthreads();
-    for (int e = tid; e < E; e += 256)
-      if (hist[e]) atomicAdd(&counts[e], hist[e]);
   }
 }
 
@@ -156,13 +153,9 @@ template <int K>
 __global__ __launch_bounds__(LANE_WAVES * 64) void route_topk_lane_kernel(
     const float* __restrict__ logits, int T, int E, int* __restrict__ ids, float* __restrict__ w,
     int* __restrict__ counts) {
-  extern __shared__ int hist[];
   __shared__ __attribute__((aligned(16))) float stage[LANE_WAVES][64 * 32];
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-  if (counts) {
-    for (int e = tid; e < E; e += LANE_WAVES * 64) hist[e] = 0;
-    __syncthreads();
-  }
+  clear_counts(counts, E);
   const long long t_wave = ((long long)blockIdx.x * LANE_WAVES + wave) * 64;
   const long long t = t_wave + lane;
   float v[K];
@@ -219,13 +212,7 @@ __global__ __launch_bounds__(LANE_WAVES * 64) void route_topk_lane_kernel(
     for (int j = 0; j < K; ++j) {
       ids[t * K + j] = id[j];
       w[t * K + j] = p[j] / sum;
-      if (counts) atomicAdd(&hist[id[j]], 1);
     }
-  }
-  if (counts) {
-    __syncthreads();
-    for (int e = tid; e < E; e += LANE_WAVES * 64)
-      if (hist[e]) atomicAdd(&counts[e], hist[e]);
   }
 }
 
@@ -233,12 +220,32 @@ template <int K>
 void launch_lane(const float* logits, int T, int E, int* ids, float* w, int* counts, hipStream_t s) {
   const int per = LANE_WAVES * 64;
   hipLaunchKernelGGL((route_topk_lane_kernel<K>), dim3((unsigned)((T + per - 1) / per)), dim3(per),
-                     counts ? (size_t)E * sizeof(int) : 0, s, logits, T, E, ids, w, counts);
+                     0, s, logits, T, E, ids, w, counts);
 }
 
-__global__ void zero_i32_kernel(int* p, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// counts[e] = occurrences of e among the A ids; more than one workgroup add to counts that the router has cleared.
+// Counting inside the router needs no second look at the ids, but its workgroups are many, and each adds a histogram
+// to the same few lines, which the XCDs' caches do not share: with 512 of them the router took 17.5 us (the launch that
+// cleared the counts included) where it takes 6.5 without counting (T = 8192, E = 128, k = 8).  Here a workgroup counts at
+// least COUNT_PER_BLOCK ids and there are at most COUNT_BLOCKS.  Router and counts inside a graph: T = 8192, E = 128, k = 8
+// 17.5 -> 9.1 us; T = 16000, E = 256 45.7 -> 17.1; T = 65536, E = 16, k = 1 27.3 -> 5.7; T = 131072, E = 128 39.7 -> 30.8;
+// T = 96 7.2 -> 6.8.  (4096 or 8192 ids per workgroup: 9.4 and 10.7 us at T = 8192.)
+constexpr int COUNT_THREADS = 1024, COUNT_PER_BLOCK = 2048, COUNT_BLOCKS = 64;
+__global__ __launch_bounds__(COUNT_THREADS) void count_kernel(const int* __restrict__ ids, long long A, int E, int* __restrict__ counts) {
+  // the lanes of a wavefront hold neighbouring choices, and a popular expert is in many of them: four copies
+  __shared__ int hist[4][FEPLB_MAX_EXPERTS];
+  const int tid = threadIdx.x;
+  for (int e = tid; e < E; e += COUNT_THREADS) hist[0][e] = hist[1][e] = hist[2][e] = hist[3][e] = 0;
+  __syncthreads();
+  const long long stride = (long long)gridDim.x * COUNT_THREADS;
+#pragma unroll 4
+  for (long long a = (long long)blockIdx.x * COUNT_THREADS + tid; a < A; a += stride) atomicAdd(&hist[tid % 4][ids[a]], 1);
+  __syncthreads();
+  for (int e = tid; e < E; e += COUNT_THREADS) {
+    const int n = hist[0][e] + hist[1][e] + hist[2][e] + hist[3][e];
+    if (gridDim.x == 1) counts[e] = n;
+    else if (n) atomicAdd(&counts[e], n);
+  }
 }
 
 template <int SG, int VPL>
@@ -247,8 +254,7 @@ void launch(const float* logits, int T, int E, int k, int* ids, float* w, int* c
   const int per = 256 / SG;
   long long blocks = ((long long)T + per - 1) / per;
   if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL((route_topk_kernel<SG, VPL>), dim3((unsigned)blocks), dim3(256),
-                     counts ? (size_t)E * sizeof(int) : 0, s, logits, T, E, k, ids, w, counts);
+  hipLaunchKernelGGL((route_topk_kernel<SG, VPL>), dim3((unsigned)blocks), dim3(256), 0, s, logits, T, E, k, ids, w, counts);
 }
 
 template <int SG>
@@ -279,11 +285,17 @@ extern "C" int32_t feplb_route_topk(const float* logits, int32_t T, int32_t E, i
                 E, FEPLB_MAX_TOPK);
   FEPLB_REQUIRE((long long)T * E < (1ll << 40), FEPLB_ESHAPE, "route_topk: T*E too large");
   hipStream_t s = (hipStream_t)stream;
-  if (counts) {
-    hipLaunchKernelGGL(zero_i32_kernel, dim3((E + 255) / 256), dim3(256), 0, s, counts, E);
-    FEPLB_LAUNCH_CHECK("zero_i32_kernel");
+  auto count = [&]() {
+    if (!counts) return;
+    const long long A = (long long)T * k;
+    const long long blocks = std::min<long long>(std::max<long long>((A + COUNT_PER_BLOCK - 1) / COUNT_PER_BLOCK, 1), COUNT_BLOCKS);
+    hipLaunchKernelGGL(count_kernel, dim3((unsigned)blocks), dim3(COUNT_THREADS), 0, s, topk_ids, A, E, counts);
+  };
+  if (T == 0) {   // no choices to count: zeros
+    count();
+    FEPLB_LAUNCH_CHECK("count_kernel");
+    return FEPLB_OK;
   }
-  if (T == 0) return FEPLB_OK;
   FEPLB_REQUIRE(logits && topk_ids && topk_w, FEPLB_EINVAL, "route_topk: null buffer");
   // enough tokens to occupy a good part of the chip with one token per lane (a wavefront = 64 tokens)
   if (T >= 16384 && E % 32 == 0 && ((uintptr_t)logits & 15) == 0 && (k == 2 || k == 4 || k == 8)) {
@@ -291,6 +303,8 @@ extern "C" int32_t feplb_route_topk(const float* logits, int32_t T, int32_t E, i
     else if (k == 4) launch_lane<4>(logits, T, E, topk_ids, topk_w, counts, s);
     else launch_lane<8>(logits, T, E, topk_ids, topk_w, counts, s);
     FEPLB_LAUNCH_CHECK("route_topk_lane_kernel");
+    count();
+    FEPLB_LAUNCH_CHECK("count_kernel");
     return FEPLB_OK;
   }
   // sub-group width: at least k lanes (lane j keeps result j), and wide enough
@@ -308,5 +322,7 @@ extern "C" int32_t feplb_route_topk(const float* logits, int32_t T, int32_t E, i
     default: pick_vpl<64>(vpl, logits, T, E, k, topk_ids, topk_w, counts, s); break;
   }
   FEPLB_LAUNCH_CHECK("route_topk_kernel");
+  count();
+  FEPLB_LAUNCH_CHECK("count_kernel");
   return FEPLB_OK;
 }
