@@ -4,27 +4,25 @@
 //
 // The row order is fully determined (groups in table order, ascending flat
 // assignment inside a group), so no atomics may decide a row position.  It is a
-// stable counting sort over the flat assignments a = t*k + j, split in chunks
-// of 256 or 1024 assignments (by batch size), one wavefront per chunk:
-//   1. chunk_hist : per-chunk, per-expert counts (LDS histogram per wave)
-//   2. chunk_scan : per expert, exclusive prefix over chunks -> the ordinal of
-//                   the first occurrence in each chunk, and the expert's total
-//   3. assign_rows: sizes of the ordinal windows -> offsets[G+1], and per-expert
-//                   chains of groups; then per chunk, walk 64 assignments at a
-//                   time; the ordinal inside the slice comes from a ballot-based
-//                   match of equal experts, the running ordinal per expert lives
-//                   in LDS; the window that contains the ordinal gives the row
-// (small batches: all three in one workgroup, permute_one_kernel)
-//   4. gather_rows: Xp[r,:] = X[row_src[r] / k, :], one wavefront per row,
-//                   16-byte lanes (pure HBM traffic: 2*R*d*2 bytes)
+// stable counting sort over the flat assignments a = t*k + j.  A workgroup owns a
+// run of them, a wavefront of it a shorter run:
+//   - per expert, the occurrences ahead of the run and in all of the batch, from
+//     one of three sources (below); inside the run LDS histograms per wavefront
+//   - sizes of the ordinal windows -> offsets[G+1], and per-expert chains of groups
+//   - each wavefront walks its run 64 assignments at a time; the ordinal inside the
+//     slice comes from a ballot-based match of equal experts, the running ordinal
+//     per expert lives in LDS; the window that contains the ordinal gives the row
+// Where the occurrences outside the run come from:
+//   COUNTED  every workgroup counts the whole batch for itself: one launch
+//   TABLE    chunk_hist has written every run's histogram, every workgroup adds them up
+//   SCANNED  chunk_scan has turned the histograms into prefix sums (very large batches)
+// gather_rows: Xp[r,:] = X[row_src[r] / k, :], one wavefront per row, 16-byte lanes
+// (pure HBM traffic: 2*R*d*2 bytes)
 #include "common.h"
 
 namespace {
 
-// assignments per wavefront: small batches get shorter chunks, i.e. more wavefronts for the
-// serial walk of assign_rows (a multiple of 64 either way)
-int chunk_for(long long A) { return A <= (1ll << 18) ? 256 : 1024; }
-constexpr int WAVES = 4;             // wavefronts per block
+constexpr int WAVES = 4;             // wavefronts per block of chunk_scan
 constexpr int BLOCK = WAVES * 64;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -33,28 +31,30 @@ struct GroupTable {
   feplb_group g[FEPLB_MAX_GROUPS];
 };
 
-__global__ __launch_bounds__(BLOCK) void chunk_hist_kernel(const int* __restrict__ ids,
-                                                           long long A, int E, int nchunks, int chunk,
-                                                           int* __restrict__ chunk_hist) {
+// LDS histograms that a whole workgroup adds to come in copies, one for each residue of the lane: the lanes of a wavefront
+// hold neighbouring assignments, and a popular expert is in many of them.
+constexpr int RUN_MAX_E = 512;   // 16 histograms, the copies and the tables in 64 KB of LDS; above it half as many wavefronts, no copies
+constexpr int copies_for(int E) { return E <= RUN_MAX_E ? 4 : 1; }
+
+constexpr int HIST_THREADS = 1024;
+__global__ __launch_bounds__(HIST_THREADS) void chunk_hist_kernel(const int* __restrict__ ids, long long A, int E, int chunk,
+                                                                  int* __restrict__ chunk_hist) {
   extern __shared__ int lds[];
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  int* h = lds + wave * E;
-  const int c = blockIdx.x * WAVES + wave;
-  for (int e = lane; e < E; e += 64) h[e] = 0;
-  __builtin_amdgcn_wave_barrier();
-  if (c < nchunks) {
-    const long long a0 = (long long)c * chunk;
-    for (int i = lane; i < chunk; i += 64) {
-      const long long a = a0 + i;
-      if (a < A) {
-        const int e = ids[a];
-        if ((unsigned)e < (unsigned)E) atomicAdd(&h[e], 1);
-      }
-    }
+  const int copies = copies_for(E), mine = threadIdx.x % copies * E;
+  for (int i = threadIdx.x; i < copies * E; i += HIST_THREADS) lds[i] = 0;
+  __syncthreads();
+  const long long a0 = (long long)blockIdx.x * chunk;
+  const int n = (int)min((long long)chunk, A - a0);
+  for (int i = threadIdx.x; i < n; i += HIST_THREADS) {
+    const int e = ids[a0 + i];
+    if ((unsigned)e < (unsigned)E) atomicAdd(&lds[mine + e], 1);
   }
   __syncthreads();
-  if (c < nchunks)
-    for (int e = lane; e < E; e += 64) chunk_hist[(long long)c * E + e] = h[e];
+  for (int e = threadIdx.x; e < E; e += HIST_THREADS) {
+    int v = 0;
+    for (int c = 0; c < copies; ++c) v += lds[c * E + e];
+    chunk_hist[(long long)blockIdx.x * E + e] = v;
+  }
 }
 
 // One wavefront per expert; lane l owns a contiguous run of chunks.
@@ -161,95 +161,111 @@ __device__ __forceinline__ int next_row(int e, int nbits, int G, volatile int* r
 
 __device__ __forceinline__ int bits_for(int E) { return E > 1 ? 32 - __builtin_clz(E - 1) : 0; }
 
-__global__ __launch_bounds__(BLOCK) void assign_rows_kernel(
-    GroupTable tab, const int* __restrict__ ids, long long A, int E, int G, int nchunks, int chunk,
-    const int* __restrict__ chunk_base, const int* __restrict__ total, int R_cap, int* offsets,
-    int* __restrict__ row_src, int* __restrict__ inv, int append) {
-  extern __shared__ int lds[];
-  // LDS: run[WAVES][E] | group tables
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int c = blockIdx.x * WAVES + wave;
-  volatile int* run = lds + wave * E;
-  if (c < nchunks)
-    for (int e = lane; e < E; e += 64) run[e] = chunk_base[(long long)c * E + e];
-  const GroupTables t(lds + WAVES * E, E, G);
-  // appending: the rows of these groups follow those of an earlier call, whose end is offsets[0]
-  make_group_tables(tab, G, E, total, append ? offsets[0] : 0, t, blockIdx.x == 0 ? offsets : nullptr, append);
-  if (c >= nchunks) return;
-  const int nbits = bits_for(E);
-  const long long a0 = (long long)c * chunk;
-  for (int i = 0; i < chunk; i += 64) {
-    const long long a = a0 + i + lane;
-    if (a0 + i >= A) break;  // uniform across the wave
-    int e = -1;
-    if (a < A) {
-      e = ids[a];
-      if ((unsigned)e >= (unsigned)E) e = -1;
-    }
-    const int row = next_row(e, nbits, G, run, t);
-    if (a < A) {
-      if (!append || row >= 0) inv[a] = row;   // appending leaves the other calls' entries alone
-      if (row >= 0 && row < R_cap) row_src[row] = (int)a;
-    }
-  }
+enum Source { COUNTED, TABLE, SCANNED };
+
+// Measured inside a graph, E = 128 unless said otherwise, 16 local experts (the three launches of before: 11.6 us at 6018 and 10004
+// assignments, 14.7 at 65536, 25.4 at 262144, 36.8 at 1048576):
+//   counting the batch in every workgroup (6018, E = 64: 6.5 us; 10004, E = 64: 7.1; 49728: 14.6) against a table of histograms by
+//   a launch of its own (7.9, 8.1 and 9.8 us): the line lies between 10004 and 49728;
+//   runs of 1024 against 4096 assignments: 12.0 against 15.2 us at 262144, where there are 256 or 64 workgroups to walk them; at
+//   1048576 the table of 1024 runs would be 1024 rows for each of 1024 workgroups, and runs of 4096 take 21.1 us;
+//   every workgroup adds up a table of at most 512 rows; beyond (2 million assignments) the rows are read by too many.
+constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, TABLE_MAX = 512;
+
+// LDS: run[RUN_WAVES][E] | before[copies][E] | after[copies][E] | total[E] | group tables
+size_t permute_lds_bytes(int waves, int E, int G) {
+  return ((size_t)(waves + 2 * copies_for(E) + 1) * E + GroupTables::ints(E, G)) * sizeof(int);
 }
 
-// All of it in one workgroup, for batches of at most ONE_WAVES * 64 * SLICES assignments: wavefront w owns a run of
-// 64 SLICES assignments, kept in registers between the counting and the walk, so the batch is read once and the
-// histograms and bases never leave LDS.  Bound by latency: the walk takes about 0.9 us
-// per slice.  Inside a graph, against the launches one after the other: T = 96, k = 8, E = 128 14.3 -> 4.8 us;
-// T = 512, k = 2, E = 8 12.2 -> 4.3 us; T = 512, k = 8, E = 128 15.1 -> 7.9 us.
-constexpr int ONE_WAVES = 16;
-constexpr int ONE_MAX_E = 512;       // 16 histograms, the totals and the tables in 64 KB of LDS
-constexpr int ONE_MAX_A = ONE_WAVES * 64 * 4;
-template <int SLICES>
-__global__ __launch_bounds__(ONE_WAVES * 64) void permute_one_kernel(GroupTable tab, const int* __restrict__ ids, int A,
-                                                                     int E, int G, int R_cap, int* offsets,
-                                                                     int* __restrict__ row_src, int* __restrict__ inv,
-                                                                     int append) {
+// A workgroup owns RUN_WAVES * 64 * SLICES assignments; they stay in registers between the counting and the walk, which takes
+// about 0.9 us per slice.
+template <int RUN_WAVES, int SLICES>
+__global__ __launch_bounds__(RUN_WAVES * 64) void permute_kernel(GroupTable tab, const int* __restrict__ ids, long long A, int E, int G,
+                                                                 int nchunks, int source, const int* __restrict__ chunk_hist,
+                                                                 const int* __restrict__ totals, int R_cap, int* offsets,
+                                                                 int* __restrict__ row_src, int* __restrict__ inv, int append) {
   extern __shared__ int lds[];
-  // LDS: run[ONE_WAVES][E] | total[E] | group tables
+  constexpr int THREADS = RUN_WAVES * 64;
+  constexpr int COPIES = copies_for(RUN_WAVES == 16 ? RUN_MAX_E : RUN_MAX_E + 1);
+  const bool alone = gridDim.x == 1;   // nothing outside the only run
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  int* const total = lds + ONE_WAVES * E;
+  int* const before = lds + RUN_WAVES * E;
+  int* const after = before + COPIES * E;
+  int* const total = after + COPIES * E;
   const GroupTables t(total + E, E, G);
-  const int a0 = wave * (64 * SLICES) + lane;
+  const int c = blockIdx.x;
+  const long long run0 = (long long)c * (THREADS * SLICES);
+  const long long a0 = run0 + wave * (64 * SLICES);
   int e[SLICES];
 #pragma unroll
   for (int i = 0; i < SLICES; ++i) {
-    const int a = a0 + i * 64;
+    const long long a = a0 + i * 64 + lane;
     e[i] = a < A ? ids[a] : -1;
     if ((unsigned)e[i] >= (unsigned)E) e[i] = -1;
   }
   const int base = append ? offsets[0] : 0;   // offsets[0] is not written when appending
-  for (int i = threadIdx.x; i < ONE_WAVES * E; i += ONE_WAVES * 64) lds[i] = 0;
+  for (int i = threadIdx.x; i < (RUN_WAVES + (alone ? 0 : 2 * COPIES)) * E; i += THREADS) lds[i] = 0;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < SLICES; ++i)
     if (e[i] >= 0) atomicAdd(&lds[wave * E + e[i]], 1);
+  if (alone) {
+  } else if (source == COUNTED) {
+    const int n = (int)A, mine = lane % COPIES * E;
+    for (int i = threadIdx.x; i < n; i += THREADS) {
+      if (i >= run0 && i < run0 + THREADS * SLICES) continue;   // (whole slices of the loop: the run is a multiple of THREADS)
+      const int x = ids[i];
+      if ((unsigned)x < (unsigned)E) atomicAdd((i < run0 ? before : after) + mine + x, 1);
+    }
+  } else if (source == TABLE) {
+    const int rows = max(1, THREADS / E);   // rows of the table in work at a time
+    for (int x = threadIdx.x; x < rows * E; x += THREADS) {
+      const int ex = x % E;
+      int nb = 0, na = 0;
+#pragma unroll 8
+      for (int r = x / E; r < nchunks; r += rows) {
+        const int v = chunk_hist[(long long)r * E + ex];
+        nb += r < c ? v : 0;
+        na += r > c ? v : 0;
+      }
+      atomicAdd(&before[ex], nb);
+      atomicAdd(&after[ex], na);
+    }
+  } else {
+    for (int x = threadIdx.x; x < E; x += THREADS) before[x] = chunk_hist[(long long)c * E + x];
+  }
   __syncthreads();
-  for (int x = threadIdx.x; x < E; x += ONE_WAVES * 64) {
-    int n[ONE_WAVES];
+  for (int x = threadIdx.x; x < E; x += THREADS) {
+    int sum = 0, rest = 0;
+    if (!alone) {
 #pragma unroll
-    for (int w = 0; w < ONE_WAVES; ++w) n[w] = lds[w * E + x];
-    int sum = 0;
+      for (int i = 0; i < COPIES; ++i) {
+        sum += before[i * E + x];
+        rest += after[i * E + x];
+      }
+    }
+    int n[RUN_WAVES];
 #pragma unroll
-    for (int w = 0; w < ONE_WAVES; ++w) {
+    for (int w = 0; w < RUN_WAVES; ++w) n[w] = lds[w * E + x];
+#pragma unroll
+    for (int w = 0; w < RUN_WAVES; ++w) {
       lds[w * E + x] = sum;
       sum += n[w];
     }
-    total[x] = sum;
+    total[x] = source == SCANNED ? totals[x] : sum + rest;
   }
   __syncthreads();
-  make_group_tables(tab, G, E, total, base, t, offsets, append);
+  // appending: the rows of these groups follow those of an earlier call, whose end is offsets[0]
+  make_group_tables(tab, G, E, total, base, t, c == 0 ? offsets : nullptr, append);
   const int nbits = bits_for(E);
 #pragma unroll
   for (int i = 0; i < SLICES; ++i) {
-    const int a = a0 + i * 64;
+    const long long a = a0 + i * 64 + lane;
     if (a - lane >= A) break;   // uniform across the wave
     const int row = next_row(e[i], nbits, G, lds + wave * E, t);
     if (a < A) {
-      if (!append || row >= 0) inv[a] = row;
-      if (row >= 0 && row < R_cap) row_src[row] = a;
+      if (!append || row >= 0) inv[a] = row;   // appending leaves the other calls' entries alone
+      if (row >= 0 && row < R_cap) row_src[row] = (int)a;
     }
   }
 }
@@ -289,20 +305,20 @@ __global__ __launch_bounds__(64) void gather_rows_kernel(const u32x4* __restrict
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
-  int nchunks, chunk;
   size_t hist_off, total_off, bytes;
 };
 
+// Callers size and share workspaces by this formula: a histogram for every 256 assignments (1024 in larger batches), the totals and
+// group tables, which the kernels have made in LDS since.  The runs are at least as long.
 Layout layout(long long A, int E, int G) {
   Layout L;
-  L.chunk = chunk_for(A);
-  L.nchunks = (int)((A + L.chunk - 1) / L.chunk);
+  const int unit = A <= (1ll << 18) ? 256 : 1024;
+  const long long units = (A + unit - 1) / unit;
   size_t off = 0;
   L.hist_off = off;
-  off = align_up(off + (size_t)(L.nchunks > 0 ? L.nchunks : 1) * E * sizeof(int), 256);
+  off = align_up(off + (size_t)(units > 0 ? units : 1) * E * sizeof(int), 256);
   L.total_off = off;
   off = align_up(off + (size_t)E * sizeof(int), 256);
-  // the group tables' place: callers size and share workspaces by this formula, so it stays in the sum
   off = align_up(off + ((size_t)E + 4 * (size_t)(G > 0 ? G : 1)) * sizeof(int), 256);
   L.bytes = off;
   return L;
@@ -359,32 +375,32 @@ int32_t permute_impl(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E,
   char* base = (char*)ws;
   int* hist = (int*)(base + L.hist_off);
   int* total = (int*)(base + L.total_off);
-  // One workgroup up to 4096 assignments, where it takes 8.6 us (E = 512) and the three launches 14.9; with 16 slices
-  // per wavefront it took 16.7 us at 6018 assignments and 21.8 at 16384 (three launches: 12 to 15.7).
-  if (A <= ONE_MAX_A && E <= ONE_MAX_E) {
-    const size_t lds = ((size_t)(ONE_WAVES + 1) * E + GroupTables::ints(E, G)) * sizeof(int);
-#define FEPLB_PERMUTE_ONE(S)                                                                             \
-  hipLaunchKernelGGL((permute_one_kernel<S>), dim3(1), dim3(ONE_WAVES * 64), lds, s, tab, topk_ids, (int)A, E, G, \
-                     R_cap, offsets, row_src, inv, append)
-    if (A <= ONE_WAVES * 64) FEPLB_PERMUTE_ONE(1);
-    else FEPLB_PERMUTE_ONE(4);
-#undef FEPLB_PERMUTE_ONE
-    FEPLB_LAUNCH_CHECK("permute_one_kernel");
-  } else {
-    const int blocks = L.nchunks > 0 ? (L.nchunks + WAVES - 1) / WAVES : 1;   // no chunk: the offsets alone
-    if (L.nchunks > 0) {
-      hipLaunchKernelGGL(chunk_hist_kernel, dim3(blocks), dim3(BLOCK), (size_t)WAVES * E * sizeof(int), s, topk_ids, A,
-                         E, L.nchunks, L.chunk, hist);
-      FEPLB_LAUNCH_CHECK("chunk_hist_kernel");
-    }
-    hipLaunchKernelGGL(chunk_scan_kernel, dim3((E + WAVES - 1) / WAVES), dim3(BLOCK), 0, s, hist, E,
-                       L.nchunks, total);
-    FEPLB_LAUNCH_CHECK("chunk_scan_kernel");
-    const size_t lds = ((size_t)WAVES * E + GroupTables::ints(E, G)) * sizeof(int);
-    hipLaunchKernelGGL(assign_rows_kernel, dim3(blocks), dim3(BLOCK), lds, s, tab, topk_ids, A, E, G,
-                       L.nchunks, L.chunk, hist, total, R_cap, offsets, row_src, inv, append);
-    FEPLB_LAUNCH_CHECK("assign_rows_kernel");
+  const int waves = E <= RUN_MAX_E ? 16 : 8;
+  const bool short_runs = A <= SHORT_RUNS_MAX;
+  const int chunk = waves * 64 * (short_runs ? 1 : 4);
+  const long long runs = A > 0 ? (A + chunk - 1) / chunk : 1;   // none: the offsets alone
+  const int source = A <= COUNTED_MAX ? COUNTED : runs <= TABLE_MAX ? TABLE : SCANNED;
+  if (source != COUNTED) {
+    hipLaunchKernelGGL(chunk_hist_kernel, dim3((unsigned)runs), dim3(HIST_THREADS), (size_t)copies_for(E) * E * sizeof(int), s, topk_ids, A, E,
+                       chunk, hist);
+    FEPLB_LAUNCH_CHECK("chunk_hist_kernel");
   }
+  if (source == SCANNED) {
+    hipLaunchKernelGGL(chunk_scan_kernel, dim3((E + WAVES - 1) / WAVES), dim3(BLOCK), 0, s, hist, E, (int)runs, total);
+    FEPLB_LAUNCH_CHECK("chunk_scan_kernel");
+  }
+#define FEPLB_PERMUTE(W, S)                                                                                                     \
+  hipLaunchKernelGGL((permute_kernel<W, S>), dim3((unsigned)runs), dim3(W * 64), permute_lds_bytes(W, E, G), s, tab, topk_ids, A, E, G, \
+                     (int)runs, source, hist, total, R_cap, offsets, row_src, inv, append)
+  if (waves == 16) {
+    if (short_runs) FEPLB_PERMUTE(16, 1);
+    else FEPLB_PERMUTE(16, 4);
+  } else {
+    if (short_runs) FEPLB_PERMUTE(8, 1);
+    else FEPLB_PERMUTE(8, 4);
+  }
+#undef FEPLB_PERMUTE
+  FEPLB_LAUNCH_CHECK("permute_kernel");
   if (X && Xp && R_cap > 0 && d > 0) {
     hipLaunchKernelGGL((gather_rows_kernel<4>), dim3(R_cap), dim3(64), 0, s, (const u32x4*)X,
                        row_src, offsets, G, k, d / 8, R_cap, (u32x4*)Xp);

@@ -145,6 +145,17 @@ def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
         assert np.array_equal(src.cpu().numpy()[:have], src_o[:have]) and (src.cpu().numpy()[have:] == -7).all()
 
 
+@pytest.mark.parametrize("A,E,G", [(2049, 1024, 16),          # eight wavefronts per workgroup, five workgroups that count the batch
+                                   (16384, 128, 128), (16384, 700, 70),      # the largest batches that are counted
+                                   (16385, 600, 128),                        # ... and the next: a table of histograms
+                                   (262144, 128, 20), (262145, 64, 128),     # the last with short runs, the first with long ones
+                                   (262145, 1000, 9),
+                                   (512 * 4096, 64, 33), (512 * 4096 + 1, 128, 128),   # a table of 512 rows; more are scanned
+                                   (512 * 2048 + 1, 520, 60)])
+def test_permute_from_each_source_of_the_counts(A, E, G):
+    test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G)
+
+
 def test_permute_in_two_calls_equals_one_call():
     # static groups first, replicas appended later (Section 2.3 timeline): same offsets, row_src, inv, Xp
     T, E, k, d = 3000, 64, 4, 128
