@@ -175,7 +175,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the Stream object, which takes 2.5 us of each call to make
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
@@ -207,11 +208,11 @@ def feplb_permute_workspace_bytes(T, k, E, G) -> int:
 
 
 def _group_array(groups: Sequence):
-    arr = (Group * max(len(groups), 1))()
-    for i, g in enumerate(groups):
+    flat = []
+    for g in groups:
         e, lo, hi = (g.expert, g.ord_lo, g.ord_hi) if isinstance(g, Group) else g
-        arr[i] = Group(int(e), int(lo), int(hi))
-    return arr
+        flat += (e, lo, hi)
+    return C.cast((C.c_int32 * max(len(flat), 3))(*map(int, flat)), C.POINTER(Group))
 
 
 def feplb_permute(topk_ids, E, groups, X, R_cap, Xp=None, offsets=None, row_src=None, inv=None,
@@ -237,9 +238,8 @@ def feplb_permute(topk_ids, E, groups, X, R_cap, Xp=None, offsets=None, row_src=
         row_src = torch.empty((max(R_cap, 1),), dtype=torch.int32, device=dev)
     if inv is None:
         inv = torch.empty((max(T * k, 1),), dtype=torch.int32, device=dev)
-    need = feplb_permute_workspace_bytes(T, k, E, G)
     if ws is None:
-        ws = torch.empty((need,), dtype=torch.uint8, device=dev)
+        ws = torch.empty((feplb_permute_workspace_bytes(T, k, E, G),), dtype=torch.uint8, device=dev)
     fn = lib().feplb_permute_append if append else lib().feplb_permute
     _check(fn(_ptr(topk_ids), T, k, E, _group_array(groups), G, _ptr(X), d, _ptr(Xp),
               R_cap, _ptr(offsets), _ptr(row_src), _ptr(inv), _ptr(ws), ws.numel(),
@@ -252,10 +252,7 @@ def feplb_grouped_ffn_workspace_bytes(R_cap, G) -> int:
 
 
 def _ptr_array(tensors: Sequence[Optional[torch.Tensor]]):
-    arr = (C.c_void_p * max(len(tensors), 1))()
-    for i, t in enumerate(tensors):
-        arr[i] = None if t is None else (t if isinstance(t, int) else _ptr(t))
-    return arr
+    return (C.c_void_p * max(len(tensors), 1))(*[t if isinstance(t, int) else _ptr(t) for t in tensors])
 
 
 def feplb_grouped_ffn(Xp, offsets, g_begin, g_end, d, f, w_gate, w_up, w_down, H, Yp,
