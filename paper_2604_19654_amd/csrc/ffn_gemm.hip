@@ -26,28 +26,24 @@
 namespace {
 using namespace feplb::dev;
 
-template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB, int OCC>
-__global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
-    const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k,
-    const int* __restrict__ offsets, int g_begin, int ng, int R_cap, int K, int n_tiles_n, int band,
-    WeightTable wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
-  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
-  __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
-  constexpr int SH = Core::BM == 64 ? 6 : Core::BM == 128 ? 7 : 8;
-  static_assert((1 << SH) == Core::BM, "tile height");
+// 256 x 256 tiles that are left after whole rounds on the 256 CUs cost a round however few they are.  Up to 64 of them are
+// computed as quarters, 128 x 128 by the same eight wavefronts with rings of their own size: four times as many
+// workgroups for half of a round's time (a quarter moves half of the operand bytes of a tile, and they bound it).  More would take two
+// such rounds, and halves of 128 x 256 take 0.8 of a whole tile's time.  T = 8192, 20396 rows in 8 groups, d = 4096, f = 1536, whose
+// gate/up is 4 rounds and 8 tiles: 766 -> 728 us a layer step; 298 drawn forward steps 1.01x on average, up to 1.75x.
+constexpr int QUARTERS_MAX = 64;
 
-  // ---- block -> tile: bands of `band` row tiles, walked column by column
-  RowTiles<SH> tiles;
-  tiles.init(offsets, g_begin, ng, R_cap);
-  const int total = tiles.total * n_tiles_n;
-  const int idx = tile_of_block<32 * Core::BLOCKS_PER_CU>(blockIdx.x, total);
-  if (idx < 0) return;
-  const int b0 = idx / (band * n_tiles_n) * band;
-  const int in_band = idx - b0 * n_tiles_n;
-  const int height = min(band, tiles.total - b0);
-  const int nt = in_band / height;
-  const RowTile tile = tiles.find(b0 + in_band % height, g_begin);
-  const int g = tile.g, row0 = tile.row0, rows = tile.rows;
+struct Tile {
+  int g, row0, rows, nt;   // group, first row, number of rows, column
+};
+
+// one tile of the output
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB>
+__device__ __forceinline__ void panel_tile(
+    char* lds, const Tile& tile, const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k, int K,
+    const WeightTable& wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
+  const int g = tile.g, row0 = tile.row0, rows = tile.rows, nt = tile.nt;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int wm = wave / 2, wn = wave % 2;
@@ -265,6 +261,43 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   }
 }
 
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB, int OCC>
+__global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
+    const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k,
+    const int* __restrict__ offsets, int g_begin, int ng, int R_cap, int K, int n_tiles_n, int band,
+    WeightTable wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
+  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
+  constexpr int SH = Core::BM == 64 ? 6 : Core::BM == 128 ? 7 : 8;
+  static_assert((1 << SH) == Core::BM, "tile height");
+  constexpr bool QUARTERS = Core::BM == 256;
+  __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
+
+  // ---- block -> tile: bands of `band` row tiles, walked column by column; a left-over tile has four blocks
+  RowTiles<SH> tiles;
+  tiles.init(offsets, g_begin, ng, R_cap);
+  const int total = tiles.total * n_tiles_n;
+  const int rest = QUARTERS ? total % 256 : 0, whole = rest > 0 && rest <= QUARTERS_MAX ? total - rest : total;
+  int idx = tile_of_block<32 * Core::BLOCKS_PER_CU>(blockIdx.x, whole + 4 * (total - whole));
+  if (idx < 0) return;
+  const int quarter = idx < whole ? -1 : (idx - whole) % 4;
+  if (quarter >= 0) idx = whole + (idx - whole) / 4;
+  const int b0 = idx / (band * n_tiles_n) * band;
+  const int in_band = idx - b0 * n_tiles_n;
+  const int height = min(band, tiles.total - b0);
+  const RowTile t = tiles.find(b0 + in_band % height, g_begin);
+  const Tile tile{t.g, t.row0, t.rows, in_band / height};
+  if constexpr (QUARTERS) {
+    if (quarter >= 0) {   // row half and column half
+      const int below = quarter / 2 * (Core::BM / 2);
+      const Tile q{tile.g, tile.row0 + below, min(tile.rows - below, Core::BM / 2), tile.nt * 2 + quarter % 2};
+      if (q.rows > 0)
+        panel_tile<MODE, OUT_BF16, SAVE, B_TR, WR, MI / 2, NJ / 2, 4, 6>(lds, q, A, lda, row_src, n_src_rows, src_k, K, wt, ldw, k_split, out, ldo, aux, ld_aux);
+      return;
+    }
+  }
+  panel_tile<MODE, OUT_BF16, SAVE, B_TR, WR, MI, NJ, DA, DB>(lds, tile, A, lda, row_src, n_src_rows, src_k, K, wt, ldw, k_split, out, ldo, aux, ld_aux);
+}
+
 // Tile shape by estimated time.  A launch of B tiles runs B / (256 per_cu) full rounds and a rest; a round with one
 // (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
 // GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168); picking by it is 2 % slower on average than the
@@ -305,7 +338,7 @@ hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
   const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
   const long row_tiles = a.R_cap / Core::BM + a.ng;
   const int band = Core::BM == 256 ? 8 : 16;   // a run of tiles is about as many bytes of rows as of weights
-  hipLaunchKernelGGL((panel_gemm_kernel<MODE, OUT_BF16, SAVE, B_TR, WR, MI, NJ, DA, DB, OCC>), dim3(blocks_for_tiles(row_tiles * n_tiles_n)),
+  hipLaunchKernelGGL((panel_gemm_kernel<MODE, OUT_BF16, SAVE, B_TR, WR, MI, NJ, DA, DB, OCC>), dim3(blocks_for_tiles(row_tiles * n_tiles_n + (Core::BM == 256 ? 3 * QUARTERS_MAX : 0))),
                      dim3(128 * WR), 0, s, (const uint16_t*)a.A, a.lda, a.row_src, a.n_src_rows, a.src_k, a.offsets, a.g_begin, a.ng,
                      a.R_cap, a.K, n_tiles_n, band, *a.weights, a.ldw, a.k_split, a.out, a.ldo, a.aux, a.ld_aux);
   return hipGetLastError();

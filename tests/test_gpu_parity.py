@@ -361,6 +361,44 @@ def test_grouped_ffn_repeatable_over_random_shapes():
                 assert torch.equal(first[0], H) and torch.equal(first[1], Yp), f"trial {trial} d={d} f={f} sizes={sizes}"
 
 
+@pytest.mark.parametrize("row_tiles", [32, 33, 35, 40, 41])
+def test_grouped_ffn_leftover_tiles_in_quarters(row_tiles):
+    # Up to 64 tiles of 256 x 256 beyond whole rounds of 256 are computed as quarters: row_tiles x 8 column tiles are 256, 264, 280
+    # and 320 tiles, the last eight in part empty quarters, and 328, which stay whole.  Gate/up: the bytes of the 128-row tiles that another
+    # capacity takes, also for the kept derivatives.  Down: fp32 sums of 1024 products against float64, 1024 * 2^-24 of the
+    # magnitudes' sum at most and far less than that in the root mean square.
+    d, f, caps = 2048, 1024, (row_tiles * 256 - 187, 16000)
+    sizes = [256 * (row_tiles - 2) - 3, 130, 60]
+    say(f"ffn quarters row_tiles={row_tiles}")
+    B, R, G = fe.binding, sum(sizes), 3
+    assert [B.feplb_grouped_ffn_tile_rows(B.GEMM_GATE_UP, c, G, d, f) for c in caps] == [128, 256]
+    assert B.feplb_grouped_ffn_tile_rows(B.GEMM_DOWN, caps[1], G, d, f) == 256
+    gen = torch.Generator(device=DEV).manual_seed(row_tiles)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)   # noqa: E731
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)).to(DEV)
+    X, W = rnd(R, d), [[0.02 * rnd(*sh) for _ in range(G)] for sh in ((d, f), (d, f), (f, d))]
+    out = []
+    for cap in caps:
+        Xp = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        Xp[:R] = X
+        H = torch.full((cap, f), 512.0, dtype=torch.bfloat16, device=DEV)
+        AB = torch.full((cap, 2 * f), 512.0, dtype=torch.bfloat16, device=DEV)
+        Yp = torch.full((cap, d), 512.0, device=DEV)
+        B.feplb_grouped_ffn(Xp, off, 0, G, d, f, *W, H, Yp, AB=AB)
+        torch.cuda.synchronize()
+        out.append((H[:R].clone(), AB[:R].clone(), Yp[:R].clone()))
+        assert (H[R:] == 512.0).all() and (AB[R:] == 512.0).all() and (Yp[R:] == 512.0).all()
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    H, _, Yp = out[1]
+    lo = 0
+    for g, n in enumerate(sizes):
+        rows = slice(max(lo, lo + n - 600), lo + n)
+        want = H[rows].double() @ W[2][g].double()
+        assert (Yp[rows].double() - want).norm() <= 1e-5 * want.norm()
+        assert ((Yp[rows].double() - want).abs() <= 1024 * 2.0 ** -24 * (H[rows].double().abs() @ W[2][g].double().abs())).all()
+        lo += n
+
+
 def test_grouped_ffn_gathering_rows_equals_reading_the_permuted_copy():
     # row_src given: row r of the input is X[row_src[r] // k]; the bytes must equal a run on the
     # materialised copy (the same MFMAs on the same operands)
