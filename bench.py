@@ -33,13 +33,13 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "aaf735130c409c8c8dc1924baa851526bae0feafa69c97dd04066d7c7ba271bc",
-           "gate_up": {"read": 2666182 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
-           "down": {"read": 1346189 * 1024 * 2.0, "written": 1578718 * 1024}},
+           "sources_sha256": "758c2853e8e3ffc30541ba57979dc8cdc25b29b410b93b30c21708a7e9e0ca65",
+           "gate_up": {"read": 2666811 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
+           "down": {"read": 1337391 * 1024 * 2.0, "written": 1573575 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "aaf735130c409c8c8dc1924baa851526bae0feafa69c97dd04066d7c7ba271bc",
-           "gate_up": {"read": 549983 * 1024 * 2.0, "written": 61188 * 1024},
-           "down": {"read": 242963 * 1024 * 2.0, "written": 327153 * 1024}},
+           "sources_sha256": "758c2853e8e3ffc30541ba57979dc8cdc25b29b410b93b30c21708a7e9e0ca65",
+           "gate_up": {"read": 554536 * 1024 * 2.0, "written": 61188 * 1024},
+           "down": {"read": 241278 * 1024 * 2.0, "written": 327190 * 1024}},
 }
 METRIC = "grouped-FFN TFLOP/s & % bf16 MFMA peak per rank share; permute/combine GB/s"
 
