@@ -33,11 +33,11 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "758c2853e8e3ffc30541ba57979dc8cdc25b29b410b93b30c21708a7e9e0ca65",
+           "sources_sha256": "862cc6c183201bf9c2c3d45c516226143691123b300edc395572b3ffbeedd542",
            "gate_up": {"read": 2666811 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
            "down": {"read": 1337391 * 1024 * 2.0, "written": 1573575 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "758c2853e8e3ffc30541ba57979dc8cdc25b29b410b93b30c21708a7e9e0ca65",
+           "sources_sha256": "862cc6c183201bf9c2c3d45c516226143691123b300edc395572b3ffbeedd542",
            "gate_up": {"read": 554536 * 1024 * 2.0, "written": 61188 * 1024},
            "down": {"read": 241278 * 1024 * 2.0, "written": 327190 * 1024}},
 }

@@ -12,8 +12,8 @@
 // 1520 TFLOP/s); all grouped GEMMs of the large shapes 1.03x (weight gradients) to 1.08x, small ones unchanged.
 //
 // What bounds it.  On large shapes the chip is limited by power and by moving operands, not by the pipeline: the matrix
-// pipes are busy 81 % of the time at a clock that has come down to 1.5 to 1.6 GHz (gate/up, 93580 and 37490 rows,
-// d = 6144, f = 2048), and ring depths, band heights, s_setprio and the order of LDS reads between the MFMAs change
+// pipes are busy 80 % of the time at a clock that has come down to 1.65 to 1.85 GHz (gate/up, 93580 and 37490 rows,
+// d = 6144, f = 2048), and, measured with MFMAs 32 x 32 x 16, ring depths, band heights, s_setprio and the order of LDS reads between the MFMAs change
 // nothing (+-0.5 %).  The loop with its loads taken out, which multiplies the same operands again and again, runs 1.3x as
 // fast (93580 x 6144 x 4096: 3500 -> 2690 us).  What did move it is data movement:
 // requesting the loads of a sub-step spread over its four slices instead of in one burst behind the

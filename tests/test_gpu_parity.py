@@ -112,7 +112,7 @@ def test_permute_parity(T, E, k, d, skew, seed):
                                    (4097, 130, 65), (4095, 512, 128), (4096, 513, 128), (16385, 128, 128),
                                    (70001, 128, 100)])
 def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
-    # up to 4096 assignments over at most 512 experts one workgroup does it all, 1 or 4 slices of 64 per wavefront;
+    # one workgroup up to 1024 assignments, then runs of as many, eight wavefronts instead of sixteen from 513 experts on;
     # groups in both wavefronts of the table, several windows per expert, ids that name no expert
     say(f"permute A={A} E={E} G={G}")
     rng = np.random.default_rng(A + E)
