@@ -15,7 +15,7 @@
 // Where the occurrences outside the run come from:
 //   COUNTED  every workgroup counts the whole batch for itself: one launch
 //   TABLE    chunk_hist has written every run's histogram, every workgroup adds them up
-//   SCANNED  chunk_scan has turned the histograms into prefix sums (very large batches)
+//   SCANNED  chunk_scan has turned the histograms into prefix sums (large batches, many experts)
 // gather_rows: Xp[r,:] = X[row_src[r] / k, :], one wavefront per row, 16-byte lanes
 // (pure HBM traffic: 2*R*d*2 bytes)
 #include "common.h"
@@ -163,14 +163,24 @@ __device__ __forceinline__ int bits_for(int E) { return E > 1 ? 32 - __builtin_c
 
 enum Source { COUNTED, TABLE, SCANNED };
 
-// Measured inside a graph, E = 128 unless said otherwise, 16 local experts (the three launches of before: 11.6 us at 6018 and 10004
-// assignments, 14.7 at 65536, 25.4 at 262144, 36.8 at 1048576):
-//   counting the batch in every workgroup (6018, E = 64: 6.5 us; 10004, E = 64: 7.1; 49728: 14.6) against a table of histograms by
-//   a launch of its own (7.9, 8.1 and 9.8 us): the line lies between 10004 and 49728;
-//   runs of 1024 against 4096 assignments: 12.0 against 15.2 us at 262144, where there are 256 or 64 workgroups to walk them; at
-//   1048576 the table of 1024 runs would be 1024 rows for each of 1024 workgroups, and runs of 4096 take 21.1 us;
-//   every workgroup adds up a table of at most 512 rows; beyond (2 million assignments) the rows are read by too many.
-constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, TABLE_MAX = 512;
+// Measured inside a graph, E = 128 unless said otherwise, 16 local experts (three launches, runs of 256 or 1024 assignments and bases
+// from a scan, as before all of this: 12.0 us at 8192 assignments, 14.7 at 65536, 24.4 at 262144, 38.7 at 1048576):
+//   counting the batch in every workgroup (8192: 6.9 us; 16384: 8.5; E = 1024 11.7; 49728, E = 128: 14.6) against a table of histograms by
+//   a launch of its own (16392: 8.7; E = 1024 12.4; 49728: 9.8): the line lies between 10004 and 49728;
+//   runs of 1024 against 4096 assignments: 11.0 against 13.8 us at 262144, where there are 256 or 64 workgroups to walk them;
+//   at 1048576 runs of 4096 take 18.4 us (from scanned bases).
+// Every workgroup reads the whole table, runs x E words, which saves the launch of the scan until reading takes longer.  Table against
+// scan, us: in runs of 1024, 32768 words (E = 128, 262144) 11.0 and 12.9, 49152 words (E = 256, 196608) 12.4 and 12.8, 65536 words (E = 256,
+// 262144) 14.0 and 13.8, 131072 words (E = 512, 262144) 19.8 and 14.8; in runs of 4096, 4096 words (E = 64, 262152) 12.3 and 13.7, 8320
+// words (E = 128) 13.8 and 13.9, 16640 words (E = 256) 16.4 and 14.3, 262144 words (E = 512, 2097152) 126 and 33.  Above RUN_MAX_E experts a
+// workgroup has half as many threads for longer rows, and the scan is ahead everywhere (16392, E = 520: 11.1 and 10.8; 1048576,
+// E = 1024: 271 and 28).
+constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, TABLE_WORDS_SHORT = 49152, TABLE_WORDS_LONG = 8192;
+
+Source pick_source(long long A, int E, long long runs, bool short_runs) {
+  if (A <= COUNTED_MAX) return COUNTED;
+  return E <= RUN_MAX_E && runs * E <= (short_runs ? TABLE_WORDS_SHORT : TABLE_WORDS_LONG) ? TABLE : SCANNED;
+}
 
 // LDS: run[RUN_WAVES][E] | before[copies][E] | after[copies][E] | total[E] | group tables
 size_t permute_lds_bytes(int waves, int E, int G) {
@@ -379,7 +389,7 @@ int32_t permute_impl(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E,
   const bool short_runs = A <= SHORT_RUNS_MAX;
   const int chunk = waves * 64 * (short_runs ? 1 : 4);
   const long long runs = A > 0 ? (A + chunk - 1) / chunk : 1;   // none: the offsets alone
-  const int source = A <= COUNTED_MAX ? COUNTED : runs <= TABLE_MAX ? TABLE : SCANNED;
+  const Source source = pick_source(A, E, runs, short_runs);
   if (source != COUNTED) {
     hipLaunchKernelGGL(chunk_hist_kernel, dim3((unsigned)runs), dim3(HIST_THREADS), (size_t)copies_for(E) * E * sizeof(int), s, topk_ids, A, E,
                        chunk, hist);

@@ -147,13 +147,43 @@ def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
 
 @pytest.mark.parametrize("A,E,G", [(2049, 1024, 16),          # eight wavefronts per workgroup, five workgroups that count the batch
                                    (16384, 128, 128), (16384, 700, 70),      # the largest batches that are counted
-                                   (16385, 600, 128),                        # ... and the next: a table of histograms
+                                   (16385, 512, 128),                        # ... and the next: a table of histograms
+                                   (16385, 600, 128), (131072, 1024, 20),    # but above 512 experts a scan
                                    (262144, 128, 20), (262145, 64, 128),     # the last with short runs, the first with long ones
-                                   (262145, 1000, 9),
-                                   (512 * 4096, 64, 33), (512 * 4096 + 1, 128, 128),   # a table of 512 rows; more are scanned
+                                   (262144, 192, 33), (262144, 193, 33),     # short runs: a table of 49152 words is the largest
+                                   (128 * 4096, 64, 33), (128 * 4096 + 1, 64, 33),   # long runs: 8192 words
+                                   (262145, 1000, 9), (512 * 4096, 8, 20), (512 * 4096, 64, 33), (512 * 4096 + 1, 128, 128),
                                    (512 * 2048 + 1, 520, 60)])
 def test_permute_from_each_source_of_the_counts(A, E, G):
     test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G)
+
+
+@pytest.mark.parametrize("A,E", [(16385, 128), (262144, 128), (262144, 512), (262145, 1000), (131072, 1024), (524288, 128),
+                                 (1048576, 520), (2097152, 256), (2097152, 512)])
+def test_permute_reads_no_large_table_in_every_workgroup(A, E):
+    # Every workgroup may read all runs' histograms (runs x E words) only while they are few: at 2 million assignments and 512
+    # experts, 512 workgroups that read 1 MB each took twice as long as three launches with a scan.  50 MB in all are the most here.  Which way a
+    # call went shows in the scratch, laid out as [histogram rows | totals]: the rows that were written are the runs,
+    # and only the scan writes the totals.
+    say(f"permute table A={A} E={E}")
+    B = fe.binding
+    ids = torch.randint(0, E, (A, 1), generator=torch.Generator(device=DEV).manual_seed(A + E), dtype=torch.int32, device=DEV)
+    ws = torch.full((B.feplb_permute_workspace_bytes(A, 1, E, 1) // 4,), -1, dtype=torch.int32, device=DEV)
+    inv = torch.empty((A,), dtype=torch.int32, device=DEV)
+    fe.feplb_permute(ids, E, [(0, 0, fe.ORD_MAX)], None, 1, None, None, torch.empty((1,), dtype=torch.int32, device=DEV), inv,
+                     ws=ws.view(torch.uint8))
+    torch.cuda.synchronize()
+    counts = torch.bincount(ids[:, 0].long(), minlength=E)
+    unit = 256 if A <= 1 << 18 else 1024
+    units = -(-A // unit)
+    total = ws[-(-units * E // 64) * 64:][:E]
+    runs = int((ws[: units * E].view(units, E) >= 0).all(dim=1).sum())
+    scanned = bool((total >= 0).any())
+    if scanned:
+        assert torch.equal(total.long(), counts)
+    say(f"  {runs} runs, {'scanned' if scanned else f'{runs * runs * E * 4 / 1e6:.1f} MB of table read'}")
+    assert runs > 0 and (scanned or runs * runs * E * 4 <= 256 * 49152 * 4)
+    assert torch.equal((inv >= 0), ids[:, 0] == 0)
 
 
 def test_permute_in_two_calls_equals_one_call():
