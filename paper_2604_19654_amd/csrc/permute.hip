@@ -177,8 +177,10 @@ enum Source { COUNTED, TABLE, SCANNED };
 // E = 1024: 271 and 28).
 constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, TABLE_WORDS_SHORT = 49152, TABLE_WORDS_LONG = 8192;
 
-Source pick_source(long long A, int E, long long runs, bool short_runs) {
-  if (A <= COUNTED_MAX) return COUNTED;
+// in_place: the rows replace the assignments (inv == topk_ids).  A workgroup that counts the batch reads other runs' assignments, which
+// those replace meanwhile; the other sources read them in launches ahead, and each run's own before its rows are written.
+Source pick_source(long long A, int E, long long runs, bool short_runs, bool in_place) {
+  if (A <= COUNTED_MAX && (runs == 1 || !in_place)) return COUNTED;
   return E <= RUN_MAX_E && runs * E <= (short_runs ? TABLE_WORDS_SHORT : TABLE_WORDS_LONG) ? TABLE : SCANNED;
 }
 
@@ -190,10 +192,10 @@ size_t permute_lds_bytes(int waves, int E, int G) {
 // A workgroup owns RUN_WAVES * 64 * SLICES assignments; they stay in registers between the counting and the walk, which takes
 // about 0.9 us per slice.
 template <int RUN_WAVES, int SLICES>
-__global__ __launch_bounds__(RUN_WAVES * 64) void permute_kernel(GroupTable tab, const int* __restrict__ ids, long long A, int E, int G,
+__global__ __launch_bounds__(RUN_WAVES * 64) void permute_kernel(GroupTable tab, const int* ids, long long A, int E, int G,
                                                                  int nchunks, int source, const int* __restrict__ chunk_hist,
                                                                  const int* __restrict__ totals, int R_cap, int* offsets,
-                                                                 int* __restrict__ row_src, int* __restrict__ inv, int append) {
+                                                                 int* __restrict__ row_src, int* inv, int append) {
   extern __shared__ int lds[];
   constexpr int THREADS = RUN_WAVES * 64;
   constexpr int COPIES = copies_for(RUN_WAVES == 16 ? RUN_MAX_E : RUN_MAX_E + 1);
@@ -389,7 +391,7 @@ int32_t permute_impl(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E,
   const bool short_runs = A <= SHORT_RUNS_MAX;
   const int chunk = waves * 64 * (short_runs ? 1 : 4);
   const long long runs = A > 0 ? (A + chunk - 1) / chunk : 1;   // none: the offsets alone
-  const Source source = pick_source(A, E, runs, short_runs);
+  const Source source = pick_source(A, E, runs, short_runs, inv == topk_ids);
   if (source != COUNTED) {
     hipLaunchKernelGGL(chunk_hist_kernel, dim3((unsigned)runs), dim3(HIST_THREADS), (size_t)copies_for(E) * E * sizeof(int), s, topk_ids, A, E,
                        chunk, hist);

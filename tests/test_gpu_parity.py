@@ -186,6 +186,22 @@ def test_permute_reads_no_large_table_in_every_workgroup(A, E):
     assert torch.equal((inv >= 0), ids[:, 0] == 0)
 
 
+@pytest.mark.parametrize("A,E", [(1000, 128), (1025, 128), (16384, 64), (12000, 1024), (70001, 128)])
+def test_permute_may_replace_the_assignments_by_their_rows(A, E):
+    # inv in the place of topk_ids: no workgroup may read another one's assignments after that one has written its rows
+    say(f"permute in place A={A} E={E}")
+    rng = np.random.default_rng(A)
+    ids = np.minimum(rng.zipf(1.3, size=(A, 1)) - 1, E - 1).astype(np.int32)
+    groups = [(int(e), 0, fe.ORD_MAX) for e in rng.permutation(E)[:20]]
+    off_o, src_o, inv_o = orc.permute(ids, groups)
+    for _ in range(5):
+        both = torch.from_numpy(ids).to(DEV)
+        _, off, src, _ = fe.feplb_permute(both, E, groups, None, max(len(src_o), 1), inv=both)
+        torch.cuda.synchronize()
+        assert np.array_equal(off.cpu().numpy(), off_o) and np.array_equal(both.cpu().numpy()[:, 0], inv_o)
+        assert np.array_equal(src.cpu().numpy()[: len(src_o)], src_o)
+
+
 def test_permute_in_two_calls_equals_one_call():
     # static groups first, replicas appended later (Section 2.3 timeline): same offsets, row_src, inv, Xp
     T, E, k, d = 3000, 64, 4, 128
