@@ -166,7 +166,10 @@ enum Source { COUNTED, TABLE, SCANNED };
 // Measured inside a graph, E = 128 unless said otherwise, 16 local experts (three launches, runs of 256 or 1024 assignments and bases
 // from a scan, as before all of this: 12.0 us at 8192 assignments, 14.7 at 65536, 24.4 at 262144, 38.7 at 1048576):
 //   counting the batch in every workgroup (8192: 6.9 us; 16384: 8.5; E = 1024 11.7; 49728, E = 128: 14.6) against a table of histograms by
-//   a launch of its own (16392: 8.7; E = 1024 12.4; 49728: 9.8): the line lies between 10004 and 49728;
+//   a launch of its own (16392: 8.7; E = 1024 12.4; 49728: 9.8): the line lies between 10004 and 49728.  Above RUN_MAX_E experts there is
+//   one copy of a workgroup's histogram, and a batch that is all one expert adds to one word of it, lane by lane: E = 600, 16384
+//   assignments 11.4 us drawn evenly, 12.5 half of them one expert, 19.2 all; from scanned bases 11.0, 11.2 and 11.3 (10240: 9.1, 9.8 and 13.9,
+//   scanned 10.9 to 11.4): the line lies at 10240;
 //   runs of 1024 against 4096 assignments: 11.0 against 13.8 us at 262144, where there are 256 or 64 workgroups to walk them;
 //   at 1048576 runs of 4096 take 18.4 us (from scanned bases).
 // Every workgroup reads the whole table, runs x E words, which saves the launch of the scan until reading takes longer.  Table against
@@ -175,12 +178,12 @@ enum Source { COUNTED, TABLE, SCANNED };
 // words (E = 128) 13.8 and 13.9, 16640 words (E = 256) 16.4 and 14.3, 262144 words (E = 512, 2097152) 126 and 33.  Above RUN_MAX_E experts a
 // workgroup has half as many threads for longer rows, and the scan is ahead everywhere (16392, E = 520: 11.1 and 10.8; 1048576,
 // E = 1024: 271 and 28).
-constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, TABLE_WORDS_SHORT = 49152, TABLE_WORDS_LONG = 8192;
+constexpr long long SHORT_RUNS_MAX = 262144, COUNTED_MAX = 16384, COUNTED_MAX_ONE_COPY = 10240, TABLE_WORDS_SHORT = 49152, TABLE_WORDS_LONG = 8192;
 
 // in_place: the rows replace the assignments (inv == topk_ids).  A workgroup that counts the batch reads other runs' assignments, which
 // those replace meanwhile; the other sources read them in launches ahead, and each run's own before its rows are written.
 Source pick_source(long long A, int E, long long runs, bool short_runs, bool in_place) {
-  if (A <= COUNTED_MAX && (runs == 1 || !in_place)) return COUNTED;
+  if (A <= (copies_for(E) > 1 ? COUNTED_MAX : COUNTED_MAX_ONE_COPY) && (runs == 1 || !in_place)) return COUNTED;
   return E <= RUN_MAX_E && runs * E <= (short_runs ? TABLE_WORDS_SHORT : TABLE_WORDS_LONG) ? TABLE : SCANNED;
 }
 
