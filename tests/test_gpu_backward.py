@@ -13,7 +13,7 @@ from paper_2604_19654_amd import binding as B
 from paper_2604_19654_amd.training import FfnTrainingStep
 from oracle import feplb_oracle as orc
 from tests.util import (f64, row_rel_err, row_rms_err, bf16_rounding_excess, BWD_RMS_TOL, BWD_MAX_TOL, FORMAT_NSIGMA,
-                        h_rounding_variance)
+                        h_rounding_variance, how_256_row_tiles_run)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -152,14 +152,18 @@ def test_grouped_ffn_backward_parity(sizes, d, f, dxp_dtype):
     assert torch.isnan(r["dAB"][R:].float()).all() and torch.isnan(r["H"][R:].float()).all()
 
 
-@pytest.mark.parametrize("d,f", [(512, 256), (256, 768)])
-def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d, f):
+@pytest.mark.parametrize("d,f,copies,large,capacities", [(512, 256, 1, "quarters", (8000, 16000, 100000)),
+                                                         (256, 768, 1, "quarters", (8000, 16000, 100000)),
+                                                         (1024, 1024, 1, "whole", (5000, 8000)), (1024, 1024, 4, "both", (24000,))])
+def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d, f, copies, large, capacities):
     # The tile shape is picked from the row capacity: each of the two GEMMs takes 64-, 128- and 256-row tiles at one of the
-    # four capacities here.  The input gradients read the weights themselves, or transposes left in WT by an earlier call where none are given.
-    # Every element is the same chain of MFMAs on all ways, so the bytes must be equal.  Group sizes lie at the
+    # capacities here (the largest batch 128- and 256-row tiles).  Few tiles of 256 rows, or few beyond whole rounds, run as quarters; `large` says
+    # which of them a set of sizes and widths has.  The input gradients read the weights themselves, or transposes left in WT by an earlier
+    # call where none are given.  Every element is the same chain of MFMAs on all ways, so the bytes must be equal.  Group sizes lie at the
     # edges of the tiles and of their 32-row blocks.
-    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
-    say(f"ffn input gradients d={d} f={f}")
+    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2] * copies
+    say(f"ffn input gradients d={d} f={f} copies={copies}")
+    assert how_256_row_tiles_run(sizes, f) == how_256_row_tiles_run(sizes, d) == large
     r = run_forward_backward(sizes, d, f, torch.float32)
     R, G = r["R"], len(sizes)
     (dXp_o, _), _ = oracle_backward(r)
@@ -168,9 +172,10 @@ def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d,
     W = [[w[i].to(DEV) for w in r["W"]] for i in range(3)]
     WT = torch.zeros((B.feplb_grouped_ffn_backward_wt_bytes(G, d, f),), dtype=torch.uint8, device=DEV)
     nothing = [[None] * G for _ in range(3)]
-    capacities = (R, 8000, 16000, 100000)
+    capacities = (R, *capacities)
     for gemm in (B.GEMM_DH, B.GEMM_DXP):
-        assert {B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities} == {64, 128, 256}
+        shapes = {B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities}
+        assert {128, 256} <= shapes and (64 in shapes or copies > 1)
     for R_cap in capacities:
         H = torch.zeros((R_cap, f), dtype=torch.bfloat16, device=DEV)
         dYp = torch.full((R_cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)

@@ -9,7 +9,7 @@ import paper_2604_19654_amd as fe
 from paper_2604_19654_amd import runner
 import workloads
 from oracle import feplb_oracle as orc
-from tests.util import f64, row_rel_err, bf16_rounding_excess, ROW_TOL
+from tests.util import f64, row_rel_err, bf16_rounding_excess, how_256_row_tiles_run, ROW_TOL
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -111,7 +111,7 @@ def test_permute_parity(T, E, k, d, skew, seed):
 @pytest.mark.parametrize("A,E,G", [(1, 8, 1), (1023, 8, 8), (1024, 3, 5), (1025, 512, 128), (4096, 512, 128),
                                    (4097, 130, 65), (4095, 512, 128), (4096, 513, 128), (16385, 128, 128),
                                    (70001, 128, 100)])
-def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
+def test_permute_at_the_edges_of_its_runs(A, E, G):
     # one workgroup up to 1024 assignments, then runs of as many, eight wavefronts instead of sixteen from 513 experts on;
     # groups in both wavefronts of the table, several windows per expert, ids that name no expert
     say(f"permute A={A} E={E} G={G}")
@@ -156,7 +156,7 @@ def test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G):
                                    (262145, 1000, 9), (512 * 4096, 8, 20), (512 * 4096, 64, 33), (512 * 4096 + 1, 128, 128),
                                    (512 * 2048 + 1, 520, 60)])
 def test_permute_from_each_source_of_the_counts(A, E, G):
-    test_permute_at_the_edges_of_its_one_workgroup_path(A, E, G)
+    test_permute_at_the_edges_of_its_runs(A, E, G)
 
 
 @pytest.mark.parametrize("A,E", [(16384, 600), (16384, 1024), (16385, 128), (262144, 128), (262144, 512), (262145, 1000), (131072, 1024), (524288, 128),
@@ -333,14 +333,19 @@ def test_grouped_ffn_short_tail_tiles_repeatable(d, f, sizes):
     assert eh <= 1.0 and ey.max() <= ROW_TOL
 
 
-@pytest.mark.parametrize("f", [384, 128])
-def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
+@pytest.mark.parametrize("d,f,copies,large,capacities", [(512, 384, 1, "quarters", (8000, 16000, 100000)),
+                                                         (512, 128, 1, "quarters", (8000, 16000, 100000)),
+                                                         (1024, 512, 1, "whole", (6000, 16000)), (1024, 512, 4, "both", (10000, 24000))])
+def test_grouped_ffn_tile_shapes_agree_at_their_edges(d, f, copies, large, capacities):
     # The tile shape of the grouped GEMM is picked from the row capacity: both GEMMs take 64-, 128- and 256-row tiles at one
-    # of the four capacities here.  Group sizes lie at the edges of the tiles, of their 32-row blocks and of the loop variants
-    # that skip empty blocks.  Every element is the same chain of MFMAs in all shapes, so the bytes must be equal.
-    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2]
-    d, G = 512, len(sizes)
-    say(f"ffn tile shapes d={d} f={f}")
+    # of the capacities here (the largest batch 128- and 256-row tiles).  Group sizes lie at the edges of the tiles, of their 32-row blocks and of
+    # the loop variants that skip empty blocks.  Few tiles of 256 rows, or few beyond whole rounds, run as quarters; `large` says which of them
+    # a set of sizes and widths has.  Every element is the same chain of MFMAs in all shapes, so the bytes must be equal: with
+    # gathered rows and without, with the derivatives kept and without.
+    sizes = [1, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 191, 255, 256, 257, 300, 2] * copies
+    G = len(sizes)
+    say(f"ffn tile shapes d={d} f={f} copies={copies}")
+    assert how_256_row_tiles_run(sizes, 2 * f) == how_256_row_tiles_run(sizes, d) == large
     offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     R = int(offsets[-1])
     Xp = torch.randn((R, d), generator=torch.Generator().manual_seed(27)).to(torch.bfloat16)
@@ -350,16 +355,22 @@ def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
     X = torch.empty_like(Xp)
     X[order.long()] = Xp
     H_o, Yp_o = orc.grouped_ffn(f64(Xp), offsets, [tuple(f64(m) for m in w) for w in W])
-    first = None
-    capacities = (R, 8000, 16000, 100000)
+    first = first_AB = None
+    capacities = (R, *capacities)
     for gemm in (fe.binding.GEMM_GATE_UP, fe.binding.GEMM_DOWN):
-        assert {fe.binding.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities} == {64, 128, 256}
+        shapes = {fe.binding.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities}
+        assert {128, 256} <= shapes and (64 in shapes or copies > 1)
+    X, Xp, order, off = X.to(DEV), Xp.to(DEV), order.to(DEV), torch.from_numpy(offsets).to(DEV)
     for R_cap in capacities:
-        for yp_dtype in (torch.float32, torch.bfloat16):
+        padded = torch.full((R_cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        padded[:R] = Xp
+        for yp_dtype, gather, keep in ((torch.float32, True, False), (torch.bfloat16, True, False), (torch.float32, False, False),
+                                       (torch.bfloat16, True, True), (torch.float32, False, True)):
             H = torch.full((R_cap, f), 512.0, dtype=torch.bfloat16, device=DEV)
             Yp = torch.full((R_cap, d), 512.0, dtype=yp_dtype, device=DEV)
-            fe.feplb_grouped_ffn(X.to(DEV), torch.from_numpy(offsets).to(DEV), 0, G, d, f, *cols, H, Yp,
-                                 row_src=order.to(DEV), k=1)
+            AB = torch.full((R_cap, 2 * f), 512.0, dtype=torch.bfloat16, device=DEV) if keep else None
+            fe.feplb_grouped_ffn(X if gather else padded, off, 0, G, d, f, *cols, H, Yp,
+                                 **(dict(row_src=order, k=1) if gather else {}), AB=AB)
             torch.cuda.synchronize()
             assert (H[R:].float() == 512.0).all() and (Yp[R:].float() == 512.0).all()
             if first is None:
@@ -367,6 +378,10 @@ def test_grouped_ffn_tile_shapes_agree_at_their_edges(f):
                 assert bf16_rounding_excess(f64(H)[:R], H_o) <= 1.0 and row_rel_err(f64(Yp)[:R], Yp_o).max() <= ROW_TOL
             else:
                 assert torch.equal(H[:R], first[0]) and torch.equal(Yp[:R], first[1].to(yp_dtype))
+            if keep:
+                assert (AB[R:].float() == 512.0).all()
+                first_AB = AB[:R] if first_AB is None else first_AB
+                assert torch.equal(AB[:R], first_AB)
 
 
 def test_grouped_ffn_repeatable_over_random_shapes():

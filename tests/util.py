@@ -1,4 +1,7 @@
 """Helpers shared by the tests: tensor -> float64 arrays, the float tolerance."""
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -135,3 +138,14 @@ def layer_tokens_with_format_bound(orc, x_rows, ids_rows, w_rows, keep_rows, wei
         out[tok] += wj * y
         var[tok] += wj * wj * v
     return out, format_bound(out, var, output_bf16=True)
+
+
+def how_256_row_tiles_run(sizes, columns):
+    """What a grouped GEMM in 256 x 256 tiles makes of groups of these sizes and a weight of `columns` columns: "whole" tiles,
+    "quarters" of 128 x 128, or "both" (whole rounds of 256 tiles, and so few left over that they run as quarters)."""
+    with open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_19654_amd", "csrc",
+                           "ffn_gemm.hip")) as fh:
+        most = int(re.search(r"QUARTERS_MAX = (\d+);", fh.read()).group(1))
+    tiles = sum(-(-n // 256) for n in sizes) * (columns // 256)
+    rest = tiles % 256
+    return "whole" if rest == 0 or rest > most else "quarters" if rest == tiles else "both"
