@@ -334,7 +334,8 @@ def feplb_grouped_ffn_backward(Xp, offsets, g_begin, g_end, d, f, w_gate, w_up, 
 
 
 def feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f) -> int:
-    """Host-only: height in rows of the tiles that grouped GEMM `gemm` (GEMM_*) would compute in."""
+    """Host-only: height in rows of the tiles that grouped GEMM `gemm` (GEMM_*) would be launched in (of 256-row tiles, a few
+    left-over ones may be computed as quarters)."""
     return int(lib().feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f))
 
 
