@@ -226,8 +226,8 @@ void launch_lane(const float* logits, int T, int E, int* ids, float* w, int* cou
 // counts[e] = occurrences of e among the A ids; more than one workgroup add to counts that the router has cleared.
 // Counting inside the router needs no second look at the ids, but its workgroups are many, and each adds a histogram
 // to the same few lines, which the XCDs' caches do not share: with 512 of them the router took 17.5 us (the launch that
-// cleared the counts included) where it takes 6.5 without counting (T = 8192, E = 128, k = 8).  Here a workgroup counts at
-// least COUNT_PER_BLOCK ids and there are at most COUNT_BLOCKS.  Router and counts inside a graph: T = 8192, E = 128, k = 8
+// cleared the counts included) where it takes 6.5 without counting (T = 8192, E = 128, k = 8).  Here there is one
+// workgroup for every COUNT_PER_BLOCK ids begun, COUNT_BLOCKS at most.  Router and counts inside a graph: T = 8192, E = 128, k = 8
 // 17.5 -> 9.1 us; T = 16000, E = 256 45.7 -> 17.1; T = 65536, E = 16, k = 1 27.3 -> 5.7; T = 131072, E = 128 39.7 -> 30.8;
 // T = 96 7.2 -> 6.8.  (4096 or 8192 ids per workgroup: 9.4 and 10.7 us at T = 8192.)
 constexpr int COUNT_THREADS = 1024, COUNT_PER_BLOCK = 2048, COUNT_BLOCKS = 64;
