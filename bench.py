@@ -33,13 +33,13 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "862cc6c183201bf9c2c3d45c516226143691123b300edc395572b3ffbeedd542",
-           "gate_up": {"read": 2666811 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
-           "down": {"read": 1337391 * 1024 * 2.0, "written": 1573575 * 1024}},
+           "sources_sha256": "95561c25c6cbc4a53e31698ff33f16bf70220bbb1fd3e3ea2a03a804bf198c76",
+           "gate_up": {"read": 2669915 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
+           "down": {"read": 1335715 * 1024 * 2.0, "written": 1573694 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "862cc6c183201bf9c2c3d45c516226143691123b300edc395572b3ffbeedd542",
-           "gate_up": {"read": 554536 * 1024 * 2.0, "written": 61188 * 1024},
-           "down": {"read": 241278 * 1024 * 2.0, "written": 327190 * 1024}},
+           "sources_sha256": "95561c25c6cbc4a53e31698ff33f16bf70220bbb1fd3e3ea2a03a804bf198c76",
+           "gate_up": {"read": 551730 * 1024 * 2.0, "written": 61188 * 1024},
+           "down": {"read": 238482 * 1024 * 2.0, "written": 327264 * 1024}},
 }
 METRIC = "grouped-FFN TFLOP/s & % bf16 MFMA peak per rank share; permute/combine GB/s"
 

@@ -194,11 +194,12 @@ __global__ __launch_bounds__(128 * WR, OCC) void wgrad_gemm_kernel(
 
 // Tile shape by estimated time, as for the forward GEMMs: a round of tiles takes `start`, most of it the write of the fp32
 // tile, plus k times the measured cost per k.  Two workgroups per CU (128 x 256) write one tile while they multiply for the
-// other: the better shape up to about 1500 rows per group.  16 groups of 512 rows, d = 4096, f = 1536: 413 us (256 x 256),
-// 383 (128 x 256), 558 (64 x 128); 32 groups of 2500 rows, d = 7168, f = 2048: 5.97, 6.20, 10.1 ms; one group of 8192
-// rows, d = 2048, f = 1024, which leaves CUs idle: 259, 175, 148 us.  (The kernel before, 256 x 256 tiles of four
-// wavefronts with masked 32-row windows: 516 us, 7.04 ms, 356 us; adding to the gradients 1175 us and 9.51 ms against
-// 507 us and 6.49 ms now, that are requested a pass ahead.)
+// other: the better shape up to about 1500 rows per group.  16 groups of 512 rows, d = 4096, f = 1536: 418 us (256 x 256),
+// 363 (128 x 256), 569 (64 x 128); 32 groups of 2500 rows, d = 7168, f = 2048: 5.73, 6.03, 10.0 ms; one group of 8192
+// rows, d = 2048, f = 1024, which leaves CUs idle: 291, 190, 137 us (the costs below were fitted with MFMAs 32x32x16, where these were 413, 383,
+// 558; 5.97, 6.20, 10.1; 259, 175, 148).  (256 x 256 tiles of four
+// wavefronts with masked 32-row windows, before all of these: 516 us, 7.04 ms, 356 us; adding to the gradients 1175 us and 9.51 ms against
+// 501 us and 6.30 ms now, that are requested a pass ahead.)
 struct WgradShape {
   int bm, bn, per_cu;
   double start, round[2];   // us; us per 1000 rows

@@ -114,7 +114,7 @@ __device__ __forceinline__ void panel_tile(
   static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
   if (blocks32 >= MI) {
     Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
-  } else if (blocks32 == 1) {
+  } else if (MI > 1 && blocks32 == 1) {
     Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
   } else {
     Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);   // its loads and barriers only
@@ -287,6 +287,7 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   const RowTile t = tiles.find(b0 + in_band % height, g_begin);
   const Tile tile{t.g, t.row0, t.rows, in_band / height};
   if constexpr (QUARTERS) {
+    static_assert(PanelGemm<WR, MI / 2, NJ / 2, 4, 6, false, B_TR>::LDS_BYTES <= Core::LDS_BYTES, "a quarter's rings fit the tile's");
     if (quarter >= 0) {   // row half and column half
       const int below = quarter / 2 * (Core::BM / 2);
       const Tile q{tile.g, tile.row0 + below, min(tile.rows - below, Core::BM / 2), tile.nt * 2 + quarter % 2};
@@ -300,11 +301,14 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
 
 // Tile shape by estimated time.  A launch of B tiles runs B / (256 per_cu) full rounds and a rest; a round with one
 // (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
-// GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168); picking by it is 2 % slower on average than the
-// best of the three each time, and 1.37x faster than 256 x 256 tiles of four wavefronts for every shape.  B is estimated from
+// GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168), timed with MFMAs 32x32x16 and with every rest of 256 x 256 tiles a round of
+// its own; picking by it was 2 % slower on average than the best of the three each time.  With the present loop it is 3.4 % slower
+// (gate/up) and 3.8 % (down) over 60 shapes drawn alike, at most 1.42x.  Part of that are rests that now run as quarters: one round and a
+// few tiles, which the estimate sends to 128 x 256, would be faster in 256 x 256 (gate/up, d = 2048, f = 1024: 264 tiles 69.0 us against 65.6, 320 tiles
+// 74.5 against 73.1; d = 6144: 184.6 against 172.5 and 204.6 against 187.9).  B is estimated from
 // the row capacity, which was the number of rows in those 60: a group of rows ends half a tile early on average, empty ones
 // included.  Where the capacity is a multiple of the rows the estimate is of another launch (64 experts, 16 groups, 2110 of
-// 6018 rows, d = 2048, f = 1408: gate/up 48 us in 128 x 256 tiles, down 29 us in 256 x 256).  A shape whose rows do not fit the loads' 32-bit
+// 6018 rows, d = 2048, f = 1408: gate/up 46 us in 128 x 256 tiles, down 30 us in 256 x 256).  A shape whose rows do not fit the loads' 32-bit
 // offsets (256 rows of more than 8.3 million elements) is not taken; the entry points see to it that 64 rows do.
 struct Shape {
   int bm, bn, per_cu;
