@@ -337,7 +337,8 @@ int32_t feplb_route_topk_backward(const int32_t* topk_ids, const float* topk_w, 
  * units, while the static experts run.  This enqueues hipMemcpyAsync(slot, src,
  * bytes) on `side_stream` and, if `done` is not NULL, records it there; the
  * compute stream then waits with feplb_stream_wait.  src may be device memory
- * or pinned host memory.
+ * or pinned host memory; a copy within one GPU's memory is made by a kernel of the runtime, on its
+ * compute units.
  */
 int32_t feplb_stage_weights(void* slot, const void* src, size_t bytes,
                             void* side_stream, void* done_event);

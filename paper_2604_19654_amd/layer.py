@@ -191,7 +191,7 @@ class RankLayer:
             raise B.FeplbError("more replicas than staging slots")
         groups = [(e, 0, B.ORD_MAX) for e in static] + [(e, lo, lo + rows) for (e, _src, _dst, rows, lo) in moves]
         G = len(groups)
-        # replicas: weights by the copy engine on the side stream, their rows appended to the
+        # replicas: weights by copies on the side stream, their rows appended to the
         # permutation, both behind the static FFN (the append shares the permute workspace and
         # buffers with the static call, hence the wait for it)
         if moves:
@@ -223,7 +223,7 @@ class RankLayer:
                            mark=False, overlap=True):
         """The rank runs its own experts as the static range and `slots[this_rank]`
         replicas as the dynamic range.  remote_sources[e] is one contiguous bf16
-        tensor [gate | up | down] of expert e living where the copy engine reads it
+        tensor [gate | up | down] of expert e living where the copies read it
         (another device buffer or pinned host memory).  Returns (Y, info)."""
         b = self.buf
         main = torch.cuda.current_stream()
@@ -245,7 +245,8 @@ class RankLayer:
         # the permute kernels go first: the GPU has been idle since the router finished
         self._permute(groups, X)
         self._mark("permuted", mark)
-        # weights of the replicas: copy engine, side stream, off the compute units.  The side
+        # weights of the replicas: copies on the side stream.  A copy engine makes them where the source is pinned host
+        # memory or another GPU's; from this GPU's own memory a blit kernel does, which shares the compute units.  The side
         # stream waits for what is queued on the main stream (the previous step's readers of the
         # slots; the few permute kernels above ride along).
         side = self.side_stream if overlap else main
