@@ -15,6 +15,7 @@ cpu_baseline = the CPU oracle timed on a bounded sample of the same workload, wi
 other_workloads = the four other workloads as short forward-only runs (skipped with --only)
 """
 import argparse
+import gc
 import json
 import os
 import sys
@@ -66,6 +67,9 @@ def time_workload(name, steps, warmup, source_kind="device", fused_gather=True, 
     from paper_2604_19654_amd import binding as B
     names = list(layer.timeline)
     timelines = [{n: B.HipEvent() for n in names} for _ in range(steps)]
+    # A full collection of Python's garbage takes 40 ms with torch loaded, and what the set-up leaves behind makes one
+    # due about here: it is made now and not in the middle of a step.  What the steps leave behind is collected as ever.
+    gc.collect()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for tl in timelines:
@@ -108,6 +112,7 @@ def time_workload(name, steps, warmup, source_kind="device", fused_gather=True, 
         workload=name, T=T, R=R, d=d, f=f, E=wl.E, k=k, groups=len(p.groups), rank=p.rank,
         ms_per_step=wall_ms, ms=ms,
         step_events_ms_median=float(np.median(per_step)), step_events_ms_min=float(np.min(per_step)),
+        step_events_ms_max=float(np.max(per_step)),
         ffn_tflops_step=ffn_flops / (wall_ms * 1e-3) / 1e12,
         ffn_tflops_kernels=ffn_flops / ((ms["gate_up"] + ms["down"]) * 1e-3) / 1e12,
         gate_up_tflops=4.0 * d * f * R / (ms["gate_up"] * 1e-3) / 1e12,

@@ -48,6 +48,35 @@ def test_measured_traffic_belongs_to_every_source_of_the_gemms(tmp_path):
         assert bench._traffic_sources_sha256(str(copy)) != now, name
 
 
+def test_garbage_of_the_setup_is_not_collected_in_the_timed_steps(monkeypatch):
+    # a full collection takes 40 ms with torch loaded; made due by the set-up, it fell into the timed steps of some runs
+    import gc
+    import types
+    import torch
+    import bench
+    from paper_2604_19654_amd import binding, runner
+    due = []
+
+    class Clocked(Exception):
+        pass
+
+    def step(p, mark, early_static):
+        p.layer.timeline = dict(p.layer.timeline, start=None)
+        due.append(gc.get_count()[1:])
+        if len(due) == 3:      # two warm-up steps, the first timed one
+            raise Clocked
+
+    def prepare(*a, **k):
+        return types.SimpleNamespace(wl=None, layer=types.SimpleNamespace(timeline={}))
+    monkeypatch.setattr(runner, "prepare", prepare)
+    monkeypatch.setattr(runner, "step", step)
+    monkeypatch.setattr(binding, "HipEvent", lambda: [[] for _ in range(2000)])     # garbage: more than a young collection's worth
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a: None)
+    with pytest.raises(Clocked):
+        bench.time_workload("C1", 20, 2)
+    assert due[2] == (0, 0), "collections were due when the clock started"
+
+
 @pytest.mark.gpu
 def test_one_json_line_with_the_agreed_keys():
     r = run_bench("--workload", "C1", "--steps", "3", "--warmup", "1", "--cpu-tokens", "256")
