@@ -31,7 +31,7 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 # same counters read for the row-copy and combine kernels of the same run (sizes known); see the named profile.
 # The figures belong to the kernel source they were measured on: bench.py reports them only while the files that
 # decide what the GEMMs move still have that content (one sha256 over all of them), and null otherwise.
-TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "panel_gemm.h", "gemm_device.h", "common.h")
+TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "ffn_down.hip", "tall_gemm.h", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
            "sources_sha256": "95561c25c6cbc4a53e31698ff33f16bf70220bbb1fd3e3ea2a03a804bf198c76",

@@ -274,7 +274,9 @@ int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* offsets,
 /* Height in rows (64, 128 or 256) of the tiles that a grouped GEMM of these entry points is launched in,
  * picked on the host from the row capacity and the sizes alone; results do not depend on it.  A launch in tiles of
  * 256 rows x 256 columns may compute some as quarters of 128 x 128: the tiles beyond whole rounds of 256 (all of them where there
- * are fewer), if they are at most 64, which the rows on the device decide.  (The weight gradients' launches do not.)  For
+ * are fewer), if they are at most 64, which the rows on the device decide.  (The weight gradients' launches do not.)  In the place of
+ * tiles of 128 and 256 rows some launches take tall tiles, whose height of 64 to 320 rows is picked on the device from
+ * the groups' rows, left-over ones as halves of their columns or as quarters.  For
  * tests that want every shape covered and for reading profiles.  R_cap, n_groups (g_end - g_begin),
  * d, f as in the call (GATE_UP: without row_src; DH, DXP: with the weights given); 0 for arguments
  * out of range.  Host-only. */

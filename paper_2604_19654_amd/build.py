@@ -5,12 +5,14 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfeplb.so")
-SOURCES = ["host.cpp", "plan.cpp", "route.hip", "permute.hip", "ffn.hip", "ffn_gemm.hip", "ffn_backward.hip", "combine.hip", "layer_backward.hip"]
+SOURCES = ["host.cpp", "plan.cpp", "route.hip", "permute.hip", "ffn.hip", "ffn_gemm.hip", "ffn_gate_up_train.hip",
+           "ffn_down.hip", "ffn_dxp.hip", "ffn_dh.hip", "ffn_backward.hip", "combine.hip", "layer_backward.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -27,7 +29,7 @@ def hipcc() -> str:
     return exe
 
 
-def build(verbose: bool = True, jobs: int = 6) -> str:
+def build(verbose: bool = True, jobs: int = 8) -> str:
     """Compile every source for gfx950 and link the shared library. Always recompiles."""
     obj_dir = os.path.join(HERE, "_build")
     os.makedirs(obj_dir, exist_ok=True)
@@ -39,16 +41,18 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
         cmd = [hipcc(), *HIPCC_FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        while sum(p.poll() is None for _, p in procs) >= jobs:
-            for _, p in procs:
+        log = tempfile.TemporaryFile("w+")   # not a pipe: a compiler with much to say would wait for it to be read
+        procs.append((src, log, subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT)))
+        while sum(p.poll() is None for *_, p in procs) >= jobs:
+            for *_, p in procs:
                 if p.poll() is None:
                     p.wait()
                     break
     failed = False
-    for src, p in procs:
-        out, _ = p.communicate()
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip())
+    for src, log, p in procs:
+        p.wait()
+        log.seek(0)
+        out = "\n".join(l for l in log.read().splitlines() if "packed-fp32-ops" not in l and l.strip())
         if p.returncode != 0:
             failed = True
             print(f"--- {src} FAILED\n{out}", file=sys.stderr)

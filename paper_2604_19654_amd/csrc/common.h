@@ -33,7 +33,9 @@ struct GroupedGemm {
   int ld_aux;
 };
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s);
+hipError_t launch_gate_up_keeping(const GroupedGemm& a, hipStream_t s);             // with aux
 hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s);
+hipError_t launch_plain_gemm_nk(const GroupedGemm& a, bool out_bf16, hipStream_t s);   // with w_nk
 hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s);
 int gemm_tile_rows(const GroupedGemm& a, bool gate_up);   // rows of a tile of the shape that these pick
 

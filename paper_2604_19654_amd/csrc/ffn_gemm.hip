@@ -5,7 +5,7 @@
 //   MODE 2  dswiglu:  dH = a_r W[g], times the derivatives in `aux`: da = dH p | db = dH q, bf16, written over them
 // One launch covers a whole range of ragged groups; a workgroup finds its tile from offsets[] (device memory), so the
 // host never needs the number of rows: the grid covers an upper bound and surplus workgroups leave at once.
-// panel_gemm.h holds the main loop and the mapping of workgroups to tiles.
+// panel_gemm.h holds the main loop and the mapping of workgroups to tiles, tall_gemm.h the loop for tall tiles.
 //
 // Three tile shapes (rows x weight columns; for gate/up half of the columns are gate, half the matching up columns):
 //   256 x 256, 8 wavefronts, one workgroup per CU: the least operand traffic per flop, for shapes with several rounds
@@ -14,6 +14,8 @@
 //   128 x 256, 4 wavefronts, two workgroups per CU: one's prologue and epilogue hide behind the other's loop and half
 //              the rows are lost to rounding a group up, but operand traffic in LDS is 1.1x its bandwidth at full MFMA rate.
 //   64 x 128,  4 wavefronts, two workgroups per CU with deep rings: for launches that would leave most CUs idle otherwise.
+// and tall tiles, up to 320 x 256, 4 wavefronts, one workgroup per CU, whose height every launch finds from its groups' rows: for the
+// plain products and for gate/up with many rounds of tiles, and wherever 128 x 256 tiles would be more than one to a CU (use_tall below).
 // 256 weight columns x 64 k of LDS-DMA loads in flight per CU also stream weights well: 16 groups of 8 rows, d = 4096,
 // f = 1536 (400 MB of gate/up weights): 109 -> 77 us, 5.2 TB/s.
 // The weights are row-major [K,N] (B_TR: the MFMA operand needs 8 consecutive k of one column, which the transposing LDS
@@ -21,7 +23,7 @@
 // weights may be two matrices that share k: w0 holds the first k_split of it, w1 the rest (dXp = [da | db] [Wg | Wu]^T).
 // The result's bits do not depend on the shape: every element is one chain of MFMAs 16x16x32 over ascending k.
 #include "common.h"
-#include "panel_gemm.h"
+#include "tall_gemm.h"
 
 namespace {
 using namespace feplb::dev;
@@ -32,17 +34,28 @@ using namespace feplb::dev;
 // such rounds, and halves of 128 x 256 take 0.8 of a whole tile's time.  T = 8192, 20396 rows in 8 groups, d = 4096, f = 1536, whose
 // gate/up is 4 rounds and 8 tiles: 766 -> 728 us a layer step; 298 drawn forward steps 1.01x on average, up to 1.75x.
 constexpr int QUARTERS_MAX = 64;
+constexpr int HALVES_MAX = 128;   // tall tiles: from 65 left-over ones on halves of 128 columns, 0.56 of a whole tile's time
 
 struct Tile {
   int g, row0, rows, nt;   // group, first row, number of rows, column
 };
 
-// one tile of the output
-template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB>
+// a tall tile's main loop, `blocks` <= ME row blocks per wave
+template <class Core, int ME, class IA, class IB, class Acc>
+__device__ __forceinline__ void run_blocks(int blocks, char* lds, int U, const typename Core::FragA& fa, const typename Core::FragB& fb, IA& issue_a,
+                                           IB& issue_b, Acc& acc) {
+  if constexpr (ME > 1) {
+    if (blocks < ME) return run_blocks<Core, ME - 1>(blocks, lds, U, fa, fb, issue_a, issue_b, acc);
+  }
+  Core::template run<ME>(lds, U, fa, fb, issue_a, issue_b, acc);
+}
+
+// one tile of the output, by panel_gemm.h's loop or (TALL, two wave rows) tall_gemm.h's
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR, int WR, int MI, int NJ, int DA, int DB, bool TALL = false>
 __device__ __forceinline__ void panel_tile(
     char* lds, const Tile& tile, const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k, int K,
     const WeightTable& wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
-  using Core = PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>;
+  using Core = std::conditional_t<TALL, TallGemm<MI, NJ, DA, DB, B_TR>, PanelGemm<WR, MI, NJ, DA, DB, false, B_TR>>;
   const int g = tile.g, row0 = tile.row0, rows = tile.rows, nt = tile.nt;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
@@ -50,11 +63,13 @@ __device__ __forceinline__ void panel_tile(
   const int KT = K / 64;
 
   // ---- loads
+  // a tall tile asks for the rows it has only: its loads go to the waves in turn
+  auto a_load = [&](int i) { return TALL ? i * 2 * WR + wave : wave * Core::LA + i; };
   uint32_t a_goff[Core::LA];
   const bool gather = MODE == 0 && row_src != nullptr;
 #pragma unroll
   for (int i = 0; i < Core::LA; ++i) {
-    const int li = wave * Core::LA + i;
+    const int li = a_load(i);
     int row = min(Core::rows_row(li, lane), rows - 1);
     if (gather) row = min(max(row_src[row0 + row] / src_k, 0), n_src_rows - 1);
     a_goff[i] = ((uint32_t)row * (uint32_t)lda + Core::rows_chunk(li, lane) * 8) * 2;
@@ -62,9 +77,9 @@ __device__ __forceinline__ void panel_tile(
   const char* a_ptr = wave_uniform(gather ? A : A + (size_t)row0 * lda);
   // the requests come in order, so each operand keeps one running scalar pointer; it stays on the last tile for
   // requests past the end
-  auto issue_a = [&](uint32_t stage, int t, int i) {
-    load_to_lds_16(a_ptr, a_goff[i], stage + (wave * Core::LA + i) * 1024);
-    if (i == Core::LA - 1) a_ptr += t < KT - 1 ? 128 : 0;
+  auto issue_a = [&](uint32_t stage, int t, int i, int la = Core::LA) {
+    load_to_lds_16(a_ptr, a_goff[i], stage + a_load(i) * 1024);
+    if (i == la - 1) a_ptr += t < KT - 1 ? 128 : 0;
   };
   uint32_t b_goff[Core::LB];
   const char *b_ptr0, *b_ptr1;
@@ -104,21 +119,25 @@ __device__ __forceinline__ void panel_tile(
   fa.init(wm * 32, lane);
   fb.init(wn * 32 * NJ, lane);
   f32x4 acc[2][2 * MI][2 * NJ];
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-    for (int i = 0; i < 2 * MI; ++i)
-#pragma unroll
-      for (int j = 0; j < 2 * NJ; ++j) acc[hf][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int blocks32 = (rows + 32 * WR - 1 - wm * 32) / (32 * WR);   // row blocks of this wave that hold rows
-  static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
-  if (blocks32 >= MI) {
-    Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
-  } else if (MI > 1 && blocks32 == 1) {
-    Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
+  if constexpr (TALL) {
+    run_blocks<Core, MI>((rows + 32 * WR - 1) / (32 * WR), lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
   } else {
-    Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);   // its loads and barriers only
-    return;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * NJ; ++j) acc[hf][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int blocks32 = (rows + 32 * WR - 1 - wm * 32) / (32 * WR);   // row blocks of this wave that hold rows
+    static_assert(MI <= 2, "loop variants for 0, 1 and 2 row blocks");
+    if (blocks32 >= MI) {
+      Core::template run<MI>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
+    } else if (MI > 1 && blocks32 == 1) {
+      Core::template run<1>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);
+    } else {
+      Core::template run<0>(lds, 2 * KT, fa, fb, issue_a, issue_b, acc);   // its loads and barriers only
+      return;
+    }
   }
 
   // ---- epilogue.  The MFMAs computed (X W)^T per 16 x 16 block: a lane holds ONE row, lane % 16, and FOUR consecutive
@@ -299,6 +318,78 @@ __global__ __launch_bounds__(128 * WR, OCC) void panel_gemm_kernel(
   panel_tile<MODE, OUT_BF16, SAVE, B_TR, WR, MI, NJ, DA, DB>(lds, tile, A, lda, row_src, n_src_rows, src_k, K, wt, ldw, k_split, out, ldo, aux, ld_aux);
 }
 
+// Estimated time of a round of large tiles of b row blocks of 64: whole[0] + whole[1] b, with half of the columns half[0] + half[1] b
+struct Heights {
+  int lo, hi;              // b may be lo .. hi
+  float whole[2], half[2];
+};
+
+// The height of the large tiles by estimated time, from the groups' rows: whole rounds of tiles of the average height, and one of the
+// tallest if tiles are left over.
+__device__ __forceinline__ int pick_height(const TallTiles& tiles, const Heights& h, int n_tiles_n) {
+  const float blocks = (float)tiles.count(1);
+  int best = h.hi;
+  float best_us = 0.f;
+#pragma unroll
+  for (int b = 5; b >= 2; --b) {
+    if (b > h.hi || b < h.lo) continue;
+    const int row_tiles = tiles.count(b), n = row_tiles * n_tiles_n, rest = n % 256;
+    const float mean = blocks * __builtin_amdgcn_rcpf((float)row_tiles);
+    const float tail = rest == 0 ? 0.f : rest <= QUARTERS_MAX ? h.half[0] + h.half[1] * (float)((b + 1) / 2)
+                       : rest <= HALVES_MAX ? h.half[0] + h.half[1] * (float)b : h.whole[0] + h.whole[1] * (float)b;
+    const float us = (float)(n / 256) * (h.whole[0] + h.whole[1] * mean) + tail;
+    if (b == h.hi || us < best_us) {
+      best = b;
+      best_us = us;
+    }
+  }
+  return __builtin_amdgcn_readfirstlane(best);
+}
+
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
+__global__ __launch_bounds__(256, 1) void tall_gemm_kernel(
+    const uint16_t* __restrict__ A, int lda, const int* __restrict__ row_src, int n_src_rows, int src_k,
+    const int* __restrict__ offsets, int g_begin, int ng, int R_cap, int K, int n_tiles_n, int band, Heights heights,
+    WeightTable wt, int ldw, int k_split, void* __restrict__ out, int ldo, void* aux, int ld_aux) {
+  using Core = TallGemm<5, 2, 2, 4, B_TR>;
+  using Half = TallGemm<5, 1, 2, 4, B_TR>;
+  static_assert(Half::LDS_BYTES <= Core::LDS_BYTES, "a half's rings fit the tile's");
+  __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
+
+  // ---- block -> tile: bands of `band` row tiles, walked column by column; a left-over tile has several blocks
+  TallTiles tiles;
+  tiles.load(offsets, g_begin, ng, R_cap);
+  tiles.split(pick_height(tiles, heights, n_tiles_n));
+  const int total = tiles.total * n_tiles_n;
+  const int rest = total % 256, pieces = rest <= QUARTERS_MAX ? 4 : 2;
+  const int whole = rest <= HALVES_MAX ? total - rest : total;
+  int idx = tile_of_block<32>(blockIdx.x, whole + pieces * (total - whole));
+  if (idx < 0) return;
+  const int piece = idx < whole ? -1 : (idx - whole) % pieces;
+  if (piece >= 0) idx = whole + (idx - whole) / pieces;
+  const int b0 = idx / (band * n_tiles_n) * band;
+  const int in_band = idx - b0 * n_tiles_n;
+  const int height = min(band, tiles.total - b0);
+  const RowTile t = tiles.find(b0 + in_band % height, g_begin);
+  Tile tile{t.g, t.row0, t.rows, in_band / height};
+  if (piece >= 0) {
+    tile.nt = tile.nt * 2 + piece % 2;
+    if (pieces == 4) {
+      const int upper = (t.rows + 127) / 128 * 64;
+      if (piece / 2) {
+        tile.row0 += upper;
+        tile.rows -= upper;
+        if (tile.rows <= 0) return;
+      } else {
+        tile.rows = min(tile.rows, upper);
+      }
+    }
+    panel_tile<MODE, OUT_BF16, SAVE, B_TR, 2, 5, 1, 2, 4, true>(lds, tile, A, lda, row_src, n_src_rows, src_k, K, wt, ldw, k_split, out, ldo, aux, ld_aux);
+    return;
+  }
+  panel_tile<MODE, OUT_BF16, SAVE, B_TR, 2, 5, 2, 2, 4, true>(lds, tile, A, lda, row_src, n_src_rows, src_k, K, wt, ldw, k_split, out, ldo, aux, ld_aux);
+}
+
 // Tile shape by estimated time.  A launch of B tiles runs B / (256 per_cu) full rounds and a rest; a round with one
 // (two) workgroups on a CU takes `start` plus k times the measured cost per k.  The costs are a fit to 60 shapes x 3
 // GEMMs (1 to 128 groups of 8 to 8000 rows, d and f from 256 to 7168), timed with MFMAs 32x32x16 and with every rest of 256 x 256 tiles a round of
@@ -349,8 +440,46 @@ hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
 }
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
+hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
+  using Core = TallGemm<5, 2, 2, 4, B_TR>;
+  const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
+  const auto most = [&](int b) { return ((long)a.R_cap / (64 * b) + a.ng) * n_tiles_n; };   // tiles of up to b row blocks
+  Heights h{5, 5, {0.f, 0.f}, {0.f, 0.f}};
+  if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see pick_shape
+  while (h.lo > 2 && most(h.lo - 1) - most(h.hi) <= 512) --h.lo;              // at most two surplus workgroups per CU
+  // us: a round starts in 5, multiplies 64 rows x 256 columns in 4.8 per 1000 k, loads the weights in 1.5 (from the caches) to 3.5, and
+  // moves its results at about 6 TB/s; with half of the columns 2.0 and 4
+  const float k = 1e-3f * a.K, out = 64.f * 256 * 256e-6f / 6 * (MODE == 0 ? (SAVE ? 3 : 1) : OUT_BF16 ? 2 : 4);
+  h.whole[0] = 5.f + (MODE == 0 ? 3.5f : 2.f) * k;
+  h.whole[1] = out + 4.8f * k;
+  h.half[0] = 5.f + 4.f * k;
+  h.half[1] = 0.5f * out + 2.f * k;
+  const long blocks = most(h.lo) + (3 * QUARTERS_MAX > HALVES_MAX ? 3 * QUARTERS_MAX : HALVES_MAX);
+  hipLaunchKernelGGL((tall_gemm_kernel<MODE, OUT_BF16, SAVE, B_TR>), dim3(blocks_for_tiles(blocks)), dim3(256), 0, s, (const uint16_t*)a.A, a.lda,
+                     a.row_src, a.n_src_rows, a.src_k, a.offsets, a.g_begin, a.ng, a.R_cap, a.K, n_tiles_n, 8, h, *a.weights, a.ldw, a.k_split, a.out,
+                     a.ldo, a.aux, a.ld_aux);
+  return hipGetLastError();
+}
+
+// Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps (us, before and in tall tiles):
+//   in the place of 256 x 256: gate/up 93580 rows, d = 6144, f = 2048 3135, 3112; 80387 rows, d = 7168, f = 2048 3295, 3182 (keeping the
+//   derivatives 3374, 3285); 8228 rows in 16 groups, d = 4096, f = 1536 209, 223; 20318 rows in 6 groups 390, 407: from eight rounds of tiles on.
+//   Plain, 8228 rows, K = 1536 143, 125; K = 3072 211, 189; 20318 rows, K = 1536 262, 251; 6390 rows in 8 groups, K = 768 38, 42: K >= 1024;
+//   in the place of 128 x 256 where those would be more than one to a CU: gate/up, K = 6144 204, 140; capacity for 6018 rows of which 2110 exist,
+//   K = 2048 45, 41 (and such a launch finds its heights from the rows it has, not from the capacity).
+bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape) {
+  if (mode == 2 || shape == 2 || (mode == 1 && a.K < 1024)) return false;
+  const double tiles = ((double)a.R_cap / SHAPES[shape].bm + 0.5 * a.ng) * (weight_cols / 256);
+  return tiles > (shape == 1 ? 256. : mode == 0 ? 8 * 256. : 0.);
+}
+
+template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
 hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
-  switch (pick_shape(a, MODE == 0 ? 2 * a.N : a.N)) {
+  const int weight_cols = MODE == 0 ? 2 * a.N : a.N, shape = pick_shape(a, weight_cols);
+  if constexpr (MODE != 2) {
+    if (use_tall(a, MODE, weight_cols, shape)) return launch_tall<MODE, OUT_BF16, SAVE, B_TR>(a, s);
+  }
+  switch (shape) {
     case 0: return launch<MODE, OUT_BF16, SAVE, B_TR, 4, 2, 2, 3, 3, 2>(a, s);
     case 1: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 2, 2, 2, 3, 2>(a, s);
     default: return launch<MODE, OUT_BF16, SAVE, B_TR, 2, 1, 1, 3, 6, 2>(a, s);
@@ -361,16 +490,27 @@ hipError_t launch_shape(const feplb::GroupedGemm& a, hipStream_t s) {
 
 namespace feplb {
 
+// compiled in parts, for the sake of the build's time
+#if !defined(FEPLB_GEMM_PART)
+int gemm_tile_rows(const GroupedGemm& a, bool gate_up) { return SHAPES[pick_shape(a, gate_up ? 2 * a.N : a.N)].bm; }
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s) {
-  return a.aux ? launch_shape<0, true, true, true>(a, s) : launch_shape<0, true, false, true>(a, s);
+  return a.aux ? launch_gate_up_keeping(a, s) : launch_shape<0, true, false, true>(a, s);
 }
+#elif FEPLB_GEMM_PART == 1
+hipError_t launch_gate_up_keeping(const GroupedGemm& a, hipStream_t s) { return launch_shape<0, true, true, true>(a, s); }
+#elif FEPLB_GEMM_PART == 2
 hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s) {
-  if (a.w_nk) return out_bf16 ? launch_shape<1, true, false, false>(a, s) : launch_shape<1, false, false, false>(a, s);
+  if (a.w_nk) return launch_plain_gemm_nk(a, out_bf16, s);
   return out_bf16 ? launch_shape<1, true, false, true>(a, s) : launch_shape<1, false, false, true>(a, s);
 }
+#elif FEPLB_GEMM_PART == 3
+hipError_t launch_plain_gemm_nk(const GroupedGemm& a, bool out_bf16, hipStream_t s) {
+  return out_bf16 ? launch_shape<1, true, false, false>(a, s) : launch_shape<1, false, false, false>(a, s);
+}
+#elif FEPLB_GEMM_PART == 4
 hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s) {
   return a.w_nk ? launch_shape<2, true, false, false>(a, s) : launch_shape<2, true, false, true>(a, s);
 }
-int gemm_tile_rows(const GroupedGemm& a, bool gate_up) { return SHAPES[pick_shape(a, gate_up ? 2 * a.N : a.N)].bm; }
+#endif
 
 }  // namespace feplb

@@ -462,6 +462,46 @@ def test_grouped_ffn_leftover_tiles_in_quarters(row_tiles):
         lo += n
 
 
+@pytest.mark.parametrize("sizes", [[2], [84, 128, 70, 606, 3, 4, 240], [64, 384, 512, 9, 15, 65, 66], [195, 3, 213, 257, 15, 314, 65, 490, 449],
+                                   [257, 37, 111, 56, 65, 261, 321, 641, 623, 124], [393, 66, 257, 128, 63, 128, 334, 31, 138, 450, 65, 646],
+                                   [69, 575, 65, 249, 298, 413, 690, 41, 82, 64, 418, 146, 585, 128, 256, 384, 30, 7, 287, 121, 193, 138],
+                                   [355, 24, 449, 383, 321, 321, 384, 319, 43, 210, 63, 129, 380, 255, 128, 384, 577, 13, 177, 13, 348, 192],
+                                   [448, 16, 513, 127, 127, 641, 63, 193, 64, 703, 321, 64, 64, 382, 192, 676, 448, 61, 19, 576, 105]])
+def test_grouped_ffn_tall_tiles_of_every_height(sizes):
+    # Tall tiles: the height (up to 2 to 5 blocks of 64 rows) comes from the groups' rows on the device, and left-over tiles run whole, as halves
+    # or as quarters.  These groups take heights 2 to 5 and all three, in less than a round and in more, with rows at the edges of the
+    # blocks, at two capacities that allow different heights.  A group alone, in a buffer of its own, runs in tiles of 64 or 128 rows;
+    # every element is the same chain of MFMAs, so the bytes must be equal.
+    d, f, G, R, B = 2048, 1024, len(sizes), sum(sizes), fe.binding
+    say(f"ffn tall tiles sizes={sizes}")
+    gen = torch.Generator(device=DEV).manual_seed(R)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)   # noqa: E731
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    off = torch.from_numpy(offsets).to(DEV)
+    X, W = rnd(R, d), [[0.02 * rnd(*sh) for _ in range(3)] * (G // 3 + 1) for sh in ((d, f), (d, f), (f, d))]
+    H, Yp, AB = torch.zeros((R, f), dtype=torch.bfloat16, device=DEV), torch.zeros((R, d), device=DEV), torch.zeros((R, 2 * f), dtype=torch.bfloat16, device=DEV)
+    dXp = torch.zeros((R, d), device=DEV)
+    for g, n in enumerate(sizes):
+        assert all(B.feplb_grouped_ffn_tile_rows(gemm, n, 1, d, f) <= 128 for gemm in (B.GEMM_GATE_UP, B.GEMM_DOWN, B.GEMM_DXP))
+        rows, one = slice(offsets[g], offsets[g + 1]), torch.tensor([0, n], dtype=torch.int32, device=DEV)
+        ws = [[w[g]] for w in W]
+        B.feplb_grouped_ffn(X[rows], one, 0, 1, d, f, *ws, H[rows], Yp[rows], AB=AB[rows])
+        B.feplb_grouped_ffn_backward(None, one, 0, 1, d, f, *ws, H[rows], AB[rows].clone(), X[rows], dXp[rows], *[[None]] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
+    for cap in (8000, 16000):
+        Xp = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        Xp[:R] = X
+        for dtype in (torch.float32, torch.bfloat16):
+            out = [torch.full((cap, c), 512.0, dtype=t, device=DEV) for c, t in ((f, torch.bfloat16), (2 * f, torch.bfloat16), (d, dtype), (d, dtype))]
+            B.feplb_grouped_ffn(Xp, off, 0, G, d, f, *W, out[0], out[2], AB=out[1] if dtype == torch.float32 else None)
+            assert dtype != torch.float32 or torch.equal(out[1][:R], AB)
+            out[1][:R] = AB
+            dAB = out[1].clone()
+            B.feplb_grouped_ffn_backward(None, off, 0, G, d, f, *W, out[0], dAB, Xp, out[3], *[[None] * G] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
+            torch.cuda.synchronize()
+            for got, want in zip(out, (H, AB, Yp, dXp)):
+                assert torch.equal(got[:R], want.to(got.dtype)) and (got[R:] == 512.0).all()
+
+
 def test_grouped_ffn_gathering_rows_equals_reading_the_permuted_copy():
     # row_src given: row r of the input is X[row_src[r] // k]; the bytes must equal a run on the
     # materialised copy (the same MFMAs on the same operands)
