@@ -463,14 +463,19 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
 
 // Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps (us, before and in tall tiles):
 //   in the place of 256 x 256: gate/up 93580 rows, d = 6144, f = 2048 3135, 3112; 80387 rows, d = 7168, f = 2048 3295, 3182 (keeping the
-//   derivatives 3374, 3285); 8228 rows in 16 groups, d = 4096, f = 1536 209, 223; 20318 rows in 6 groups 390, 407: from eight rounds of tiles on.
-//   Plain, 8228 rows, K = 1536 143, 125; K = 3072 211, 189; 20318 rows, K = 1536 262, 251; 6390 rows in 8 groups, K = 768 38, 42: K >= 1024;
+//   derivatives 3374, 3285); 8228 rows in 16 groups, d = 4096, f = 1536 209, 223; 20318 rows in 6 groups 390, 407;
+//   93430 rows in 8 groups, d = 1536, f = 1024 3 % of the step lost: from eight rounds of tiles and K = 6144 on.
+//   Plain, 8228 rows, K = 1536 143, 125; K = 3072 211, 189; 20318 rows, K = 1536 262, 251; 2110 rows, K = 1408 29, 23; 6390 rows in 8 groups, K = 768
+//   38, 42; some hundred rows, K = 1024 1 % of the step lost, and with one column of tiles too; 93430 rows, K = 1024 3 % of the step gained: K >= 1280 and
+//   128 tiles, or K >= 1024 and four rounds;
 //   in the place of 128 x 256 where those would be more than one to a CU: gate/up, K = 6144 204, 140; capacity for 6018 rows of which 2110 exist,
-//   K = 2048 45, 41 (and such a launch finds its heights from the rows it has, not from the capacity).
+//   K = 2048 45, 41 (and such a launch finds its heights from the rows it has, not from the capacity); 4567 rows, K = 512 7 % of the step lost: K >= 2048.
 bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape) {
-  if (mode == 2 || shape == 2 || (mode == 1 && a.K < 1024)) return false;
   const double tiles = ((double)a.R_cap / SHAPES[shape].bm + 0.5 * a.ng) * (weight_cols / 256);
-  return tiles > (shape == 1 ? 256. : mode == 0 ? 8 * 256. : 0.);
+  if (mode == 2 || shape == 2) return false;
+  if (shape == 1) return a.K >= 2048 && tiles > 256.;
+  if (mode == 0) return a.K >= 6144 && tiles > 8 * 256.;
+  return a.K >= 1280 ? tiles > 128. : a.K >= 1024 && tiles > 4 * 256.;
 }
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>

@@ -59,6 +59,29 @@ def test_route_topk_empty_and_no_counts():
     assert counts is None and np.array_equal(ids.cpu().numpy(), orc.route_topk(logits.numpy(), 4)[0])
 
 
+@pytest.mark.parametrize("T,E,k", [(1, 4, 4), (1, 32, 1), (255, 8, 2), (257, 8, 4), (1024, 4, 1), (1024, 8, 4), (1024, 16, 2), (1023, 16, 1), (512, 32, 2),
+                                   (513, 32, 2), (512, 32, 1), (256, 32, 4), (1025, 4, 1), (64, 12, 4), (64, 10, 2), (64, 36, 2), (512, 8, 3)])
+def test_route_topk_of_small_batches(T, E, k):
+    # A small batch of few experts is routed and counted by one workgroup, a token per lane; sizes at the edges of that rule, and logits
+    # that the general kernel orders as bits: infinities, masks, values of one sign, ties.  A call without counts runs the
+    # general kernel: the same bytes.
+    say(f"route small T={T} E={E} k={k}")
+    logits = torch.randn((T, E), generator=torch.Generator().manual_seed(T + 7 * E + k))
+    logits[::3, : max(E - k, 1)] = -float("inf")
+    if T > 4:
+        logits[1], logits[2, E // 2:], logits[4] = 0.25, torch.finfo(torch.float32).min, -float("inf")
+        logits[1, ::2] = -0.0
+    logits[0, E - 1] = 3.0
+    x = logits.to(DEV)
+    ids, w, counts = fe.feplb_route_topk(x, k)
+    ids_g, w_g, _ = fe.feplb_route_topk(x, k, want_counts=False)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids_g) and torch.equal(w.view(torch.int32), w_g.view(torch.int32))
+    assert counts.cpu().tolist() == torch.bincount(ids.reshape(-1).long().cpu(), minlength=E).tolist()
+    finite = torch.isfinite(logits).all(dim=1).numpy()
+    assert np.array_equal(ids.cpu().numpy()[finite], orc.route_topk(logits.numpy()[finite], k)[0])
+
+
 # ------------------------------------------------------------------ permute
 def random_ids(T, E, k, seed, skew=0.0):
     rng = np.random.default_rng(seed)
@@ -472,7 +495,7 @@ def test_grouped_ffn_tall_tiles_of_every_height(sizes):
     # or as quarters.  These groups take heights 2 to 5 and all three, in less than a round and in more, with rows at the edges of the
     # blocks, at two capacities that allow different heights.  A group alone, in a buffer of its own, runs in tiles of 64 or 128 rows;
     # every element is the same chain of MFMAs, so the bytes must be equal.
-    d, f, G, R, B = 2048, 1024, len(sizes), sum(sizes), fe.binding
+    d, f, G, R, B = 2048, 1536, len(sizes), sum(sizes), fe.binding
     say(f"ffn tall tiles sizes={sizes}")
     gen = torch.Generator(device=DEV).manual_seed(R)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)   # noqa: E731
