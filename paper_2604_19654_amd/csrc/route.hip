@@ -122,15 +122,15 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
 // Sorted insertion without branches: x enters before the first entry it is strictly greater than,
 // the entries from there on move down one place, the last one drops out.  above[i] = (x > v[i]) is
 // monotone in i because the list is sorted descending.
-template <int K>
-__device__ __forceinline__ void insert_sorted(float (&v)[K], int (&id)[K], float x, int e) {
-  float nv[K];
+template <int K, class V>
+__device__ __forceinline__ void insert_sorted(V (&v)[K], int (&id)[K], V x, int e) {
+  V nv[K];
   int ni[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
     const bool above = x > v[i];
     const bool above_prev = i > 0 ? x > v[i > 0 ? i - 1 : 0] : false;
-    const float shifted_v = above_prev ? v[i > 0 ? i - 1 : 0] : x;
+    const V shifted_v = above_prev ? v[i > 0 ? i - 1 : 0] : x;
     const int shifted_i = above_prev ? id[i > 0 ? i - 1 : 0] : e;
     nv[i] = above ? shifted_v : v[i];
     ni[i] = above ? shifted_i : id[i];
@@ -216,6 +216,57 @@ __global__ __launch_bounds__(LANE_WAVES * 64) void route_topk_lane_kernel(
   }
 }
 
+// A small batch of few experts in one workgroup, a token per lane, which counts in LDS what it routes: one launch instead of two,
+// and no clearing.  The keys order as route_topk_kernel's (any bit pattern is a logit), and the weights are its to the bit.  K = k exactly; E a multiple
+// of 4; logits 16-byte aligned.  Two launches and this one inside a graph, us: T = 512, E = 8, k = 2 4.14, 2.55; T = 32, E = 32, k = 4 4.61, 3.88; and at the
+// line, T E max(k, 2) = 32768, T = 1024, E = 8, k = 4 4.75, 3.98; T = 512, E = 32, k = 1 4.26, 3.73; beyond it T = 1024, E = 16, k = 4 4.99, 5.41;
+// T = 1024, E = 32, k = 1 4.35, 5.51.  (Sub-groups of lanes as in route_topk_kernel: T = 512, E = 8, k = 2 5.25.)
+constexpr int ONE_T = 1024, ONE_E = 32, ONE_WORK = 32768;
+template <int K>
+__global__ __launch_bounds__(ONE_T) void route_count_kernel(const float* __restrict__ logits, int T, int E, int* __restrict__ ids,
+                                                            float* __restrict__ w, int* __restrict__ counts) {
+  __shared__ int hist[4][ONE_E];
+  const int t = threadIdx.x;
+  if (t < 4 * ONE_E) hist[t / ONE_E][t % ONE_E] = 0;
+  uint32_t v[K];
+  int id[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    v[i] = 0u;   // below every key; E >= K fills all entries
+    id[i] = 0;
+  }
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  if (t < T) {
+    const f32x4* row = (const f32x4*)(logits + (long long)t * E);
+#pragma unroll 2
+    for (int c = 0; c < E / 4; ++c) {
+      const f32x4 x = row[c];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t key = orderable(x[i]);
+        insert_sorted<K, uint32_t>(v, id, key > 1u ? key : 1u, 4 * c + i);
+      }
+    }
+  }
+  __syncthreads();
+  if (t < T) {
+    float p[K], sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      p[j] = expf(from_orderable(v[j]) - from_orderable(v[0]));
+      sum += p[j];
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      ids[t * K + j] = id[j];
+      w[t * K + j] = p[j] / sum;
+      atomicAdd(&hist[t % 4][id[j]], 1);
+    }
+  }
+  __syncthreads();
+  if (t < E) counts[t] = hist[0][t] + hist[1][t] + hist[2][t] + hist[3][t];
+}
+
 template <int K>
 void launch_lane(const float* logits, int T, int E, int* ids, float* w, int* counts, hipStream_t s) {
   const int per = LANE_WAVES * 64;
@@ -297,6 +348,14 @@ extern "C" int32_t feplb_route_topk(const float* logits, int32_t T, int32_t E, i
     return FEPLB_OK;
   }
   FEPLB_REQUIRE(logits && topk_ids && topk_w, FEPLB_EINVAL, "route_topk: null buffer");
+  if (counts && T <= ONE_T && E <= ONE_E && (long long)T * E * std::max(k, 2) <= ONE_WORK && E % 4 == 0 && ((uintptr_t)logits & 15) == 0 && (k == 1 || k == 2 || k == 4)) {
+    auto one = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3((T + 255) / 256 * 256), 0, s, logits, T, E, topk_ids, topk_w, counts); };
+    if (k == 1) one(route_count_kernel<1>);
+    else if (k == 2) one(route_count_kernel<2>);
+    else one(route_count_kernel<4>);
+    FEPLB_LAUNCH_CHECK("route_count_kernel");
+    return FEPLB_OK;
+  }
   // enough tokens to occupy a good part of the chip with one token per lane (a wavefront = 64 tokens)
   if (T >= 16384 && E % 32 == 0 && ((uintptr_t)logits & 15) == 0 && (k == 2 || k == 4 || k == 8)) {
     if (k == 2) launch_lane<2>(logits, T, E, topk_ids, topk_w, counts, s);
