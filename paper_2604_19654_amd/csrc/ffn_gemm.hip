@@ -445,7 +445,7 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
   const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
   const auto most = [&](int b) { return ((long)a.R_cap / (64 * b) + a.ng) * n_tiles_n; };   // tiles of up to b row blocks
   Heights h{5, 5, {0.f, 0.f}, {0.f, 0.f}};
-  if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see pick_shape
+  if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see use_tall
   while (h.lo > 2 && most(h.lo - 1) - most(h.hi) <= 512) --h.lo;              // at most two surplus workgroups per CU
   // us: a round starts in 5, multiplies 64 rows x 256 columns in 4.8 per 1000 k, loads the weights in 1.5 (from the caches) to 3.5, and
   // moves its results at about 6 TB/s; with half of the columns 2.0 and 4
@@ -472,7 +472,7 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
 //   K = 2048 45, 41 (and such a launch finds its heights from the rows it has, not from the capacity); 4567 rows, K = 512 7 % of the step lost: K >= 2048.
 bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape) {
   const double tiles = ((double)a.R_cap / SHAPES[shape].bm + 0.5 * a.ng) * (weight_cols / 256);
-  if (mode == 2 || shape == 2) return false;
+  if (mode == 2 || shape == 2 || !(a.row_src || feplb::rows_fit_32_bits(256, a.lda))) return false;
   if (shape == 1) return a.K >= 2048 && tiles > 256.;
   if (mode == 0) return a.K >= 6144 && tiles > 8 * 256.;
   return a.K >= 1280 ? tiles > 128. : a.K >= 1024 && tiles > 4 * 256.;
