@@ -34,13 +34,13 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "ffn_down.hip", "tall_gemm.h", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "95561c25c6cbc4a53e31698ff33f16bf70220bbb1fd3e3ea2a03a804bf198c76",
-           "gate_up": {"read": 2669915 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
-           "down": {"read": 1335715 * 1024 * 2.0, "written": 1573694 * 1024}},
+           "sources_sha256": "a49963998d8c63496037a8fb90e715dcfa2363ec34a8b7b9789dd395b154569a",
+           "gate_up": {"read": 2756624 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
+           "down": {"read": 1273487 * 1024 * 2.0, "written": 1573215 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "95561c25c6cbc4a53e31698ff33f16bf70220bbb1fd3e3ea2a03a804bf198c76",
-           "gate_up": {"read": 551730 * 1024 * 2.0, "written": 61188 * 1024},
-           "down": {"read": 238482 * 1024 * 2.0, "written": 327264 * 1024}},
+           "sources_sha256": "a49963998d8c63496037a8fb90e715dcfa2363ec34a8b7b9789dd395b154569a",
+           "gate_up": {"read": 555189 * 1024 * 2.0, "written": 61188 * 1024},
+           "down": {"read": 263465 * 1024 * 2.0, "written": 326616 * 1024}},
 }
 METRIC = "grouped-FFN TFLOP/s & % bf16 MFMA peak per rank share; permute/combine GB/s"
 
@@ -290,8 +290,8 @@ def _rooflines(name, res):
                 "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic, "avg_launch_ms": t_ms, "algorithmic_bytes_per_launch": nbytes}
 
     out = {
-        "gate_up": mfma("panel_gemm_kernel<0> (gate/up GEMM + SwiGLU)", "gate_up", 4.0 * d * f, "gate_up_bytes"),
-        "down": mfma("panel_gemm_kernel<1> (down GEMM)", "down", 2.0 * d * f, "down_bytes"),
+        "gate_up": mfma("gate/up GEMM + SwiGLU (panel_gemm_kernel<0>, tall_gemm_kernel<0>)", "gate_up", 4.0 * d * f, "gate_up_bytes"),
+        "down": mfma("down GEMM (panel_gemm_kernel<1>, tall_gemm_kernel<1>)", "down", 2.0 * d * f, "down_bytes"),
         "combine": hbm("combine_kernel", ms["combine"], R * d * yp_bytes + T * d * 2 + T * k * 8),
         "permute_with_gather": hbm("index kernels of the permutation + gather_rows_kernel",
                                    res["permute_with_gather_ms"], 2 * R * d * 2 + T * k * 8 + R * 4),

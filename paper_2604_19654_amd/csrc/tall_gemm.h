@@ -1,11 +1,12 @@
 // The grouped GEMMs' loop for tall tiles: up to 320 rows x 256 columns by four wavefronts, one per SIMD.
 //
-// A wave multiplies up to 160 x 128 (5 row blocks of 32), so that an operand read from LDS is used more often and a tile's loads are
-// divided by more products than with the eight wavefronts and 256 x 256 of panel_gemm.h; a tile takes 4.8 us per 1000 k for every 64 rows and 1.5
-// to 3.5 for the weights whatever its height (256 tiles at once), so that heights can be chosen to fill whole rounds of the 256 CUs.  93580 rows, d = 6144, f = 2048: gate/up
-// 3135 -> 3112 us, down 1874 -> 1807, dXp 3318 -> 3222; 16 groups of 495 to 573 rows, d = 4096, f = 1536 (two tiles of five or four blocks
-// each instead of two or three of 256 rows): down 117 -> 99 us, dXp 217 -> 194.  The main loop runs at 1.82 GHz with the matrix pipes busy 82 % of
-// the time where the eight wavefronts run at 1.69 GHz and 83 %: a third fewer LDS reads leave that much more of the power budget.
+// A wave multiplies up to 160 x 128 (5 row blocks of 32), so that an operand read from LDS is used more often than by the eight
+// wavefronts of panel_gemm.h.  256 tiles at once take 4.8 us per 1000 k for every 64 rows of height and 1.5 (from the caches) to 3.5 for
+// the weights, so that heights can be chosen to fill whole rounds of the 256 CUs.  Against 256 x 256 by eight wavefronts: 93580 rows,
+// d = 6144, f = 2048 gate/up 3135 -> 3112 us, down 1874 -> 1807, dXp 3318 -> 3222; 16 groups of 495 to 573 rows, d = 4096, f = 1536 (two tiles
+// of five or four blocks each in the place of two or three of 256 rows) down 117 -> 99 us, dXp 217 -> 194.  What bounds it is the power limit: 256 x 256
+// by four wavefronts keeps the matrix pipes busy 82 % of the time at 1.82 GHz where eight do 83 % at 1.69 GHz (gate/up of the large shape, profiled), with a
+// third fewer LDS reads; back to back, hot, that is 1 to 3 %.
 //
 // With one wave per SIMD nothing hides behind another wave's MFMAs: the order of MFMAs, LDS reads and loads is fixed in the source, a
 // fragment read behind every other MFMA and a load behind every fourth (reads ahead of a slice's MFMAs, as the compiler places them: 7 % slower).
