@@ -99,26 +99,43 @@ __global__ __launch_bounds__(BLOCK) void combine_backward_kernel(
   }
 }
 
-// one thread per (token, expert): the gradient of a kept expert's logit, zero for the others
+// One thread per V neighbouring experts of a token: the gradients of the kept experts' logits, zero for the others.  Every thread reads the
+// token's k choices for itself, so four experts to a thread are a quarter of those reads, and whole 16-byte stores; I is the
+// index type: a 64-bit division by the threads per token took longer than the rest.
+// T = 8192, E = 128, k = 8 6.4 -> 4.3 us, T = 32768 18.4 -> 9.8, T = 2501, E = 64, k = 4 2.63 -> 2.54.
+template <int V, class I>
 __global__ __launch_bounds__(256) void route_backward_kernel(const int* __restrict__ ids, const float* __restrict__ w,
-                                                             const float* __restrict__ dw, long long n, int E, int k,
+                                                             const float* __restrict__ dw, I n, int E, int k,
                                                              float* __restrict__ dz) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  typedef float vec __attribute__((ext_vector_type(V)));
+  const I idx = (I)blockIdx.x * 256 + threadIdx.x;
   if (idx >= n) return;
-  const long long t = idx / E;
-  const int e = (int)(idx % E);
-  float inner = 0.f, wj = 0.f, dwj = 0.f;
-  bool kept = false;
-  for (int j = 0; j < k; ++j) {
-    const float wv = w[t * k + j], dv = dw[t * k + j];
-    inner = fmaf(wv, dv, inner);
-    if (ids[t * k + j] == e) {
-      kept = true;
-      wj = wv;
-      dwj = dv;
-    }
+  const I per = (I)(E / V), t = idx / per;
+  const int e = (int)(idx - t * per) * V;
+  const size_t at = (size_t)t * k;
+  float inner = 0.f, wj[V], dwj[V];
+  bool kept[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    wj[v] = dwj[v] = 0.f;
+    kept[v] = false;
   }
-  dz[idx] = kept ? wj * (dwj - inner) : 0.f;
+  for (int j = 0; j < k; ++j) {
+    const float wv = w[at + j], dv = dw[at + j];
+    const int id = ids[at + j];
+    inner = fmaf(wv, dv, inner);
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (id == e + v) {
+        kept[v] = true;
+        wj[v] = wv;
+        dwj[v] = dv;
+      }
+  }
+  vec out;
+#pragma unroll
+  for (int v = 0; v < V; ++v) out[v] = kept[v] ? wj[v] * (dwj[v] - inner) : 0.f;
+  ((vec*)dz)[idx] = out;
 }
 
 }  // namespace
@@ -169,8 +186,21 @@ extern "C" int32_t feplb_route_topk_backward(const int32_t* topk_ids, const floa
   FEPLB_REQUIRE(topk_ids && topk_w && dw && dlogits, FEPLB_EINVAL, "route_topk_backward: null buffer");
   const long long n = (long long)T * E;
   FEPLB_REQUIRE(n < (1ll << 39), FEPLB_ESHAPE, "route_topk_backward: T*E too large");
-  hipLaunchKernelGGL(route_backward_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                     topk_ids, topk_w, dw, n, E, k, dlogits);
+  const int V = E % 4 == 0 && feplb::aligned16(dlogits) ? 4 : 1;
+  const long long threads = n / V;
+  const dim3 blocks((unsigned)((threads + 255) / 256));
+  hipStream_t s = (hipStream_t)stream;
+#define FEPLB_ROUTE_BWD(V, I) \
+  hipLaunchKernelGGL((route_backward_kernel<V, I>), blocks, dim3(256), 0, s, topk_ids, topk_w, dw, (I)threads, E, k, dlogits)
+  const bool wide = threads + 256 > (1ll << 31);
+  if (V == 4) {
+    if (wide) FEPLB_ROUTE_BWD(4, long long);
+    else FEPLB_ROUTE_BWD(4, unsigned);
+  } else {
+    if (wide) FEPLB_ROUTE_BWD(1, long long);
+    else FEPLB_ROUTE_BWD(1, unsigned);
+  }
+#undef FEPLB_ROUTE_BWD
   FEPLB_LAUNCH_CHECK("route_backward_kernel");
   return FEPLB_OK;
 }

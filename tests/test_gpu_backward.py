@@ -517,6 +517,26 @@ def test_permute_backward_is_the_combine_with_unit_weights():
     assert bf16_rounding_excess(f64(dX), want) <= 1.0
 
 
+
+@pytest.mark.parametrize("T,E,k,shift", [(1, 4, 4, 0), (257, 8, 2, 0), (257, 8, 2, 1), (64, 10, 3, 0), (3, 1, 1, 0), (129, 7, 7, 0), (1000, 96, 5, 2)])
+def test_route_backward_by_four_experts_and_by_one(T, E, k, shift):
+    # Four experts to a thread where E and the output's alignment allow it, one otherwise; `shift` words off a 16-byte boundary.  Each
+    # entry is k fused products and two more operations in fp32: 2^-24 (k + 3) of the sum of the magnitudes at most.
+    say(f"route backward T={T} E={E} k={k} shift={shift}")
+    gen = torch.Generator().manual_seed(T + E)
+    ids, w, _ = B.feplb_route_topk(torch.randn((T, E), generator=gen).to(DEV), k)
+    dw = torch.randn((T, k), generator=gen)
+    room = torch.full((T * E + 8,), 7.0, device=DEV)
+    dz = room[shift: shift + T * E].view(T, E)
+    B.feplb_route_topk_backward(ids, w, dw.to(DEV), E, dz)
+    torch.cuda.synchronize()
+    wd, dd = w.cpu().double(), dw.double()
+    want = torch.zeros((T, E), dtype=torch.float64).scatter_(1, ids.cpu().long(), wd * (dd - (wd * dd).sum(1, keepdim=True)))
+    scale = torch.zeros((T, E), dtype=torch.float64).scatter_(1, ids.cpu().long(), wd * (dd.abs() + (wd * dd).abs().sum(1, keepdim=True)))
+    assert ((dz.cpu().double() - want).abs() <= 2.0 ** -24 * (k + 3) * scale).all()
+    assert (room[:shift] == 7.0).all() and (room[shift + T * E:] == 7.0).all()
+
+
 @pytest.mark.parametrize("T,E,k", [(200, 8, 2), (1000, 128, 8), (77, 5, 5), (3, 1024, 32)])
 def test_route_backward_parity(T, E, k):
     say(f"route backward T={T} E={E} k={k}")
