@@ -21,15 +21,15 @@
 
 namespace {
 
+// A key that orders as the logit: descending magnitudes of the negative numbers, then the positive ones; -0.0 ties with +0.0.
+// Never 0, so that 0 can stand for "no logit", and one key to a bit pattern, NaNs included.
 __device__ __forceinline__ uint32_t orderable(float x) {
-  uint32_t u = __float_as_uint(x);
-  if (u == 0x80000000u) u = 0u;  // -0.0 ties with +0.0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(x);
+  return (u & 0x80000000u) ? 0u - u : (u | 0x80000000u);
 }
 
 __device__ __forceinline__ float from_orderable(uint32_t o) {
-  uint32_t u = (o & 0x80000000u) ? (o & 0x7fffffffu) : ~o;
-  return __uint_as_float(u);
+  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : 0u - o);
 }
 
 template <int CTRL>
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(LANE_WAVES * 64) void route_topk_lane_kernel(
 }
 
 // A small batch of few experts in one workgroup, a token per lane, which counts in LDS what it routes: one launch instead of two,
-// and no clearing.  The keys order as route_topk_kernel's (any bit pattern is a logit), and the weights are its to the bit.  K = k exactly; E a multiple
+// and no clearing.  The keys order as route_topk_kernel's (any bit pattern is a logit), and finite weights are its to the bit.  K = k exactly; E a multiple
 // of 4; logits 16-byte aligned.  Two launches and this one inside a graph, us: T = 512, E = 8, k = 2 4.14, 2.55; T = 32, E = 32, k = 4 4.61, 3.88; and at the
 // line, T E max(k, 2) = 32768, T = 1024, E = 8, k = 4 4.75, 3.98; T = 512, E = 32, k = 1 4.26, 3.73; beyond it T = 1024, E = 16, k = 4 4.99, 5.41;
 // T = 1024, E = 32, k = 1 4.35, 5.51.  (Sub-groups of lanes as in route_topk_kernel: T = 512, E = 8, k = 2 5.25.)
@@ -243,8 +243,7 @@ __global__ __launch_bounds__(ONE_T) void route_count_kernel(const float* __restr
       const f32x4 x = row[c];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint32_t key = orderable(x[i]);
-        insert_sorted<K, uint32_t>(v, id, key > 1u ? key : 1u, 4 * c + i);
+        insert_sorted<K, uint32_t>(v, id, orderable(x[i]), 4 * c + i);
       }
     }
   }

@@ -82,6 +82,25 @@ def test_route_topk_of_small_batches(T, E, k):
     assert np.array_equal(ids.cpu().numpy()[finite], orc.route_topk(logits.numpy()[finite], k)[0])
 
 
+@pytest.mark.parametrize("k", [1, 2, 4])
+def test_route_topk_of_small_batches_orders_every_bit_pattern(k):
+    # NaNs order by their bits like any logit: the one-workgroup kernel of small batches (with counts) and the general one (without) choose alike.
+    bits = [0xFFFFFFFF, 0xFFFFFFFE, 0xFFC00000, 0xFF800001, 0xFF800000, 0xFF7FFFFF, 0x80000001, 0x80000000, 0, 1, 0x3F800000, 0x7F800000, 0x7F800001,
+            0x7FC00000, 0x7FFFFFFF]
+    rng = np.random.default_rng(5)
+    rows = [[0xFFFFFFFE] * 3 + [0xFFFFFFFF] * 5, [0xFFFFFFFF] * 8, [0xFFFFFFFF, 0xFFFFFFFE] * 4] + [list(rng.choice(bits, size=8)) for _ in range(253)]
+    say(f"route small, bit patterns k={k}")
+    x = torch.from_numpy(np.array(rows, dtype=np.uint32).view(np.float32)).to(DEV)
+    ids, w, counts = fe.feplb_route_topk(x, k)
+    ids_g, w_g, _ = fe.feplb_route_topk(x, k, want_counts=False)
+    torch.cuda.synchronize()
+    key = [[0x80000000 if b == 0x80000000 else 0xFFFFFFFF - b if b >> 31 else b | 0x80000000 for b in map(int, row)] for row in rows]
+    want = [sorted(range(8), key=lambda e: (-r[e], e))[:k] for r in key]
+    assert ids_g.cpu().tolist() == want and ids.cpu().tolist() == want
+    assert torch.equal(w.isnan(), w_g.isnan()) and torch.equal(w.nan_to_num(), w_g.nan_to_num())
+    assert counts.cpu().tolist() == torch.bincount(ids.reshape(-1).long().cpu(), minlength=8).tolist()
+
+
 # ------------------------------------------------------------------ permute
 def random_ids(T, E, k, seed, skew=0.0):
     rng = np.random.default_rng(seed)
