@@ -274,9 +274,8 @@ int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* offsets,
 /* Height in rows (64, 128 or 256) of the tiles that a grouped GEMM of these entry points is launched in,
  * picked on the host from the row capacity and the sizes alone; results do not depend on it.  A launch in tiles of
  * 256 rows x 256 columns may compute some as quarters of 128 x 128: the tiles beyond whole rounds of 256 (all of them where there
- * are fewer), if they are at most 64, which the rows on the device decide.  (The weight gradients' launches do not.)  In the place of
- * tiles of 128 and 256 rows some launches take tall tiles, whose height of 64 to 320 rows is picked on the device from
- * the groups' rows, left-over ones as halves of their columns or as quarters.  For
+ * are fewer), if they are at most 64, which the rows on the device decide.  (The weight gradients' launches do not.)
+ * Launches for which the next query is not 0 run in tall tiles instead.  For
  * tests that want every shape covered and for reading profiles.  R_cap, n_groups (g_end - g_begin),
  * d, f as in the call (GATE_UP: without row_src; DH, DXP: with the weights given); 0 for arguments
  * out of range.  Host-only. */
@@ -287,6 +286,13 @@ int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* offsets,
 #define FEPLB_GEMM_DW_DOWN 4
 #define FEPLB_GEMM_DW_GATE_UP 5
 int32_t feplb_grouped_ffn_tile_rows(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f);
+
+/* Some launches of GATE_UP, DOWN and DXP take tall tiles of 256 columns, picked on the host as above, whose height is picked on the
+ * device from the groups' rows; left-over tiles are computed as halves of their columns or as quarters.  Returns the height in rows (128 to
+ * 320) of the tallest tiles that groups with these offsets may take, 0 for a launch in other tiles or arguments out of range.
+ * out: GATE_UP: 1 with AB, else 0; DOWN, DXP: the type of the result (FEPLB_F32, FEPLB_BF16).  offsets [n_groups + 1]: host memory.  Host-only. */
+int32_t feplb_grouped_ffn_tall_rows(int32_t gemm, int32_t out, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f,
+                                    const int32_t* offsets);
 
 /* ------------------------------------------------------------------ combine
  * Section 2.3: the last step of a micro-batch hands the experts' outputs back to the

@@ -75,6 +75,7 @@ def lib():
                                                  vp, vp, vp, vp, i32, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp),
                                                  vp, sz, i32, vp, sz, vp]
         L.feplb_grouped_ffn_tile_rows.argtypes = [i32] * 5
+        L.feplb_grouped_ffn_tall_rows.argtypes = [i32] * 6 + [C.POINTER(i32)]
         L.feplb_unpermute_combine.argtypes = [vp, i32, i32, vp, vp, i32, i32, i32, vp, vp]
         L.feplb_combine_backward.argtypes = [vp, vp, i32, i32, vp, vp, i32, i32, i32, vp, vp, vp]
         L.feplb_route_topk_backward.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp]
@@ -335,8 +336,15 @@ def feplb_grouped_ffn_backward(Xp, offsets, g_begin, g_end, d, f, w_gate, w_up, 
 
 def feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f) -> int:
     """Host-only: height in rows of the tiles that grouped GEMM `gemm` (GEMM_*) would be launched in (of 256-row tiles, a few
-    left-over ones may be computed as quarters)."""
+    left-over ones may be computed as quarters), unless feplb_grouped_ffn_tall_rows says tall ones."""
     return int(lib().feplb_grouped_ffn_tile_rows(gemm, R_cap, n_groups, d, f))
+
+
+def feplb_grouped_ffn_tall_rows(gemm, out, R_cap, d, f, offsets) -> int:
+    """Host-only: height in rows of the tall tiles that GEMM_GATE_UP (`out`: 1 with AB), GEMM_DOWN or GEMM_DXP (`out`: F32 or BF16)
+    would take for groups with these offsets (a sequence of n_groups + 1); 0 if it would be launched in other tiles."""
+    off = (C.c_int32 * len(offsets))(*[int(x) for x in offsets])
+    return int(lib().feplb_grouped_ffn_tall_rows(gemm, out, R_cap, len(offsets) - 1, d, f, off))
 
 
 def feplb_unpermute_combine(Yp, inv, topk_w, T, k, d, Y=None, stream=None):

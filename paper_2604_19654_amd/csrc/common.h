@@ -38,6 +38,7 @@ hipError_t launch_plain_gemm(const GroupedGemm& a, bool out_bf16, hipStream_t s)
 hipError_t launch_plain_gemm_nk(const GroupedGemm& a, bool out_bf16, hipStream_t s);   // with w_nk
 hipError_t launch_dswiglu(const GroupedGemm& a, hipStream_t s);
 int gemm_tile_rows(const GroupedGemm& a, bool gate_up);   // rows of a tile of the shape that these pick
+int gemm_tall_rows(const GroupedGemm& a, bool gate_up, bool save, bool out_bf16, const int* offsets);   // of a launch in tall tiles, else 0
 
 // The GEMMs address the rows of a tile as 32-bit byte offsets from its first row: can `rows` rows of `ld` bf16 be?
 inline bool rows_fit_32_bits(int64_t rows, int64_t ld) { return rows * ld * 2 <= 0xffffffffll; }

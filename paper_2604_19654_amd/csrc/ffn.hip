@@ -253,18 +253,36 @@ extern "C" int32_t feplb_grouped_ffn_backward(const void* Xp, const int32_t* off
   return FEPLB_OK;
 }
 
-extern "C" int32_t feplb_grouped_ffn_tile_rows(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f) {
-  if (R_cap < 0 || n_groups < 1 || n_groups > FEPLB_MAX_GROUPS || d < 256 || f < 128) return 0;
-  feplb::GroupedGemm a{};
+namespace {
+// the sizes of the call that launches this GEMM; false for one of the weight gradients'
+bool sizes_of(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f, feplb::GroupedGemm& a) {
   a.R_cap = R_cap;
   a.ng = n_groups;
   switch (gemm) {
-    case FEPLB_GEMM_GATE_UP: a.K = a.lda = d; a.N = a.ldw = f; return feplb::gemm_tile_rows(a, true);
-    case FEPLB_GEMM_DOWN: a.K = a.lda = f; a.N = a.ldw = d; return feplb::gemm_tile_rows(a, false);
-    case FEPLB_GEMM_DH: a.K = a.lda = a.ldw = d; a.N = f; a.w_nk = true; return feplb::gemm_tile_rows(a, false);
-    case FEPLB_GEMM_DXP: a.K = a.lda = 2 * f; a.N = d; a.ldw = f; a.w_nk = true; return feplb::gemm_tile_rows(a, false);
+    case FEPLB_GEMM_GATE_UP: a.K = a.lda = d; a.N = a.ldw = f; return true;
+    case FEPLB_GEMM_DOWN: a.K = a.lda = f; a.N = a.ldw = d; return true;
+    case FEPLB_GEMM_DH: a.K = a.lda = a.ldw = d; a.N = f; a.w_nk = true; return true;
+    case FEPLB_GEMM_DXP: a.K = a.lda = 2 * f; a.N = d; a.ldw = f; a.w_nk = true; return true;
+    default: return false;
+  }
+}
+}  // namespace
+
+extern "C" int32_t feplb_grouped_ffn_tile_rows(int32_t gemm, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f) {
+  if (R_cap < 0 || n_groups < 1 || n_groups > FEPLB_MAX_GROUPS || d < 256 || f < 128) return 0;
+  feplb::GroupedGemm a{};
+  if (sizes_of(gemm, R_cap, n_groups, d, f, a)) return feplb::gemm_tile_rows(a, gemm == FEPLB_GEMM_GATE_UP);
+  switch (gemm) {
     case FEPLB_GEMM_DW_DOWN: return feplb::wgrad_tile_rows(R_cap, n_groups, f, d);
     case FEPLB_GEMM_DW_GATE_UP: return feplb::wgrad_tile_rows(R_cap, n_groups, d, 2 * f);
     default: return 0;
   }
+}
+
+extern "C" int32_t feplb_grouped_ffn_tall_rows(int32_t gemm, int32_t out, int32_t R_cap, int32_t n_groups, int32_t d, int32_t f,
+                                               const int32_t* offsets) {
+  if (R_cap < 0 || n_groups < 1 || n_groups > FEPLB_MAX_GROUPS || d < 256 || f < 128 || !offsets) return 0;
+  feplb::GroupedGemm a{};
+  if (gemm == FEPLB_GEMM_DH || !sizes_of(gemm, R_cap, n_groups, d, f, a)) return 0;
+  return feplb::gemm_tall_rows(a, gemm == FEPLB_GEMM_GATE_UP, out != 0, out == FEPLB_BF16, offsets);
 }

@@ -325,16 +325,17 @@ struct Heights {
 };
 
 // The height of the large tiles by estimated time, from the groups' rows: whole rounds of tiles of the average height, and one of the
-// tallest if tiles are left over.
-__device__ __forceinline__ int pick_height(const TallTiles& tiles, const Heights& h, int n_tiles_n) {
-  const float blocks = (float)tiles.count(1);
+// tallest if tiles are left over.  count(b): row tiles of height up to b in all groups; rcp: 1 / x
+template <class Count, class Rcp>
+__host__ __device__ __forceinline__ int pick_height(const Heights& h, int n_tiles_n, Count&& count, Rcp&& rcp) {
+  const float blocks = (float)count(1);
   int best = h.hi;
   float best_us = 0.f;
 #pragma unroll
   for (int b = 5; b >= 2; --b) {
     if (b > h.hi || b < h.lo) continue;
-    const int row_tiles = tiles.count(b), n = row_tiles * n_tiles_n, rest = n % 256;
-    const float mean = blocks * __builtin_amdgcn_rcpf((float)row_tiles);
+    const int row_tiles = count(b), n = row_tiles * n_tiles_n, rest = n % 256;
+    const float mean = blocks * rcp((float)row_tiles);
     const float tail = rest == 0 ? 0.f : rest <= QUARTERS_MAX ? h.half[0] + h.half[1] * (float)((b + 1) / 2)
                        : rest <= HALVES_MAX ? h.half[0] + h.half[1] * (float)b : h.whole[0] + h.whole[1] * (float)b;
     const float us = (float)(n / 256) * (h.whole[0] + h.whole[1] * mean) + tail;
@@ -343,7 +344,7 @@ __device__ __forceinline__ int pick_height(const TallTiles& tiles, const Heights
       best_us = us;
     }
   }
-  return __builtin_amdgcn_readfirstlane(best);
+  return best;
 }
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
@@ -359,7 +360,8 @@ __global__ __launch_bounds__(256, 1) void tall_gemm_kernel(
   // ---- block -> tile: bands of `band` row tiles, walked column by column; a left-over tile has several blocks
   TallTiles tiles;
   tiles.load(offsets, g_begin, ng, R_cap);
-  tiles.split(pick_height(tiles, heights, n_tiles_n));
+  tiles.split(__builtin_amdgcn_readfirstlane(pick_height(heights, n_tiles_n, [&](int b) { return tiles.count(b); },
+                                                         [](float x) { return __builtin_amdgcn_rcpf(x); })));
   const int total = tiles.total * n_tiles_n;
   const int rest = total % 256, pieces = rest <= QUARTERS_MAX ? 4 : 2;
   const int whole = rest <= HALVES_MAX ? total - rest : total;
@@ -439,22 +441,31 @@ hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// tiles of up to b row blocks in a launch, at most
+long most_tiles(const feplb::GroupedGemm& a, int b, int n_tiles_n) { return ((long)a.R_cap / (64 * b) + a.ng) * n_tiles_n; }
+
+// the heights that a launch may take, and what they cost.  us: a round starts in 5, multiplies 64 rows x 256 columns in 4.8 per 1000 k, loads the
+// weights in 1.5 (from the caches) to 3.5, and moves its results (`tensors` of 64 rows x 128 columns in 16 bits) at about 6 TB/s; with half of the
+// columns 2.0 and 4
+Heights tall_heights(const feplb::GroupedGemm& a, bool gate_up, int tensors, int n_tiles_n) {
+  Heights h{5, 5, {0.f, 0.f}, {0.f, 0.f}};
+  if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see use_tall
+  while (h.lo > 2 && most_tiles(a, h.lo - 1, n_tiles_n) - most_tiles(a, h.hi, n_tiles_n) <= 512) --h.lo;   // at most two surplus workgroups per CU
+  const float k = 1e-3f * a.K, out = 64.f * 256 * 256e-6f / 6 * tensors;
+  h.whole[0] = 5.f + (gate_up ? 3.5f : 2.f) * k;
+  h.whole[1] = out + 4.8f * k;
+  h.half[0] = 5.f + 4.f * k;
+  h.half[1] = 0.5f * out + 2.f * k;
+  return h;
+}
+int tall_tensors(bool gate_up, bool save, bool out_bf16) { return gate_up ? (save ? 3 : 1) : out_bf16 ? 2 : 4; }
+
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
 hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
   using Core = TallGemm<5, 2, 2, 4, B_TR>;
   const int n_tiles_n = a.N / (MODE == 0 ? Core::HW : Core::BN);
-  const auto most = [&](int b) { return ((long)a.R_cap / (64 * b) + a.ng) * n_tiles_n; };   // tiles of up to b row blocks
-  Heights h{5, 5, {0.f, 0.f}, {0.f, 0.f}};
-  if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see use_tall
-  while (h.lo > 2 && most(h.lo - 1) - most(h.hi) <= 512) --h.lo;              // at most two surplus workgroups per CU
-  // us: a round starts in 5, multiplies 64 rows x 256 columns in 4.8 per 1000 k, loads the weights in 1.5 (from the caches) to 3.5, and
-  // moves its results at about 6 TB/s; with half of the columns 2.0 and 4
-  const float k = 1e-3f * a.K, out = 64.f * 256 * 256e-6f / 6 * (MODE == 0 ? (SAVE ? 3 : 1) : OUT_BF16 ? 2 : 4);
-  h.whole[0] = 5.f + (MODE == 0 ? 3.5f : 2.f) * k;
-  h.whole[1] = out + 4.8f * k;
-  h.half[0] = 5.f + 4.f * k;
-  h.half[1] = 0.5f * out + 2.f * k;
-  const long blocks = most(h.lo) + (3 * QUARTERS_MAX > HALVES_MAX ? 3 * QUARTERS_MAX : HALVES_MAX);
+  const Heights h = tall_heights(a, MODE == 0, tall_tensors(MODE == 0, SAVE, OUT_BF16), n_tiles_n);
+  const long blocks = most_tiles(a, h.lo, n_tiles_n) + (3 * QUARTERS_MAX > HALVES_MAX ? 3 * QUARTERS_MAX : HALVES_MAX);
   hipLaunchKernelGGL((tall_gemm_kernel<MODE, OUT_BF16, SAVE, B_TR>), dim3(blocks_for_tiles(blocks)), dim3(256), 0, s, (const uint16_t*)a.A, a.lda,
                      a.row_src, a.n_src_rows, a.src_k, a.offsets, a.g_begin, a.ng, a.R_cap, a.K, n_tiles_n, 8, h, *a.weights, a.ldw, a.k_split, a.out,
                      a.ldo, a.aux, a.ld_aux);
@@ -498,6 +509,19 @@ namespace feplb {
 // compiled in parts, for the sake of the build's time
 #if !defined(FEPLB_GEMM_PART)
 int gemm_tile_rows(const GroupedGemm& a, bool gate_up) { return SHAPES[pick_shape(a, gate_up ? 2 * a.N : a.N)].bm; }
+int gemm_tall_rows(const GroupedGemm& a, bool gate_up, bool save, bool out_bf16, const int* offsets) {
+  const int weight_cols = gate_up ? 2 * a.N : a.N, n_tiles_n = weight_cols / 256;
+  if (!use_tall(a, gate_up ? 0 : 1, weight_cols, pick_shape(a, weight_cols))) return 0;
+  auto count = [&](int b) {
+    int n = 0;
+    for (int g = 0; g < a.ng; ++g) {
+      const int lo = offsets[g] < a.R_cap ? offsets[g] : a.R_cap, hi = offsets[g + 1] < a.R_cap ? offsets[g + 1] : a.R_cap;
+      if (hi > lo) n += ((hi - lo + 63) / 64 + b - 1) / b;
+    }
+    return n;
+  };
+  return 64 * pick_height(tall_heights(a, gate_up, tall_tensors(gate_up, save, out_bf16), n_tiles_n), n_tiles_n, count, [](float x) { return 1.f / x; });
+}
 hipError_t launch_gate_up(const GroupedGemm& a, hipStream_t s) {
   return a.aux ? launch_gate_up_keeping(a, s) : launch_shape<0, true, false, true>(a, s);
 }

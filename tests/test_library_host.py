@@ -128,6 +128,29 @@ def test_tiles_whose_rows_do_not_fit_32_bit_offsets_are_not_used():
     assert forward(big, 128, fe.FFN_GATE_UP, row_src=4096) == -4                   # gathered rows: T * d counts
 
 
+def test_tall_rows_says_which_launches_are_not_in_the_tiles_that_tile_rows_names():
+    # feplb_grouped_ffn_tile_rows names one of three shapes for every launch; the launches that take tall tiles in their place have a query of
+    # their own, with the height that these groups' rows may take.
+    B = fe.binding
+    tall, tile = B.feplb_grouped_ffn_tall_rows, B.feplb_grouped_ffn_tile_rows
+    even = lambda ng, rows: [rows * g // ng for g in range(ng + 1)]   # noqa: E731
+    one_round = (9130, 1024, 1536)       # 8 groups of about 1141 rows: 160 tiles of 256 x 256
+    for gemm, outs, d, f in ((B.GEMM_DOWN, (B.F32, B.BF16), 1024, 1536), (B.GEMM_DXP, (B.F32, B.BF16), 1024, 768)):
+        assert tile(gemm, 9130, 8, d, f) == 256 and all(tall(gemm, out, 9130, d, f, even(8, 9130)) in (128, 192, 256, 320) for out in outs)
+    for out in (0, 1):
+        assert tall(B.GEMM_GATE_UP, out, 93580, 6144, 2048, even(4, 93580)) == 320
+    # the rows on the device decide the height, not the capacity
+    assert len({tall(B.GEMM_DOWN, B.F32, *one_round, even(8, rows)) for rows in (1000, 9130)}) == 2
+    # 320 rows of 6912000 elements do not fit 32-bit byte offsets, 256 do; of 2^24, neither does
+    assert [tall(B.GEMM_GATE_UP, 0, 1 << 20, d, 128, [0, 1 << 20]) for d in (1 << 22, 6912000, 1 << 24)] == [320, 256, 0]
+    # other tiles, no GEMM of this kind, arguments out of range
+    assert tall(B.GEMM_DOWN, B.F32, 768, 4096, 1536, even(16, 768)) == 0
+    for gemm in (B.GEMM_DH, B.GEMM_DW_DOWN, B.GEMM_DW_GATE_UP, 17):
+        assert tall(gemm, 0, 93580, 6144, 2048, even(4, 93580)) == 0
+    assert tall(B.GEMM_DOWN, B.F32, -1, 1024, 1536, even(8, 9130)) == 0 and tall(B.GEMM_DOWN, B.F32, 9130, 1024, 1536, [0]) == 0
+    assert fe.lib().feplb_grouped_ffn_tall_rows(B.GEMM_DOWN, 0, 9130, 8, 1024, 1536, None) == 0
+
+
 def as_tuples(moves):
     return [tuple(int(v) for v in m) for m in moves]
 
