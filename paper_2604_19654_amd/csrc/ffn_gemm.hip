@@ -14,8 +14,8 @@
 //   128 x 256, 4 wavefronts, two workgroups per CU: one's prologue and epilogue hide behind the other's loop and half
 //              the rows are lost to rounding a group up, but operand traffic in LDS is 1.1x its bandwidth at full MFMA rate.
 //   64 x 128,  4 wavefronts, two workgroups per CU with deep rings: for launches that would leave most CUs idle otherwise.
-// and tall tiles, up to 320 x 256, 4 wavefronts, one workgroup per CU, whose height every launch finds from its groups' rows: for the
-// plain products and for gate/up with many rounds of tiles, and wherever 128 x 256 tiles would be more than one to a CU (use_tall below).
+// and tall tiles, up to 320 x 256, 4 wavefronts, one workgroup per CU, whose height every launch finds from its groups' rows: where another
+// height fills the rounds better, and for gate/up with many rounds of tiles (use_tall below).
 // 256 weight columns x 64 k of LDS-DMA loads in flight per CU also stream weights well: 16 groups of 8 rows, d = 4096,
 // f = 1536 (400 MB of gate/up weights): 109 -> 77 us, 5.2 TB/s.
 // The weights are row-major [K,N] (B_TR: the MFMA operand needs 8 consecutive k of one column, which the transposing LDS
@@ -444,18 +444,26 @@ hipError_t launch(const feplb::GroupedGemm& a, hipStream_t s) {
 // tiles of up to b row blocks in a launch, at most
 long most_tiles(const feplb::GroupedGemm& a, int b, int n_tiles_n) { return ((long)a.R_cap / (64 * b) + a.ng) * n_tiles_n; }
 
-// the heights that a launch may take, and what they cost.  us: a round starts in 5, multiplies 64 rows x 256 columns in 4.8 per 1000 k, loads the
-// weights in 1.5 (from the caches) to 3.5, and moves its results (`tensors` of 64 rows x 128 columns in 16 bits) at about 6 TB/s; with half of the
-// columns 2.0 and 4
+// The heights that a launch may take, and what they cost: a fit to 1975 launches drawn over the layer's sizes, each at the four heights, timed
+// inside layer steps, where the weights come from memory (`tensors` of 64 rows x 128 columns in 16 bits leave per block and CU).  Off by 10 % in
+// the root mean square; the height picked by it is 0.7 % slower than the best of the four.  (Constants from launches timed back to back, whose weights the
+// memory-side cache then holds, took lower tiles: 2.5 % slower than the best, plain, and 5 % gate/up.)
 Heights tall_heights(const feplb::GroupedGemm& a, bool gate_up, int tensors, int n_tiles_n) {
   Heights h{5, 5, {0.f, 0.f}, {0.f, 0.f}};
   if (!(a.row_src || feplb::rows_fit_32_bits(320, a.lda))) h.lo = h.hi = 4;   // 256 rows do, see use_tall
   while (h.lo > 2 && most_tiles(a, h.lo - 1, n_tiles_n) - most_tiles(a, h.hi, n_tiles_n) <= 512) --h.lo;   // at most two surplus workgroups per CU
-  const float k = 1e-3f * a.K, out = 64.f * 256 * 256e-6f / 6 * tensors;
-  h.whole[0] = 5.f + (gate_up ? 3.5f : 2.f) * k;
-  h.whole[1] = out + 4.8f * k;
-  h.half[0] = 5.f + 4.f * k;
-  h.half[1] = 0.5f * out + 2.f * k;
+  const float k = 1e-3f * a.K, t = (float)tensors;
+  if (gate_up) {
+    h.whole[0] = 3.1f + 8.f * k;
+    h.whole[1] = 0.9f * t + 3.2f * k;
+    h.half[0] = 6.8f * k;
+    h.half[1] = 1.6f * t + 1.9f * k;
+  } else {
+    h.whole[0] = 4.4f + 5.8f * k;
+    h.whole[1] = 0.5f * t + 3.7f * k;
+    h.half[0] = 2.7f + 6.2f * k;
+    h.half[1] = 0.1f * t + 2.2f * k;
+  }
   return h;
 }
 int tall_tensors(bool gate_up, bool save, bool out_bf16) { return gate_up ? (save ? 3 : 1) : out_bf16 ? 2 : 4; }
@@ -472,21 +480,27 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps (us, before and in tall tiles):
-//   in the place of 256 x 256: gate/up 93580 rows, d = 6144, f = 2048 3135, 3112; 80387 rows, d = 7168, f = 2048 3295, 3182 (keeping the
-//   derivatives 3374, 3285); 8228 rows in 16 groups, d = 4096, f = 1536 209, 223; 20318 rows in 6 groups 390, 407;
-//   93430 rows in 8 groups, d = 1536, f = 1024 3 % of the step lost: from eight rounds of tiles and K = 6144 on.
-//   Plain, 8228 rows, K = 1536 143, 125; K = 3072 211, 189; 20318 rows, K = 1536 262, 251; 2110 rows, K = 1408 29, 23; 6390 rows in 8 groups, K = 768
-//   38, 42; some hundred rows, K = 1024 1 % of the step lost, and with one column of tiles too; 93430 rows, K = 1024 3 % of the step gained: K >= 1280 and
-//   128 tiles, or K >= 1024 and four rounds;
-//   in the place of 128 x 256 where those would be more than one to a CU: gate/up, K = 6144 204, 140; capacity for 6018 rows of which 2110 exist,
-//   K = 2048 45, 41 (and such a launch finds its heights from the rows it has, not from the capacity); 4567 rows, K = 512 7 % of the step lost: K >= 2048.
+// Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps, some 3500 launches drawn over the layer's
+// sizes, each in that shape and in tall tiles at the height that pick_height takes: geometric mean of the gain, and its first and last tenth.  `tiles`
+// are those of the shape, and like it estimated from the row capacity; a fifth of the launches had rows for a part of it only.
+//   In the place of 256 x 256, plain, K >= 1280:
+//     more than half a round of 256 and up to one, which lower tiles fill better: 1.040 (0.92, 1.22).  Rows for a quarter of a round, which run as
+//     quarters of 256 x 256, lose (capacity for 178 tiles, rows for 60: 13 -> 18 us), rows for half of one gain more (for 163 and 60 % of them: 41 -> 29).
+//     K = 768 to 1279 1.037 (0.86, 1.23), left out for its first tenth;
+//     two rounds and a rest, more than quarters take, that tiles of 320 rows save: 1.037 (0.94, 1.15), e.g. 16 groups of about 512 rows, d = 4096,
+//     f = 1536, down 130 -> 113 us, dXp 221 -> 189.  From 577 to 656 tiles, where the gain crosses 1: up to 576 0.970, 657 to 832 0.962;
+//     more than four rounds, K < 2048 0.976, from 2048 on 0.998 (0.96, 1.04).
+//   Gate/up, more than eight rounds: K < 2048 0.88, to 3071 0.951, to 4095 0.994, to 6143 1.009, from there on 1.012 (0.96, 1.05; 93580 rows,
+//     d = 6144, f = 2048 3300 -> 3170 us); fewer rounds, K >= 6144 1.019 (0.92, 1.16).
+//   In the place of 128 x 256 where those would be more than one to a CU, plain, K >= 2048: 1.100 (0.96, 1.29), smaller K 0.986, up to one to a CU 0.991;
+//   gate/up, K >= 3072: 1.077 (0.94, 1.30); K = 2048 to 3071, a rest of up to a quarter after a round of 512 1.039 (0.90, 1.20), else 0.973; smaller K 0.905.
 bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape) {
   const double tiles = ((double)a.R_cap / SHAPES[shape].bm + 0.5 * a.ng) * (weight_cols / 256);
   if (mode == 2 || shape == 2 || !(a.row_src || feplb::rows_fit_32_bits(256, a.lda))) return false;
-  if (shape == 1) return a.K >= 2048 && tiles > 256.;
+  if (shape == 1) return a.K >= (mode == 0 ? 3072 : 2048) ? tiles > 256. : mode == 0 && a.K >= 2048 && tiles > 512. && tiles <= 640.;
   if (mode == 0) return a.K >= 6144 && tiles > 8 * 256.;
-  return a.K >= 1280 ? tiles > 128. : a.K >= 1024 && tiles > 4 * 256.;
+  if (a.K < 1280) return false;
+  return tiles <= 256. ? tiles > 128. : tiles > 2 * 256. + QUARTERS_MAX && tiles <= 656.;
 }
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>
