@@ -489,7 +489,9 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
 //     K = 768 to 1279 1.037 (0.86, 1.23), left out for its first tenth;
 //     two rounds and a rest, more than quarters take, that tiles of 320 rows save: 1.037 (0.94, 1.15), e.g. 16 groups of about 512 rows, d = 4096,
 //     f = 1536, down 130 -> 113 us, dXp 221 -> 189.  From 577 to 656 tiles, where the gain crosses 1: up to 576 0.970, 657 to 832 0.962;
-//     more than four rounds, K < 2048 0.976, from 2048 on 0.998 (0.96, 1.04).
+//     more tiles: K < 2048 0.979 (0.93, 1.04), up to four columns of tiles 0.962 (0.92, 1.03; few tiles share a row of A, which then comes from memory);
+//     other 1.001 (0.95, 1.05), taken, since copies beside such a launch find CUs free sooner (replicas' weights staged beside it, 6214 rows,
+//     d = 6144, f = 2048: a layer step of 645 to 658 us instead of 673 to 677).
 //   Gate/up, more than eight rounds: K < 2048 0.88, to 3071 0.951, to 4095 0.994, to 6143 1.009, from there on 1.012 (0.96, 1.05; 93580 rows,
 //     d = 6144, f = 2048 3300 -> 3170 us); fewer rounds, K >= 6144 1.019 (0.92, 1.16).
 //   In the place of 128 x 256 where those would be more than one to a CU, plain, K >= 2048: 1.100 (0.96, 1.29), smaller K 0.986, up to one to a CU 0.991;
@@ -500,7 +502,7 @@ bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape)
   if (shape == 1) return a.K >= (mode == 0 ? 3072 : 2048) ? tiles > 256. : mode == 0 && a.K >= 2048 && tiles > 512. && tiles <= 640.;
   if (mode == 0) return a.K >= 6144 && tiles > 8 * 256.;
   if (a.K < 1280) return false;
-  return tiles <= 256. ? tiles > 128. : tiles > 2 * 256. + QUARTERS_MAX && tiles <= 656.;
+  return tiles <= 256. ? tiles > 128. : tiles > 2 * 256. + QUARTERS_MAX && (tiles <= 656. || (a.K >= 2048 && weight_cols > 1024));
 }
 
 template <int MODE, bool OUT_BF16, bool SAVE, bool B_TR>

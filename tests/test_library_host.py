@@ -156,14 +156,15 @@ def test_tall_tiles_are_taken_where_they_were_measured_to_gain():
     # shape and in tall tiles; on either side of each line.
     B = fe.binding
     up, keep, down, dxp = (B.GEMM_GATE_UP, 0), (B.GEMM_GATE_UP, 1), (B.GEMM_DOWN, B.F32), (B.GEMM_DXP, B.F32)
-    slower = [(down, 102196, 16, 512, 1280, (158.6, 173.9)), (dxp, 102196, 16, 512, 1280, (220.7, 241.2)), (dxp, 4234, 12, 5632, 768, (73.0, 80.9)),
-              (down, 31253, 32, 1024, 1536, (109.0, 119.5)), (dxp, 13611, 16, 2816, 1280, (177.3, 214.9)), (dxp, 29320, 8, 2304, 1536, (316.8, 338.4)),
-              (dxp, 45788, 12, 2048, 512, (194.9, 203.8)), (down, 38953, 32, 5888, 1280, (467.7, 491.3)), (up, 22692, 12, 2816, 512, (114.9, 137.0)),
+    down16, dxp16 = (B.GEMM_DOWN, B.BF16), (B.GEMM_DXP, B.BF16)
+    slower = [(down, 102196, 16, 512, 1280, (158.6, 173.9)), (dxp16, 102196, 16, 512, 1280, (220.7, 241.2)), (dxp16, 4234, 12, 5632, 768, (73.0, 80.9)),
+              (down, 31253, 32, 1024, 1536, (109.0, 119.5)), (down, 41344, 12, 1024, 1920, (147.6, 160.4)), (dxp, 15499, 32, 4096, 768, (179.8, 197.2)),
+              (dxp, 45788, 12, 2048, 512, (194.9, 203.8)), (down16, 38953, 32, 5888, 1280, (467.7, 491.3)), (up, 22692, 12, 2816, 512, (114.9, 137.0)),
               (keep, 4201, 32, 2048, 1792, (57.2, 65.1)), (keep, 4752, 8, 2560, 1536, (71.6, 104.8)), (up, 20318, 6, 4096, 1536, (390.0, 407.0))]
     faster = [(down, 9130, 8, 1024, 1536, (38.6, 35.3)), (dxp, 9130, 8, 1024, 1536, (66.5, 57.3)), (dxp, 10501, 16, 768, 1536, (61.7, 55.4)),
               (down, 16453, 16, 512, 1792, (41.8, 36.2)), (dxp, 8185, 16, 4096, 1536, (220.9, 191.2)), (down, 8185, 16, 4096, 1536, (129.9, 116.1)),
-              (up, 93580, 4, 6144, 2048, (3308., 3178.)), (keep, 7881, 16, 2304, 1024, (92.8, 83.6)), (up, 2859, 32, 5376, 1408, (136.0, 99.8)),
-              (dxp, 5767, 16, 2816, 2048, (178.7, 158.3))]
+              (up, 93580, 4, 6144, 2048, (3308., 3178.)), (keep, 7881, 16, 2304, 1024, (92.8, 83.6)), (up, 2859, 32, 5376, 1408, (136.0, 99.8)), (dxp, 80088, 32, 7168, 2048, (3452., 3386.)),
+              (dxp16, 5767, 16, 2816, 2048, (178.7, 158.3))]
     for launches, want in ((slower, False), (faster, True)):
         for (gemm, out), R_cap, ng, d, f, (before, in_tall) in launches:
             rows = [R_cap * g // ng for g in range(ng + 1)]
