@@ -9,7 +9,7 @@ import paper_2604_19654_amd as fe
 from paper_2604_19654_amd import runner
 import workloads
 from oracle import feplb_oracle as orc
-from tests.util import f64, row_rel_err, bf16_rounding_excess, how_256_row_tiles_run, ROW_TOL
+from tests.util import f64, row_rel_err, bf16_rounding_excess, how_256_row_tiles_run, ROW_TOL, TALL_CASES
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -400,7 +400,8 @@ def test_grouped_ffn_tile_shapes_agree_at_their_edges(d, f, copies, large, capac
     first = first_AB = None
     capacities = (R, *capacities)
     for gemm in (fe.binding.GEMM_GATE_UP, fe.binding.GEMM_DOWN):
-        shapes = {fe.binding.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities}
+        shapes = {fe.binding.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities
+                  if not any(fe.binding.feplb_grouped_ffn_tall_rows(gemm, out, c, d, f, offsets) for out in (0, 1))}
         assert {128, 256} <= shapes and (64 in shapes or copies > 1)
     X, Xp, order, off = X.to(DEV), Xp.to(DEV), order.to(DEV), torch.from_numpy(offsets).to(DEV)
     for R_cap in capacities:
@@ -469,7 +470,7 @@ def test_grouped_ffn_repeatable_over_random_shapes():
 @pytest.mark.parametrize("row_tiles", [32, 33, 35, 40, 41])
 def test_grouped_ffn_leftover_tiles_in_quarters(row_tiles):
     # Up to 64 tiles of 256 x 256 beyond whole rounds of 256 are computed as quarters: row_tiles x 8 column tiles are 256, 264, 280
-    # and 320 tiles, the last eight in part empty quarters, and 328, which stay whole.  Gate/up: the bytes of the 128-row tiles that another
+    # and 320 tiles, the last eight in part empty quarters, and 328, which stay whole.  Gate/up: the bytes of the 128-row or tall tiles that another
     # capacity takes, also for the kept derivatives.  Down: fp32 sums of 1024 products against float64, 1024 * 2^-24 of the
     # magnitudes' sum at most and far less than that in the root mean square.
     d, f, caps = 2048, 1024, (row_tiles * 256 - 187, 16000)
@@ -478,6 +479,8 @@ def test_grouped_ffn_leftover_tiles_in_quarters(row_tiles):
     B, R, G = fe.binding, sum(sizes), 3
     assert [B.feplb_grouped_ffn_tile_rows(B.GEMM_GATE_UP, c, G, d, f) for c in caps] == [128, 256]
     assert B.feplb_grouped_ffn_tile_rows(B.GEMM_DOWN, caps[1], G, d, f) == 256
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    assert not any(B.feplb_grouped_ffn_tall_rows(gemm, out, caps[1], d, f, offsets) for gemm, out in ((B.GEMM_GATE_UP, 1), (B.GEMM_DOWN, B.F32)))
     gen = torch.Generator(device=DEV).manual_seed(row_tiles)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)   # noqa: E731
     off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)).to(DEV)
@@ -504,44 +507,50 @@ def test_grouped_ffn_leftover_tiles_in_quarters(row_tiles):
         lo += n
 
 
-@pytest.mark.parametrize("sizes", [[2], [84, 128, 70, 606, 3, 4, 240], [64, 384, 512, 9, 15, 65, 66], [195, 3, 213, 257, 15, 314, 65, 490, 449],
-                                   [257, 37, 111, 56, 65, 261, 321, 641, 623, 124], [393, 66, 257, 128, 63, 128, 334, 31, 138, 450, 65, 646],
-                                   [69, 575, 65, 249, 298, 413, 690, 41, 82, 64, 418, 146, 585, 128, 256, 384, 30, 7, 287, 121, 193, 138],
-                                   [355, 24, 449, 383, 321, 321, 384, 319, 43, 210, 63, 129, 380, 255, 128, 384, 577, 13, 177, 13, 348, 192],
-                                   [448, 16, 513, 127, 127, 641, 63, 193, 64, 703, 321, 64, 64, 382, 192, 676, 448, 61, 19, 576, 105]])
-def test_grouped_ffn_tall_tiles_of_every_height(sizes):
+@pytest.mark.parametrize("case", range(len(TALL_CASES)))
+def test_grouped_ffn_tall_tiles_of_every_height(case):
     # Tall tiles: the height (up to 2 to 5 blocks of 64 rows) comes from the groups' rows on the device, and left-over tiles run whole, as halves
-    # or as quarters.  These groups take heights 2 to 5 and all three, in less than a round and in more, with rows at the edges of the
-    # blocks, at two capacities that allow different heights.  A group alone, in a buffer of its own, runs in tiles of 64 or 128 rows;
-    # every element is the same chain of MFMAs, so the bytes must be equal.
-    d, f, G, R, B = 2048, 1536, len(sizes), sum(sizes), fe.binding
-    say(f"ffn tall tiles sizes={sizes}")
+    # or as quarters; what TALL_CASES covers is held by a host test.  A group alone, in a buffer of its own, runs in tiles of 64 or 128 rows;
+    # every element is the same chain of MFMAs, so the bytes must be equal.  Gate/up runs with the derivatives kept, and without them on
+    # rows that it gathers.
+    d, f, cap, sizes = TALL_CASES[case]
+    G, R, B = len(sizes), sum(sizes), fe.binding
+    say(f"ffn tall tiles d={d} f={f} cap={cap} sizes={sizes}")
     gen = torch.Generator(device=DEV).manual_seed(R)
     rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)   # noqa: E731
     offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     off = torch.from_numpy(offsets).to(DEV)
+    tall = {B.feplb_grouped_ffn_tall_rows(gemm, out, cap, d, f, offsets) > 0 for gemm in (B.GEMM_GATE_UP, B.GEMM_DOWN, B.GEMM_DXP) for out in (0, 1)}
+    assert True in tall
     X, W = rnd(R, d), [[0.02 * rnd(*sh) for _ in range(3)] * (G // 3 + 1) for sh in ((d, f), (d, f), (f, d))]
+    order = torch.from_numpy(np.random.default_rng(R).permutation(R).astype(np.int32)).to(DEV)
+    tokens = torch.empty_like(X)
+    tokens[order.long()] = X
     H, Yp, AB = torch.zeros((R, f), dtype=torch.bfloat16, device=DEV), torch.zeros((R, d), device=DEV), torch.zeros((R, 2 * f), dtype=torch.bfloat16, device=DEV)
     dXp = torch.zeros((R, d), device=DEV)
     for g, n in enumerate(sizes):
-        assert all(B.feplb_grouped_ffn_tile_rows(gemm, n, 1, d, f) <= 128 for gemm in (B.GEMM_GATE_UP, B.GEMM_DOWN, B.GEMM_DXP))
+        for gemm in (B.GEMM_GATE_UP, B.GEMM_DOWN, B.GEMM_DXP):
+            assert B.feplb_grouped_ffn_tile_rows(gemm, n, 1, d, f) <= 128
+            assert not any(B.feplb_grouped_ffn_tall_rows(gemm, out, n, d, f, [0, n]) for out in (0, 1))
         rows, one = slice(offsets[g], offsets[g + 1]), torch.tensor([0, n], dtype=torch.int32, device=DEV)
         ws = [[w[g]] for w in W]
-        B.feplb_grouped_ffn(X[rows], one, 0, 1, d, f, *ws, H[rows], Yp[rows], AB=AB[rows])
-        B.feplb_grouped_ffn_backward(None, one, 0, 1, d, f, *ws, H[rows], AB[rows].clone(), X[rows], dXp[rows], *[[None]] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
-    for cap in (8000, 16000):
-        Xp = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
-        Xp[:R] = X
-        for dtype in (torch.float32, torch.bfloat16):
-            out = [torch.full((cap, c), 512.0, dtype=t, device=DEV) for c, t in ((f, torch.bfloat16), (2 * f, torch.bfloat16), (d, dtype), (d, dtype))]
-            B.feplb_grouped_ffn(Xp, off, 0, G, d, f, *W, out[0], out[2], AB=out[1] if dtype == torch.float32 else None)
-            assert dtype != torch.float32 or torch.equal(out[1][:R], AB)
-            out[1][:R] = AB
-            dAB = out[1].clone()
-            B.feplb_grouped_ffn_backward(None, off, 0, G, d, f, *W, out[0], dAB, Xp, out[3], *[[None] * G] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
-            torch.cuda.synchronize()
-            for got, want in zip(out, (H, AB, Yp, dXp)):
-                assert torch.equal(got[:R], want.to(got.dtype)) and (got[R:] == 512.0).all()
+        if n:
+            B.feplb_grouped_ffn(X[rows], one, 0, 1, d, f, *ws, H[rows], Yp[rows], AB=AB[rows])
+            B.feplb_grouped_ffn_backward(None, one, 0, 1, d, f, *ws, H[rows], AB[rows].clone(), X[rows], dXp[rows], *[[None]] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
+    W = [w[:G] for w in W]
+    Xp = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    Xp[:R] = X
+    for dtype in (torch.float32, torch.bfloat16):
+        keep = dtype == torch.float32
+        out = [torch.full((cap, c), 512.0, dtype=t, device=DEV) for c, t in ((f, torch.bfloat16), (2 * f, torch.bfloat16), (d, dtype), (d, dtype))]
+        B.feplb_grouped_ffn(Xp if keep else tokens, off, 0, G, d, f, *W, out[0], out[2], **(dict(AB=out[1]) if keep else dict(row_src=order, k=1)))
+        assert not keep or torch.equal(out[1][:R], AB)
+        out[1][:R] = AB
+        dAB = out[1].clone()
+        B.feplb_grouped_ffn_backward(None, off, 0, G, d, f, *W, out[0], dAB, Xp, out[3], *[[None] * G] * 3, phases=B.BWD_DGRAD | B.BWD_DIRECT)
+        torch.cuda.synchronize()
+        for got, want in zip(out, (H, AB, Yp, dXp)):
+            assert torch.equal(got[:R], want.to(got.dtype)) and (got[R:] == 512.0).all()
 
 
 def test_grouped_ffn_gathering_rows_equals_reading_the_permuted_copy():

@@ -11,6 +11,7 @@ import pytest
 import paper_2604_19654_amd as fe
 from oracle import feplb_oracle as orc
 from tests.test_oracle_pins import read_golden, random_plan_case
+from tests.util import TALL_CASES, how_tall_tiles_run
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -170,6 +171,24 @@ def test_tall_tiles_are_taken_where_they_were_measured_to_gain():
             rows = [R_cap * g // ng for g in range(ng + 1)]
             assert (in_tall < before) == want
             assert (B.feplb_grouped_ffn_tall_rows(gemm, out, R_cap, d, f, rows) > 0) == want, (gemm, out, R_cap, ng, d, f)
+
+
+def test_tall_cases_cover_every_product_height_and_rest():
+    # Which tall tiles the GPU tests' list runs, by the library's own choice: every product (gate/up without and with AB, down and dXp in either type)
+    # in heights of 128 to 320 rows, left-over tiles of every kind, whole rounds, and more groups than the 64 lanes that hold the first of them.
+    B = fe.binding
+    products = [(B.GEMM_GATE_UP, 0), (B.GEMM_GATE_UP, 1), (B.GEMM_DOWN, B.F32), (B.GEMM_DOWN, B.BF16), (B.GEMM_DXP, B.F32), (B.GEMM_DXP, B.BF16)]
+    seen = {product: set() for product in products}
+    for d, f, R_cap, sizes in TALL_CASES:
+        offsets = np.concatenate([[0], np.cumsum(sizes)])
+        assert offsets[-1] <= R_cap
+        for gemm, out in products:
+            height = B.feplb_grouped_ffn_tall_rows(gemm, out, R_cap, d, f, offsets)
+            if height:
+                rounds, rest = how_tall_tiles_run(sizes, height, 2 * f if gemm == B.GEMM_GATE_UP else d)
+                seen[gemm, out] |= {height, rest} | ({"rounds"} if rounds else set()) | ({"many groups"} if len(sizes) > 64 else set())
+    for product, got in seen.items():
+        assert got >= {128, 192, 256, 320, "whole", "halves", "quarters", "rounds", "many groups"}, (product, got)
 
 
 def as_tuples(moves):

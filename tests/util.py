@@ -140,12 +140,52 @@ def layer_tokens_with_format_bound(orc, x_rows, ids_rows, w_rows, keep_rows, wei
     return out, format_bound(out, var, output_bf16=True)
 
 
+def _ffn_gemm_constant(name):
+    with open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_19654_amd", "csrc",
+                           "ffn_gemm.hip")) as fh:
+        return int(re.search(rf"{name} = (\d+);", fh.read()).group(1))
+
+
 def how_256_row_tiles_run(sizes, columns):
     """What a grouped GEMM in 256 x 256 tiles makes of groups of these sizes and a weight of `columns` columns: "whole" tiles,
     "quarters" of 128 x 128, or "both" (whole rounds of 256 tiles, and so few left over that they run as quarters)."""
-    with open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_19654_amd", "csrc",
-                           "ffn_gemm.hip")) as fh:
-        most = int(re.search(r"QUARTERS_MAX = (\d+);", fh.read()).group(1))
+    most = _ffn_gemm_constant("QUARTERS_MAX")
     tiles = sum(-(-n // 256) for n in sizes) * (columns // 256)
     rest = tiles % 256
     return "whole" if rest == 0 or rest > most else "quarters" if rest == tiles else "both"
+
+
+def how_tall_tiles_run(sizes, height, columns):
+    """What a grouped GEMM in tall tiles of up to `height` rows makes of groups of these sizes: whole rounds of 256 tiles, and how the tiles left over
+    run: "whole", as "halves" of their columns, as "quarters", or "none"."""
+    tiles = 0
+    for n in sizes:
+        blocks = -(-n // 64)
+        if blocks:
+            split = -(-blocks // (height // 64))
+            tiles += -(-blocks // -(-blocks // split))   # all of one height but the last
+    rounds, rest = divmod(tiles * (columns // 256), 256)
+    return rounds, ("none" if rest == 0 else "quarters" if rest <= _ffn_gemm_constant("QUARTERS_MAX") else
+                    "halves" if rest <= _ffn_gemm_constant("HALVES_MAX") else "whole")
+
+
+def _spread(n, sizes):
+    return [sizes[i * 7919 // 13 % len(sizes)] for i in range(n)]
+
+
+# d, f, row capacity and group sizes, at the edges of the tall tiles' blocks of 64 rows, at which the grouped GEMMs run in tall tiles: together every
+# product in every height, with left-over tiles of every kind, in less than a round and in more, and with more groups than a wavefront has lanes.  A
+# host test holds the list to that.
+TALL_CASES = [
+    (2048, 1536, 5500, [2]),
+    (2048, 2048, 24000, [84, 128, 70, 606, 3, 4, 240]),
+    (3072, 1536, 3000, [84, 128, 70, 606, 3, 4, 240]),
+    (2048, 2048, 4000, [195, 3, 213, 257, 15, 314, 65, 490, 449]),
+    (3072, 1536, 3000, [257, 37, 111, 56, 65, 261, 321, 641, 623, 124]),
+    (2048, 2048, 4000, [257, 37, 111, 56, 65, 261, 321, 641, 623, 124]),
+    (3072, 1536, 4000, [393, 66, 257, 128, 63, 128, 334, 31, 138, 450, 65, 646]),
+    (3072, 1024, 6000, [355, 24, 449, 383, 321, 321, 384, 319, 43, 210, 63, 129, 380, 255, 128, 384, 577, 13, 177, 13, 348, 192]),
+    (2048, 2048, 5500, _spread(128, [0, 1, 2, 17, 33, 63, 64, 65])),
+    (3072, 1024, 9500, _spread(128, [0, 1, 2, 17, 33, 63, 64, 65])),
+    (2048, 2048, 16000, _spread(100, [1, 2, 3, 15, 16, 17, 31, 33, 63, 64, 65, 66, 127, 128, 129, 191, 192, 193, 255, 256, 257, 319, 320, 321])),
+]
