@@ -154,10 +154,10 @@ def test_grouped_ffn_backward_parity(sizes, d, f, dxp_dtype):
 
 @pytest.mark.parametrize("d,f,copies,large,capacities", [(512, 256, 1, "quarters", (8000, 16000, 100000)),
                                                          (256, 768, 1, "quarters", (8000, 16000, 100000)),
-                                                         (1024, 1024, 1, "whole", (5000, 8000)), (1024, 1024, 4, "both", (24000,))])
+                                                         (1024, 1024, 1, "whole", (5000, 8000, 24000)), (1024, 1024, 4, "both", (24000,))])
 def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d, f, copies, large, capacities):
     # The tile shape is picked from the row capacity: each of the two GEMMs takes 64-, 128- and 256-row tiles at one of the
-    # capacities here (the largest batch 128- and 256-row tiles).  Few tiles of 256 rows, or few beyond whole rounds, run as quarters; `large` says
+    # capacities here (the largest batch 128- and 256-row tiles, its dXp tall and 256-row tiles).  Few tiles of 256 rows, or few beyond whole rounds, run as quarters; `large` says
     # which of them a set of sizes and widths has.  The input gradients read the weights themselves, or transposes left in WT by an earlier
     # call where none are given.  Every element is the same chain of MFMAs on all ways, so the bytes must be equal.  Group sizes lie at the
     # edges of the tiles and of their 32-row blocks.
@@ -174,8 +174,9 @@ def test_input_gradients_do_not_depend_on_the_tile_shape_or_on_who_transposes(d,
     nothing = [[None] * G for _ in range(3)]
     capacities = (R, *capacities)
     for gemm in (B.GEMM_DH, B.GEMM_DXP):
-        shapes = {B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f) for c in capacities}
-        assert {128, 256} <= shapes and (64 in shapes or copies > 1)
+        shapes = {"tall" if B.feplb_grouped_ffn_tall_rows(gemm, B.F32, c, d, f, r["offsets"]) else B.feplb_grouped_ffn_tile_rows(gemm, c, G, d, f)
+                  for c in capacities}
+        assert ({64, 128, 256} if copies == 1 else {128, 256} if gemm == B.GEMM_DH else {"tall", 256}) <= shapes
     for R_cap in capacities:
         H = torch.zeros((R_cap, f), dtype=torch.bfloat16, device=DEV)
         dYp = torch.full((R_cap, d), float("nan"), dtype=torch.bfloat16, device=DEV)
