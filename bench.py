@@ -34,13 +34,13 @@ HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
 TRAFFIC_SOURCES = ("ffn.hip", "ffn_gemm.hip", "ffn_down.hip", "tall_gemm.h", "panel_gemm.h", "gemm_device.h", "common.h")
 MEASURED_TRAFFIC = {
     "C4": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "a49963998d8c63496037a8fb90e715dcfa2363ec34a8b7b9789dd395b154569a",
-           "gate_up": {"read": 2756624 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
-           "down": {"read": 1273487 * 1024 * 2.0, "written": 1573215 * 1024}},
+           "sources_sha256": "56fa952720de8e333fcb99314622bee967c95271dc6e809ba95884970a411bf4",
+           "gate_up": {"read": 2790099 * 1024 * 2.0, "written": 262140 * 1024},       # FETCH_SIZE KiB x 2.000, WRITE_SIZE KiB
+           "down": {"read": 1288113 * 1024 * 2.0, "written": 1573158 * 1024}},
     "C3": {"profile": "profiles/hbm_traffic_C4_C3_pmc.md",
-           "sources_sha256": "a49963998d8c63496037a8fb90e715dcfa2363ec34a8b7b9789dd395b154569a",
-           "gate_up": {"read": 555189 * 1024 * 2.0, "written": 61188 * 1024},
-           "down": {"read": 263465 * 1024 * 2.0, "written": 326616 * 1024}},
+           "sources_sha256": "56fa952720de8e333fcb99314622bee967c95271dc6e809ba95884970a411bf4",
+           "gate_up": {"read": 554488 * 1024 * 2.0, "written": 61188 * 1024},
+           "down": {"read": 244260 * 1024 * 2.0, "written": 327044 * 1024}},
 }
 METRIC = "grouped-FFN TFLOP/s & % bf16 MFMA peak per rank share; permute/combine GB/s"
 

@@ -34,7 +34,7 @@ using namespace feplb::dev;
 // such rounds, and halves of 128 x 256 take 0.8 of a whole tile's time.  T = 8192, 20396 rows in 8 groups, d = 4096, f = 1536, whose
 // gate/up is 4 rounds and 8 tiles: 766 -> 728 us a layer step; 298 drawn forward steps 1.01x on average, up to 1.75x.
 constexpr int QUARTERS_MAX = 64;
-constexpr int HALVES_MAX = 128;   // tall tiles: from 65 left-over ones on halves of 128 columns, 0.56 of a whole tile's time
+constexpr int HALVES_MAX = 128;   // tall tiles: from 65 left-over ones on halves of 128 columns, 0.6 of a whole tile's time
 
 struct Tile {
   int g, row0, rows, nt;   // group, first row, number of rows, column
@@ -480,22 +480,22 @@ hipError_t launch_tall(const feplb::GroupedGemm& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps, some 3500 launches drawn over the layer's
+// Does a launch that pick_shape gives to shape 0 or 1 run in tall tiles instead?  Measured inside layer steps, some 4500 launches drawn over the layer's
 // sizes, each in that shape and in tall tiles at the height that pick_height takes: geometric mean of the gain, and its first and last tenth.  `tiles`
-// are those of the shape, and like it estimated from the row capacity; a fifth of the launches had rows for a part of it only.
+// are those of the shape, and like it estimated from the row capacity; a fourth of the launches had rows for a part of it only.
 //   In the place of 256 x 256, plain, K >= 1280:
-//     more than half a round of 256 and up to one, which lower tiles fill better: 1.040 (0.92, 1.22).  Rows for a quarter of a round, which run as
+//     more than half a round of 256 and up to one, which lower tiles fill better: 1.043 (0.93, 1.21).  Rows for a quarter of a round, which run as
 //     quarters of 256 x 256, lose (capacity for 178 tiles, rows for 60: 13 -> 18 us), rows for half of one gain more (for 163 and 60 % of them: 41 -> 29).
 //     K = 768 to 1279 1.037 (0.86, 1.23), left out for its first tenth;
-//     two rounds and a rest, more than quarters take, that tiles of 320 rows save: 1.037 (0.94, 1.15), e.g. 16 groups of about 512 rows, d = 4096,
-//     f = 1536, down 130 -> 113 us, dXp 221 -> 189.  From 577 to 656 tiles, where the gain crosses 1: up to 576 0.970, 657 to 832 0.962;
-//     more tiles: K < 2048 0.979 (0.93, 1.04), up to four columns of tiles 0.962 (0.92, 1.03; few tiles share a row of A, which then comes from memory);
+//     two rounds and a rest, more than quarters take, that tiles of 320 rows save, 577 to 656 tiles: 1.034 (0.95, 1.15), e.g. 16 groups of about 512 rows,
+//     d = 4096, f = 1536, down 126 -> 111 us, dXp 214 -> 193.  Fewer 0.986 (0.92, 1.05);
+//     more tiles: K < 2048 0.984 (0.93, 1.05), up to four columns of tiles 0.967 (0.92, 1.03; few tiles share a row of A, which then comes from memory);
 //     other 1.001 (0.95, 1.05), taken, since copies beside such a launch find CUs free sooner (replicas' weights staged beside it, 6214 rows,
 //     d = 6144, f = 2048: a layer step of 645 to 658 us instead of 673 to 677).
-//   Gate/up, more than eight rounds: K < 2048 0.88, to 3071 0.951, to 4095 0.994, to 6143 1.009, from there on 1.012 (0.96, 1.05; 93580 rows,
-//     d = 6144, f = 2048 3300 -> 3170 us); fewer rounds, K >= 6144 1.019 (0.92, 1.16).
-//   In the place of 128 x 256 where those would be more than one to a CU, plain, K >= 2048: 1.100 (0.96, 1.29), smaller K 0.986, up to one to a CU 0.991;
-//   gate/up, K >= 3072: 1.077 (0.94, 1.30); K = 2048 to 3071, a rest of up to a quarter after a round of 512 1.039 (0.90, 1.20), else 0.973; smaller K 0.905.
+//   Gate/up, more than eight rounds: K < 2048 0.876, to 3071 0.951, to 4095 0.994, to 6143 1.009, from there on, rows for the whole capacity, 1.019 (80387
+//     rows, d = 7168, f = 2048 3296 -> 3192 us), for a part of it 0.984; fewer rounds, K >= 6144 1.019 (0.92, 1.16).
+//   In the place of 128 x 256 where those would be more than one to a CU, plain, K >= 2048: 1.099 (0.95, 1.30), smaller K 0.986, up to one to a CU 0.991;
+//   gate/up, K >= 3072: 1.074 (0.93, 1.30); K = 2048 to 3071, a rest of up to a quarter after a round of 512 1.033 (0.89, 1.21), else 0.973; smaller K 0.905.
 bool use_tall(const feplb::GroupedGemm& a, int mode, int weight_cols, int shape) {
   const double tiles = ((double)a.R_cap / SHAPES[shape].bm + 0.5 * a.ng) * (weight_cols / 256);
   if (mode == 2 || shape == 2 || !(a.row_src || feplb::rows_fit_32_bits(256, a.lda))) return false;

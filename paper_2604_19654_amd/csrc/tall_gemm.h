@@ -1,12 +1,16 @@
 // The grouped GEMMs' loop for tall tiles: up to 320 rows x 256 columns by four wavefronts, one per SIMD.
 //
 // A wave multiplies up to 160 x 128 (5 row blocks of 32), so that an operand read from LDS is used more often than by the eight
-// wavefronts of panel_gemm.h.  256 tiles at once take 4.8 us per 1000 k for every 64 rows of height and 1.5 (from the caches) to 3.5 for
-// the weights, so that heights can be chosen to fill whole rounds of the 256 CUs.  Against 256 x 256 by eight wavefronts: 93580 rows,
-// d = 6144, f = 2048 gate/up 3135 -> 3112 us, down 1874 -> 1807, dXp 3318 -> 3222; 16 groups of 495 to 573 rows, d = 4096, f = 1536 (two tiles
-// of five or four blocks each in the place of two or three of 256 rows) down 117 -> 99 us, dXp 217 -> 194.  What bounds it is the power limit: 256 x 256
+// wavefronts of panel_gemm.h.  Inside layer steps a round of 256 tiles takes 6 to 8 us per 1000 k and 3.2 to 3.7 more for every 64 rows of height
+// (tall_heights in ffn_gemm.hip), so that heights can be chosen to fill whole rounds of the 256 CUs: 16 groups of about 512 rows, d = 4096,
+// f = 1536 (two tiles of five or four blocks each in the place of two or three of 256 rows), profiled in a training step: down 126 -> 111 us,
+// dXp 214 -> 193.  Over many rounds, back to back, against 256 x 256 by eight wavefronts: 93580 rows, d = 6144, f = 2048 gate/up 3135 -> 3112 us,
+// down 1874 -> 1807, dXp 3318 -> 3222.  What bounds it is the power limit: 256 x 256
 // by four wavefronts keeps the matrix pipes busy 82 % of the time at 1.82 GHz where eight do 83 % at 1.69 GHz (gate/up of the large shape, profiled), with a
 // third fewer LDS reads; back to back, hot, that is 1 to 3 %.
+//
+// The rings of four wavefronts hold fewer k ahead (two tiles of A, four half tiles of the weights), so launches whose operands come from memory and that are
+// short (small K), read a row of A for few columns, or have few tiles are faster in the other shapes (use_tall in ffn_gemm.hip has both sides).
 //
 // With one wave per SIMD nothing hides behind another wave's MFMAs: the order of MFMAs, LDS reads and loads is fixed in the source, a
 // fragment read behind every other MFMA and a load behind every fourth (reads ahead of a slice's MFMAs, as the compiler places them: 7 % slower).
